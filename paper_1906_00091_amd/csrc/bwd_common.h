@@ -91,7 +91,7 @@ constexpr int kRouteHugeInPlace = 7;            // runs above kHugeRun summed by
 // Workspace layout (all offsets 256-byte aligned)
 struct WsLayout {
   size_t keys[2], vals[2];   // uint32[nnz] ping-pong: row ids / bag ids
-  size_t hist;               // uint32[kMaxBuckets * nt_max]: per-tile digit counts / offsets
+  size_t hist;               // uint32[nt_max][1 << top_bits] (room for kMaxBuckets): per-tile digit counts / offsets
   size_t bucket_start;       // uint32[K * kMaxBuckets + 1]
   size_t tile_heads;         // uint32[nt_max + 1]   (export only)
   size_t seg_start;          // uint32[nnz + 1]      (export only; a weighted update keeps its nnz
@@ -182,6 +182,7 @@ struct GroupArgs {            // everything the grouping kernels need
   uint32_t* keys[2];
   uint32_t* vals[2];
   uint32_t* hist;
+  uint32_t* digit_total;      // [K << top_bits] pairs per bucket, between the column scan and the scatter
   uint32_t* bucket_start;
   uint32_t* tile_heads;
   uint32_t* seg_start;
@@ -536,13 +537,16 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   // time and -21 % fetched bytes; 0.5 MB slices +8 % time), because a die then has whole tables and tables
   // differ in work: with 4 MB slices and tables of 100 to 10 M rows the kernel lost 15 %.
   g.by_die = (int64_t)s->B * s->d * 4 >= (6 << 20) ? 1 : 0;
-  g.fused_scan = L.nt_max <= kFusedScanMaxTiles ? 1 : 0;
+  // the totals of the column scan lie in pair buffer 0, idle until the reduce; the batch has more lookups than
+  // buckets unless it has more tables than lookups, whose few tiles each the scatter may as well add up itself
+  g.fused_scan = L.nt_max <= kFusedScanMaxTiles || ((int64_t)s->K << tb) > s->nnz_total ? 1 : 0;
   g.no_tail = s->nnz_total <= kSmallBatch ? 1 : 0;
   for (int i = 0; i < 2; ++i) {
     g.keys[i] = reinterpret_cast<uint32_t*>(base + L.keys[i]);
     g.vals[i] = reinterpret_cast<uint32_t*>(base + L.vals[i]);
   }
   g.hist = reinterpret_cast<uint32_t*>(base + L.hist);
+  g.digit_total = reinterpret_cast<uint32_t*>(base + L.keys[0]);
   g.bucket_start = reinterpret_cast<uint32_t*>(base + L.bucket_start);
   g.tile_heads = reinterpret_cast<uint32_t*>(base + L.tile_heads);
   g.seg_start = reinterpret_cast<uint32_t*>(base + L.seg_start);

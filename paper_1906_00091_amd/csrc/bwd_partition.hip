@@ -3,6 +3,12 @@
 
 namespace dlrm {
 
+// A bucket of n pairs goes to the list that the first workgroups of the reduce kernel take, if it is heavy.
+__device__ inline void list_if_heavy(const GroupArgs& a, int k, int dg, uint32_t n) {
+  if (n > a.big) a.over_list[atomicAdd(a.list_cnt, 1u)] = (uint32_t)((k << a.top_bits) + dg);
+  if (n > (uint32_t)kBktCap) atomicAdd(a.over_cnt, 1u);
+}
+
 // --- 1. per-tile histogram of the partition digit ----------------------------------
 template <typename IT>
 __global__ __launch_bounds__(kThreads) void bucket_hist_kernel(GroupArgs a) {
@@ -19,7 +25,7 @@ __global__ __launch_bounds__(kThreads) void bucket_hist_kernel(GroupArgs a) {
   for (int i = threadIdx.x; i < ti.count; i += kThreads)
     atomicAdd(&h[((uint32_t)idx[i] >> shift) & mask], 1u);
   __syncthreads();
-  for (int i = threadIdx.x; i < nb; i += kThreads) a.hist[(size_t)i * a.nt_max + blockIdx.x] = h[i];
+  for (int i = threadIdx.x; i < nb; i += kThreads) a.hist[(size_t)blockIdx.x * nb + i] = h[i];
   if (blockIdx.x == 0 && threadIdx.x == 0) {  // consumed by later launches of the same call
     *a.over_cnt = 0u;
     *a.list_cnt = 0u;
@@ -28,69 +34,57 @@ __global__ __launch_bounds__(kThreads) void bucket_hist_kernel(GroupArgs a) {
   }
 }
 
-// --- 2. per-table scan (large batches only): counts -> destination offsets ------------
-// One workgroup per table walks (digit, tile) in digit-major order with a running carry
-// that starts at the table's slice, so every table is scattered inside its own slice.
-// (256 threads: a 1024-thread workgroup is not placed on a compute unit while the forward kernel,
-// which runs beside this one, keeps filling every freed slot with its own 256-thread workgroups --
-// measured: the scan then only starts when the forward kernel drains)
+// --- 2. column scan (large batches only): counts -> pairs of the digit in earlier tiles ------
+// hist[tile][digit] becomes the number of pairs of that digit in the table's earlier tiles, in
+// place, and the digit's total goes to digit_total; the scatter turns totals into bucket starts
+// itself.  A workgroup owns kScanDigits digits of one table and walks the table's tiles
+// kScanSegs * kScanItems at a time: the loads of a round are in flight together, consecutive
+// threads read consecutive digits of a tile.  Bound by the latency of a round (256 tiles).  The step
+// it serves, before with one workgroup per table walking all of its (digit, tile) pairs / now:
+// 4 tables of 164 K lookups 528 / 447 us, 64 tables of 524 K lookups 3016 / 2905 us, 8 tables of
+// 103 K lookups with Adagrad 291 / 264 us.
+constexpr int kScanDigits = 16, kScanSegs = kThreads / kScanDigits, kScanItems = 16;
 __global__ __launch_bounds__(kThreads) void bucket_scan_kernel(GroupArgs a) {
-  __shared__ uint32_t smem[kThreads / DLRM_WAVE + 1];
-  const int k = blockIdx.x;
+  __shared__ uint32_t part[kScanSegs][kScanDigits];
+  __shared__ uint32_t smem[kNW + 1];
+  const int k = blockIdx.y, nb = 1 << a.top_bits;
+  const int64_t tsize = (int64_t)1 << a.tile_shift;
   // first tile of table k = tiles of all earlier tables
-  uint32_t t0 = 0;
-  const int64_t tile = (int64_t)1 << a.tile_shift;
-  for (int j = 0; j < k; ++j) t0 += (uint32_t)((a.tbl_off[j + 1] - a.tbl_off[j] + tile - 1) >> a.tile_shift);
-  const int nt = (int)((a.tbl_off[k + 1] - a.tbl_off[k] + tile - 1) >> a.tile_shift);
-  const int nb = 1 << a.top_bits;
-  uint32_t carry = (uint32_t)a.tbl_off[k];
-  if (nt <= 0) {
-    for (int i = threadIdx.x; i < nb; i += kThreads) a.bucket_start[(size_t)k * nb + i] = carry;
-    return;
-  }
-  // kScanItems consecutive entries per thread and round: their loads are in flight together and a
-  // round costs one workgroup scan (the kernel shares the machine with the forward pass, where every
-  // dependent round trip to memory is several microseconds)
-  constexpr int kScanItems = 16;
-  const uint32_t n = (uint32_t)nt * (uint32_t)nb;   // < 2^31: nt <= nnz / tile + 1 (<= 1024 + 1 with small tiles), nb <= 1024
-  for (uint32_t e0 = 0; e0 < n; e0 += kThreads * kScanItems) {
-    uint32_t v[kScanItems], digit[kScanItems], t[kScanItems];
-    size_t addr[kScanItems];
-    uint32_t sum = 0;
+  uint32_t mine = 0, t0;
+  for (int j = threadIdx.x; j < k; j += kThreads)
+    mine += (uint32_t)((a.tbl_off[j + 1] - a.tbl_off[j] + tsize - 1) >> a.tile_shift);
+  block_exclusive_scan<kThreads>(mine, smem, &t0);
+  const int nt = (int)((a.tbl_off[k + 1] - a.tbl_off[k] + tsize - 1) >> a.tile_shift);
+  const int dl = threadIdx.x % kScanDigits, seg = threadIdx.x / kScanDigits;
+  const int dg = blockIdx.x * kScanDigits + dl;
+  uint32_t* col = a.hist + (size_t)t0 * nb + dg;
+  uint32_t carry = 0;
+  for (int r0 = 0; r0 < nt; r0 += kScanSegs * kScanItems) {   // uniform
+    const int first = r0 + seg * kScanItems;
+    uint32_t v[kScanItems], sum = 0;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-      const uint32_t e = e0 + threadIdx.x * kScanItems + j;
-      v[j] = 0;
-      digit[j] = t[j] = 0;
-      addr[j] = 0;
-      if (e < n) {
-        digit[j] = e / (uint32_t)nt;
-        t[j] = e - digit[j] * (uint32_t)nt;
-        addr[j] = (size_t)digit[j] * a.nt_max + t0 + t[j];
-        v[j] = a.hist[addr[j]];
-      }
-    }
+    for (int j = 0; j < kScanItems; ++j) v[j] = (dg < nb && first + j < nt) ? col[(size_t)(first + j) * nb] : 0u;
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) sum += v[j];
-    uint32_t total;
-    uint32_t run = carry + block_exclusive_scan<kThreads>(sum, smem, &total);
+    __syncthreads();   // the previous round's sums have been read
+    part[seg][dl] = sum;
+    __syncthreads();
+    uint32_t run = carry;
+#pragma unroll
+    for (int s = 0; s < kScanSegs; ++s) {
+      const uint32_t c = part[s][dl];
+      run += s < seg ? c : 0u;
+      carry += c;
+    }
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
-      const uint32_t e = e0 + threadIdx.x * kScanItems + j;
-      if (e < n) {
-        a.hist[addr[j]] = run;
-        if (t[j] == 0) a.bucket_start[(size_t)k * nb + digit[j]] = run;
-        run += v[j];
-      }
+      if (dg < nb && first + j < nt) col[(size_t)(first + j) * nb] = run;
+      run += v[j];
     }
-    carry += total;
   }
-  __syncthreads();  // this workgroup's bucket_start writes are visible to it
-  for (int dg = threadIdx.x; dg < nb; dg += kThreads) {
-    const uint32_t st = a.bucket_start[(size_t)k * nb + dg];
-    const uint32_t en = dg + 1 < nb ? a.bucket_start[(size_t)k * nb + dg + 1] : (uint32_t)a.tbl_off[k + 1];
-    if (en - st > a.big) a.over_list[atomicAdd(a.list_cnt, 1u)] = (uint32_t)(k * nb + dg);
-    if (en - st > (uint32_t)kBktCap) atomicAdd(a.over_cnt, 1u);
+  if (seg == 0 && dg < nb && nt > 0) {
+    a.digit_total[(size_t)k * nb + dg] = carry;
+    list_if_heavy(a, k, dg, carry);
   }
 }
 
@@ -126,35 +120,73 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(GroupArgs a) {
     key[j] = ok[j] ? (uint32_t)kin[li] : 0xFFFFFFFFu;
     dg[j] = (key[j] >> shift) & mask;
   }
+  // per digit: pairs of the digit in the table (stot) and in the table's earlier tiles (sbef)
+  uint32_t* stot = skey;
+  uint32_t* sbef = sval;
+  if (a.fused_scan) {
+    // Few tiles: every workgroup adds up the table's raw tile counts (a launch less).  nb / 4 threads
+    // take 4 consecutive digits each; with fewer than 1024 digits up to kScanSegs times as many threads
+    // split the tiles, so that 256 digits and 50 tiles are 13 dependent steps instead of 50.
+    const int quads = nb >= 4 ? nb >> 2 : 1;
+    const int segs = kThreads / quads < kScanSegs ? kThreads / quads : kScanSegs;
+    const int quad = tid % quads, seg = tid / quads;
+    const uint32_t* h0 = a.hist + (size_t)ti.t0 * nb;
+    uint32_t tt[4] = {0, 0, 0, 0}, bb[4] = {0, 0, 0, 0};
+    if (nb >= 4) {
+      for (int t = seg < segs ? seg : ti.nt; t < ti.nt; t += segs * 8) {
+        u32x4 c[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) {
+          const int tz = t + z * segs;
+          c[z] = *reinterpret_cast<const u32x4*>(h0 + (size_t)(tz < ti.nt ? tz : ti.nt - 1) * nb + quad * 4);
+        }
+#pragma unroll
+        for (int z = 0; z < 8; ++z) {
+          const int tz = t + z * segs;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            tt[q] += tz < ti.nt ? c[z][q] : 0u;
+            bb[q] += tz < ti.t ? c[z][q] : 0u;
+          }
+        }
+      }
+    } else {
+      for (int t = seg < segs ? seg : ti.nt; t < ti.nt; t += segs) {
+        for (int q = 0; q < nb; ++q) {
+          const uint32_t c = h0[(size_t)t * nb + q];
+          tt[q] += c;
+          bb[q] += t < ti.t ? c : 0u;
+        }
+      }
+    }
+    if (seg < segs) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        stot[(seg * quads + quad) * 4 + q] = tt[q];   // segs * quads * 4 <= 1024 words
+        sbef[(seg * quads + quad) * 4 + q] = bb[q];
+      }
+    }
+  }
   // thread t owns the partition digits t*kDPT .. t*kDPT + kDPT-1
   uint32_t goff[kDPT], before[kDPT], total[kDPT];
+  if (a.fused_scan) __syncthreads();
 #pragma unroll
   for (int q = 0; q < kDPT; ++q) {
     const int dgt = tid * kDPT + q;
-    goff[q] = before[q] = total[q] = 0;
+    before[q] = total[q] = 0;
     if (dgt >= nb) continue;
     if (a.fused_scan) {
-      const uint32_t* hrow = a.hist + (size_t)dgt * a.nt_max + ti.t0;
-      int t = 0;
-      for (; t + 8 <= ti.nt; t += 8) {
-        uint32_t c[8];
-#pragma unroll
-        for (int z = 0; z < 8; ++z) c[z] = hrow[t + z];
-#pragma unroll
-        for (int z = 0; z < 8; ++z) {
-          total[q] += c[z];
-          before[q] += t + z < ti.t ? c[z] : 0u;
-        }
-      }
-      for (; t < ti.nt; ++t) {
-        const uint32_t c = hrow[t];
-        total[q] += c;
-        before[q] += t < ti.t ? c : 0u;
+      const int row = nb >= 4 ? nb : 4, rows = kThreads * 4 / row < kScanSegs ? kThreads * 4 / row : kScanSegs;
+      for (int sg = 0; sg < rows; ++sg) {
+        total[q] += stot[sg * row + dgt];
+        before[q] += sbef[sg * row + dgt];
       }
     } else {
-      goff[q] = a.hist[(size_t)dgt * a.nt_max + blockIdx.x];
+      total[q] = a.digit_total[(size_t)ti.k * nb + dgt];
+      before[q] = a.hist[(size_t)blockIdx.x * nb + dgt];
     }
   }
+  if (a.fused_scan) __syncthreads();   // skey and sval are written again below
 
   // ---- bag of every position of the tile, from the offsets
   // b0 = the bag holding the tile's first position: last b with off[b] <= P0.
@@ -223,8 +255,7 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(GroupArgs a) {
   __syncthreads();
 
   // ---- destination offsets of this tile's digits
-  if (a.fused_scan) {
-    // few tiles: the raw counts of the table's tiles were summed above instead of a separate scan
+  {
     uint32_t sum = 0, all;
 #pragma unroll
     for (int q = 0; q < kDPT; ++q) sum += total[q];
@@ -235,8 +266,7 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(GroupArgs a) {
       goff[q] = (uint32_t)ti.tbl_start + base + before[q];
       if (ti.t == 0 && dgt < nb) {
         a.bucket_start[(size_t)ti.k * nb + dgt] = (uint32_t)ti.tbl_start + base;
-        if (total[q] > a.big) a.over_list[atomicAdd(a.list_cnt, 1u)] = (uint32_t)(ti.k * nb + dgt);
-        if (total[q] > (uint32_t)kBktCap) atomicAdd(a.over_cnt, 1u);
+        if (a.fused_scan) list_if_heavy(a, ti.k, dgt, total[q]);
       }
       base += total[q];
     }
@@ -278,7 +308,8 @@ int enqueue_partition(const dlrm_sparse_batch* s, const GroupArgs& g, hipStream_
     hipLaunchKernelGGL(bucket_hist_kernel<int64_t>, dim3(g.nt_max), dim3(kThreads), 0, st, g);
   DLRM_CHECK_LAUNCH();
   if (!g.fused_scan) {
-    hipLaunchKernelGGL(bucket_scan_kernel, dim3(s->K), dim3(kThreads), 0, st, g);
+    hipLaunchKernelGGL(bucket_scan_kernel, dim3(div_up((int64_t)1 << g.top_bits, kScanDigits), s->K), dim3(kThreads), 0, st,
+                       g);
     DLRM_CHECK_LAUNCH();
   }
   const bool small = g.tile_shift == 10;
