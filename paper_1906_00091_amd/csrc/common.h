@@ -165,25 +165,25 @@ __device__ inline void stamp_start(uint32_t* stamp, uint32_t value) {
 __device__ inline int lane_id() { return threadIdx.x & (DLRM_WAVE - 1); }
 __device__ inline int wave_id() { return threadIdx.x >> 6; }
 
-// ---- block-wide exclusive scan of one uint32 per thread (THREADS multiple of 64) ----
-// smem: at least THREADS/64 + 1 words.  Returns the exclusive prefix; *total = block sum.
-template <int THREADS>
-__device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* smem, uint32_t* total) {
+// ---- block-wide exclusive scan of one integer per thread (THREADS multiple of 64) ----
+// smem: at least THREADS/64 + 1 elements.  Returns the exclusive prefix; *total = block sum.
+template <int THREADS, typename T = uint32_t>
+__device__ inline T block_exclusive_scan(T v, T* smem, T* total) {
   constexpr int NW = THREADS / DLRM_WAVE;
   const int lane = lane_id(), w = wave_id();
-  uint32_t inc = v;
+  T inc = v;
 #pragma unroll
   for (int o = 1; o < DLRM_WAVE; o <<= 1) {
-    uint32_t t = __shfl_up(inc, o, DLRM_WAVE);
+    T t = __shfl_up(inc, o, DLRM_WAVE);
     if (lane >= o) inc += t;
   }
   __syncthreads();  // smem may still be read from a previous call
   if (lane == DLRM_WAVE - 1) smem[w] = inc;
   __syncthreads();
-  uint32_t base = 0, sum = 0;
+  T base = 0, sum = 0;
 #pragma unroll
   for (int i = 0; i < NW; ++i) {
-    uint32_t c = smem[i];
+    T c = smem[i];
     if (i < w) base += c;
     sum += c;
   }

@@ -56,3 +56,17 @@ def test_grouping_equals_the_oracle_at_partition_edges(case):
         assert int(nu[k]) == len(wu)
         assert np.array_equal(uniq[a0:a0 + len(wu)], wu) and np.array_equal(seg[a0:a0 + len(wu)], wseg)
         assert np.array_equal(sbag[a0:a1], wbag)
+
+
+# around the limits of the one-launch form (65536 lengths, 4096 tables), a scan round (4096 bags) and a wavefront
+@pytest.mark.parametrize("K,B", [(1, 1), (3, 63), (1, 4096), (2, 4097), (1, 65536), (1, 65537), (16, 4096), (17, 4096),
+                                 (4096, 16), (4097, 3), (4096, 1)])
+def test_lengths_to_offsets_is_exact_around_its_launch_limits(K, B):
+    print("[case] lengths K=%d B=%d" % (K, B), flush=True)
+    lengths = np.random.default_rng([K, B]).integers(0, 200, size=(K, B)).astype(np.int32)
+    off = torch.full((K, B + 1), -7, dtype=torch.int64, device=DEV)
+    tbl = torch.full((K + 1,), -7, dtype=torch.int64, device=DEV)
+    hot.dlrm_lengths_to_offsets(torch.from_numpy(lengths).to(DEV), off, tbl)
+    torch.cuda.synchronize()
+    want_off, want_tbl = oracle.lengths_to_offsets(lengths)
+    assert np.array_equal(off.cpu().numpy(), want_off) and np.array_equal(tbl.cpu().numpy(), want_tbl)
