@@ -23,11 +23,11 @@
 //                       off their dominant rows unsorted (4a); what still does not fit goes to
 //   4b. segment_sort / segment_reduce : a large list sorted by one workgroup per 2048 pairs
 //                       with per-row counters in LDS, then reduced window by window.
-//   5. hot_rows       : workgroup (bag group, table) streams the gradient rows of its bags
-//                       through LDS once and adds them into every hot row that names them;
-//      hot_rows_dense : the same for tables with many hot rows, as a dense contraction on the
-//                       matrix cores (multiplicity matrix [bag][hot row] times gradient tile);
-//      hot_finish     : adds a hot row's partial sums in bag-group order and updates the row.
+//   5. hot_rows       : workgroup (bag group, table) sums the gradient rows of its bags for every hot
+//                       row that names them: gathered (few hot rows), as a dense contraction on the
+//                       matrix cores (multiplicity matrix [bag][hot row] times gradient tile), or,
+//                       in weighted batches, from tiles staged in LDS.  The last workgroup of a table
+//                       adds the partial sums in bag-group order and updates the rows.
 // Steps 1-3 read indices and offsets only; dlrm_emb_bag_bwd_prepare enqueues just them.
 // ATOMIC path (fp32 tables): a lane group per bag adds -lr*dS[b,k,:] to every row of the bag
 // with hardware fp32 atomics; no workspace, one launch.  Measured 6x slower than SORT on the
@@ -36,7 +36,7 @@
 // Files: bwd_common.h (this: constants, workspace, arguments, shared device helpers),
 // bwd_partition.hip (steps 1-3), bwd_sort.h (bucket and segment sorts), bwd_reduce.h (steps 4, 4a and
 // the row updates; instantiated per optimizer in bwd_reduce_sgd.hip / bwd_reduce_adagrad.hip),
-// bwd_tail.hip (segment sort, hot rows), bwd_export.hip (grouping exported for tests),
+// bwd_tail.hip (segment sort, hot rows and their updates), bwd_export.hip (grouping exported for tests),
 // emb_bwd.hip (entry points, ATOMIC path).
 #pragma once
 #include "common.h"
@@ -66,7 +66,7 @@ constexpr int kHugeRun = 2048;                  // longer runs are split over wo
 constexpr int kHotTileFloats = 16384;            // 64 KB of LDS: gradient rows of one bag tile
 constexpr int kHotZeroRow = 256;                // floats of the widest gradient row
 constexpr int kHotStagePasses = 16;             // float4 registers per thread holding the next tile
-constexpr int kHotTilesPerGroup = 8;            // bag tiles streamed by one workgroup
+constexpr int kHotTilesPerGroup = 8;            // bag tiles streamed by one workgroup, at most
 constexpr int kHotRunsPerWave = 8;              // hot runs a wavefront accumulates at once
 constexpr int kFusedScanMaxTiles = 512;         // fold the scan into the scatter below this
 constexpr int kSegMaxBits = 13;                 // oversized buckets with at most this many low bits are
@@ -103,7 +103,7 @@ struct WsLayout {
   size_t segs;               // SegInfo[nnz / kBktCap + 2]: those of them sorted by many workgroups
   size_t seg_meta;           // uint32[8]: segment tiles, segments, -, -, route counters (kRoute*)
   size_t huge_runs;          // HugeRun[nnz / kHugeRun + K]: table k's list starts at sum_{j<k}(nnz_j/kHugeRun + 1)
-  size_t huge_part;          // float[max_runs * bag groups * d]
+  size_t huge_part;          // float[max_runs * bag groups * d], where more groups fit nowhere else (launch_hot)
   size_t total;
   int64_t nt_max;            // upper bound on the number of tiles
   int64_t max_huge;          // upper bound on the number of queued runs
@@ -129,7 +129,7 @@ struct HugeRun {
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// bags whose gradient rows one hot-row workgroup streams: kHotTilesPerGroup tiles of
+// bags whose gradient rows one weighted hot-row workgroup streams at most: kHotTilesPerGroup tiles of
 // kHotStagePasses passes of kThreads / G rows (G lanes per row)
 inline int hot_group_bags(int d) { return kThreads / pow2_ceil(d / 4) * kHotStagePasses * kHotTilesPerGroup; }
 inline int hot_groups(int B, int d) {
@@ -172,6 +172,8 @@ struct GroupArgs {            // everything the grouping kernels need
   const float* weights;       // NULL, or the weight of every lookup (parallel to indices)
   PosEntry* pos_entry;        // weighted batches: bag and weight of every position, in the original order
   int32_t K, B;
+  int64_t nnz;                // lookups of all tables
+  int64_t max_huge;           // upper bound on the queued hot runs of all tables
   int32_t nt_max;
   int32_t tile_shift;         // log2 of the positions per partition tile (10 or 12)
   int32_t top_bits;           // bits of the partition digit (0..kMaxTopBits)
@@ -189,6 +191,7 @@ struct GroupArgs {            // everything the grouping kernels need
   uint32_t* seg_tbl;
   uint32_t* n_seg;
   uint32_t* hot_cnt;
+  uint32_t* hot_done;         // [K] workgroups that have left their partial sums of table k's hot rows
   uint32_t* list_cnt;         // heavy buckets listed by the partition (more than `big` pairs)
   uint32_t* over_cnt;         // those of them with more than kBktCap pairs (oversized)
   uint32_t* over_list;
@@ -519,6 +522,8 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   g.weights = s->weights;
   g.K = s->K;
   g.B = s->B;
+  g.nnz = s->nnz_total;
+  g.max_huge = L.max_huge;
   g.nt_max = (int32_t)L.nt_max;
   g.tile_shift = tile_shift_for(s->nnz_total);
   // partition digit: one workgroup per bucket, so aim at >= ~1536 buckets when the batch is
@@ -555,6 +560,7 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   g.seg_tbl = reinterpret_cast<uint32_t*>(base + L.seg_tbl);
   g.n_seg = reinterpret_cast<uint32_t*>(base + L.n_seg);
   g.hot_cnt = reinterpret_cast<uint32_t*>(base + L.hot_cnt);
+  g.hot_done = g.tile_heads;   // idle during an update, and holds more than K words
   g.list_cnt = reinterpret_cast<uint32_t*>(base + L.huge_ctr + 8);
   g.over_cnt = reinterpret_cast<uint32_t*>(base + L.huge_ctr + 12);
   g.over_list = reinterpret_cast<uint32_t*>(base + L.over_list);
@@ -600,8 +606,6 @@ int run_reduce_adagrad_weighted(const GroupArgs& g, const UpdArgs& u, int dtype,
                                 const dlrm_bwd_timing* tm, hipStream_t st);
 // bwd_tail.hip
 int launch_segment_sort(const GroupArgs& g, hipStream_t st);
-// *dense_groups_used: bag groups the dense kernel wrote partial sums for (tables it took; the others: ngroups)
-int launch_hot_rows(const GroupArgs& g, const UpdArgs& u, int G, int K, int ngroups, int* dense_groups_used,
-                    hipStream_t st);
+int launch_hot_rows(const GroupArgs& g, const UpdArgs& u, int G, int dtype, int opt, hipStream_t st);
 
 }  // namespace dlrm

@@ -1,5 +1,6 @@
 // Backward tail: the segment sort (oversized lists the bucket kernel could not take) and the hot
-// rows kernel.  Neither updates a row, so neither depends on the optimizer.
+// rows kernels.  A hot row is updated by the workgroup that completes its table; storage type and
+// optimizer are run-time values there (a few rows per table).
 #include "bwd_sort.h"
 
 namespace dlrm {
@@ -89,15 +90,101 @@ __global__ __launch_bounds__(kThreads) void segment_sort_kernel(GroupArgs a) {
 }
 
 
+// --- the update of the hot rows -----------------------------------------------------------------
+// The workgroup (bag group) of table k that leaves its partial sums last adds them up and updates the
+// rows: a counter per table (zeroed by the reduce kernel of the same call) tells it so, and nobody waits.
+// The barrier puts every thread's partial sums before thread 0's release; its acquire and the second
+// barrier put everybody's before the reads.  Uniform answer; all threads call it.
+__device__ inline bool last_of_table(const GroupArgs& a, int k, uint32_t groups) {
+  __shared__ uint32_t is_last;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    is_last = __hip_atomic_fetch_add(&a.hot_done[k], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == groups - 1u;
+  __syncthreads();
+  return is_last != 0u;
+}
+
+// A lane group of GL lanes (4 columns each) per hot run adds the run's partial sums in bag-group order
+// and updates the row.
+template <int DT, int OPT, int GL>
+__device__ inline void finish_rows(const GroupArgs& a, const UpdArgs& u, int k, uint32_t base, uint32_t nruns, int groups) {
+  const int chunk = threadIdx.x % GL;
+  if (chunk * 4 >= u.d) return;
+  char* W = static_cast<char*>(u.tables[k]);
+  float* H = state_base<OPT>(u, k);
+  for (uint32_t r = threadIdx.x / GL; r < nruns; r += kThreads / GL) {
+    const float* part = a.huge_part + ((size_t)(base + r) * groups) * u.d + chunk * 4;
+    const RowRef ref = row_ref<DT, OPT>(W, H, u.d, a.huge_runs[base + r].row, chunk);
+    const RowVal val = row_load<DT, OPT>(ref);
+    f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int g0 = 0; g0 < groups; g0 += 8) {
+      f32x4 v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = loadf4(part + (size_t)(g0 + q < groups ? g0 + q : g0) * u.d);
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (g0 + q < groups) sum += v[q];
+    }
+    row_update_store<DT, OPT>(ref, val, sum, u);
+  }
+}
+
+// kind: storage type and optimizer of the call (row_kind), uniform
+template <int GL>
+__device__ inline void finish_table(const GroupArgs& a, const UpdArgs& u, int kind, int k, uint32_t base, uint32_t nruns,
+                                    int groups) {
+  if (!last_of_table(a, k, (uint32_t)groups)) return;
+  switch (kind) {
+    case DLRM_F32 * 2 + kSgd: finish_rows<DLRM_F32, kSgd, GL>(a, u, k, base, nruns, groups); break;
+    case DLRM_F16 * 2 + kSgd: finish_rows<DLRM_F16, kSgd, GL>(a, u, k, base, nruns, groups); break;
+    case DLRM_BF16 * 2 + kSgd: finish_rows<DLRM_BF16, kSgd, GL>(a, u, k, base, nruns, groups); break;
+    case DLRM_F32 * 2 + kAdagrad: finish_rows<DLRM_F32, kAdagrad, GL>(a, u, k, base, nruns, groups); break;
+    case DLRM_F16 * 2 + kAdagrad: finish_rows<DLRM_F16, kAdagrad, GL>(a, u, k, base, nruns, groups); break;
+    case DLRM_BF16 * 2 + kAdagrad: finish_rows<DLRM_BF16, kAdagrad, GL>(a, u, k, base, nruns, groups); break;
+  }
+}
+
+// start of table k's hot-run list, summed by a wavefront (hot_list_base walks the tables one by one)
+__device__ inline uint32_t hot_list_base_wave(const GroupArgs& a, int k) {
+  uint32_t base = 0;
+  for (int j = lane_id(); j < k; j += DLRM_WAVE) base += (uint32_t)((a.tbl_off[j + 1] - a.tbl_off[j]) / kHugeRun) + 1u;
+#pragma unroll
+  for (int o = 1; o < DLRM_WAVE; o <<= 1) base += (uint32_t)__shfl_xor((int)base, o, DLRM_WAVE);
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+}
+
+// First of the ascending bags list[0..n) at or after `bound`: seven probes a round are in flight
+// together (a third of the dependent loads of a binary search).
+__device__ inline uint32_t lower_bag(const uint32_t* list, uint32_t n, uint32_t bound) {
+  uint32_t lo = 0, hi = n;
+  while (lo < hi) {
+    const uint32_t step = (hi - lo + 7u) >> 3;
+    uint32_t probe[7], below = 0;
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+      const uint32_t q = lo + (uint32_t)(j + 1) * step - 1u;   // < n where it counts
+      probe[j] = list[q < hi ? q : hi - 1u];
+    }
+#pragma unroll
+    for (int j = 0; j < 7; ++j) below += (lo + (uint32_t)(j + 1) * step - 1u < hi && probe[j] < bound) ? 1u : 0u;
+    // the first `below` probes lie before the answer, the next one (if there is one) does not
+    const uint32_t end = lo + (below + 1u) * step - 1u;
+    lo += below * step;
+    if (below < 7u && end < hi) hi = end;
+  }
+  return lo;
+}
+
+
 // --- 5. hot rows: runs too long for one workgroup -------------------------------------------------
-// A hot row is looked up by a large share of the bags, so summing its run entry by entry would
-// fetch nearly the whole gradient slice dS[:, k, :] once per hot row.  Instead workgroup (g, k)
-// streams the gradient rows of bag group g of table k through LDS ONCE, tile by tile (the next
-// tile travels in registers while the current one is consumed), and every wavefront adds, for
-// each of its hot runs, the rows of the run's entries whose bag lies in the tile.  A run's bags
-// ascend, so binary searches give its entry range per tile, and equal neighbours (a bag that
-// looks the row up several times) are folded into one LDS read times a multiplicity.  Partial
-// sums per (run, bag group) go to global memory; hot_finish_kernel adds them in group order.
+// A hot row is looked up by a large share of the bags.  Workgroup (g, k) takes bag group g of table k and
+// adds, for each hot run of the table, the gradient rows of the run's entries whose bag lies in the
+// group; partial sums per (run, bag group) go to global memory, and finish_table adds them in group order.
+// A run's bags ascend, so a search gives its first entry of a group.  Three ways to sum, all in an order
+// fixed by the batch:
+//   weighted batches     : bag tiles of gradient rows staged in LDS (hot_rows_weighted_kernel),
+//   fewer than kDenseFrom hot rows in the table : gathered bag by bag (sum_few_runs),
+//   more                 : a dense contraction on the matrix cores (hot_rows_dense_kernel).
 
 // Entry e + slot of the 64 values the lanes hold in `v` (e: uniform).  Few slots: scalar lane
 // reads and selects, no LDS round trip; many slots: a lane permute.
@@ -116,8 +203,11 @@ __device__ inline uint32_t lane_entry(uint32_t v, uint32_t e, int slot) {
   }
 }
 
-template <int G, bool WT>
-__global__ __launch_bounds__(kThreads) void hot_rows_kernel(GroupArgs a, UpdArgs u, int ngroups, int dense_from) {
+// Weighted batches.  The next tile travels in registers while the current one is consumed; every
+// wavefront adds the rows of its runs' entries from LDS, each times the entry's weight.
+template <int G>
+__global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a, UpdArgs u, int kind, int ngroups,
+                                                                     int ntiles) {
   constexpr int S = DLRM_WAVE / G;
   constexpr int MR = kHotRunsPerWave;
   constexpr int NT = kHotTilesPerGroup;
@@ -125,32 +215,29 @@ __global__ __launch_bounds__(kThreads) void hot_rows_kernel(GroupArgs a, UpdArgs
   constexpr int NG = kThreads / G;                // gradient rows staged per pass of the workgroup
   constexpr int NP = kHotStagePasses;
   constexpr int TB = NG * NP;                     // bags per tile: TB * d <= kHotTileFloats
-  constexpr int GB = TB * NT;                     // bags per workgroup
+  const int GB = TB * ntiles;                     // bags per workgroup, ntiles <= NT
   __shared__ float tile[kHotTileFloats + kHotZeroRow];  // gradient rows of a bag tile, then a row of zeros
   __shared__ uint32_t cursor[kNW * MR][NT + 1];  // first entry of a run at or after every tile boundary
   __shared__ uint32_t rsrc[kNW * MR];            // pair buffer holding the run
-  __shared__ uint32_t wsc[kNW][DLRM_WAVE];       // per wavefront: compacted (offset, multiplicity) words
-  // weighted batches: a run lists positions; bag and weight are looked up by position
-  const int64_t tbl = WT ? a.tbl_off[blockIdx.y] : 0;
+  // a run lists positions; bag and weight are looked up by position
+  const int64_t tbl = a.tbl_off[blockIdx.y];
   const int k = blockIdx.y, g = blockIdx.x;
   const uint32_t nruns = a.hot_cnt[k];
   if (nruns == 0) return;  // uniform
-  if (dense_from > 0 && nruns >= (uint32_t)dense_from) return;  // hot_rows_dense_kernel has this table
-  const uint32_t base = hot_list_base(a, k);
+  const uint32_t base = hot_list_base_wave(a, k);
   const int lane = lane_id(), w = wave_id(), tid = threadIdx.x;
   const int slot = lane / G, chunk = lane % G;
   const int grp = tid / G;
   const bool col_ok = chunk * 4 < u.d;
   const int cchunk = col_ok ? chunk : 0;  // lanes past the last column shadow column group 0, never store
-  const unsigned long long lt = (1ull << lane) - 1ull;
   const int bag_lo = g * GB;
   const int bag_hi = bag_lo + GB < a.B ? bag_lo + GB : a.B;
   const float* gk = u.dS + (int64_t)k * u.stride_k + cchunk * 4;
   for (int i = tid; i < kHotZeroRow; i += kThreads) tile[kHotTileFloats + i] = 0.0f;
   for (uint32_t r0 = 0; r0 < nruns; r0 += kNW * MR) {  // uniform
     __syncthreads();
-    for (int task = tid; task < kNW * MR * (NT + 1); task += kThreads) {
-      const int rl = task / (NT + 1), tb = task - rl * (NT + 1);
+    for (int task = tid; task < kNW * MR * (ntiles + 1); task += kThreads) {
+      const int rl = task / (ntiles + 1), tb = task - rl * (ntiles + 1);
       const uint32_t r = r0 + (uint32_t)rl;
       uint32_t c = 0;
       if (r < nruns) {
@@ -161,8 +248,7 @@ __global__ __launch_bounds__(kThreads) void hot_rows_kernel(GroupArgs a, UpdArgs
         uint32_t lo = 0, hi = hr.len;
         while (lo < hi) {
           const uint32_t mid = (lo + hi) >> 1;
-          const uint32_t bm = WT ? a.pos_entry[tbl + bags[mid]].bag : bags[mid];
-          if (bm < bound) lo = mid + 1; else hi = mid;
+          if (a.pos_entry[tbl + bags[mid]].bag < bound) lo = mid + 1; else hi = mid;
         }
         c = hr.start + lo;
         if (tb == 0) rsrc[rl] = hr.src;
@@ -225,53 +311,21 @@ __global__ __launch_bounds__(kThreads) void hot_rows_kernel(GroupArgs a, UpdArgs
           uint32_t nxt = 0;  // the next 64 bags travel while these are summed
           if (e0 + DLRM_WAVE + (uint32_t)lane < c1) nxt = bags[i][e0 + DLRM_WAVE + lane];
           const uint32_t cnt = c1 - e0 < (uint32_t)DLRM_WAVE ? c1 - e0 : (uint32_t)DLRM_WAVE;
-          if constexpr (WT) {
-            // every entry on its own: LDS offset of its bag's gradient row and its weight
-            uint32_t moff = (uint32_t)kHotTileFloats;  // entries past the end: the row of zeros, weight 0
-            float mw = 0.0f;
-            if ((uint32_t)lane < cnt) {
-              const PosEntry pe = a.pos_entry[tbl + cur];
-              moff = (pe.bag - (uint32_t)tb0) * (uint32_t)u.d;
-              mw = pe.w;
-            }
-            for (uint32_t e = 0; e < cnt; e += HU * S) {
-              f32x4 v[HU];
-              float m[HU];
-#pragma unroll
-              for (int q = 0; q < HU; ++q) {
-                v[q] = loadf4(tile + lane_entry<S>(moff, e + (uint32_t)(q * S), slot) + cchunk * 4);
-                m[q] = u2f(lane_entry<S>(f2u(mw), e + (uint32_t)(q * S), slot));
-              }
-#pragma unroll
-              for (int q = 0; q < HU; ++q) {
-                acc[i].x = fmaf(m[q], v[q].x, acc[i].x);
-                acc[i].y = fmaf(m[q], v[q].y, acc[i].y);
-                acc[i].z = fmaf(m[q], v[q].z, acc[i].z);
-                acc[i].w = fmaf(m[q], v[q].w, acc[i].w);
-              }
-            }
-            cur = nxt;
-            continue;
+          // every entry on its own: LDS offset of its bag's gradient row and its weight
+          uint32_t moff = (uint32_t)kHotTileFloats;  // entries past the end: the row of zeros, weight 0
+          float mw = 0.0f;
+          if ((uint32_t)lane < cnt) {
+            const PosEntry pe = a.pos_entry[tbl + cur];
+            moff = (pe.bag - (uint32_t)tb0) * (uint32_t)u.d;
+            mw = pe.w;
           }
-          // fold equal neighbours: the first entry of each distinct bag carries how many follow
-          const uint32_t prev = (uint32_t)__shfl_up((int)cur, 1, DLRM_WAVE);
-          const bool head = (uint32_t)lane < cnt && (lane == 0 || cur != prev);
-          const unsigned long long hm = __ballot(head);
-          const uint32_t nh = (uint32_t)__popcll(hm);
-          const unsigned long long rest = (hm >> lane) >> 1;
-          const uint32_t nextp = rest ? (uint32_t)lane + (uint32_t)__ffsll((long long)rest) : cnt;
-          // LDS offset of the bag's gradient row (< 2^16) | multiplicity << 16
-          if (head) wsc[w][__popcll(hm & lt)] = ((nextp - (uint32_t)lane) << 16) | ((cur - (uint32_t)tb0) * (uint32_t)u.d);
-          uint32_t mine = wsc[w][lane];
-          mine = (uint32_t)lane < nh ? mine : (uint32_t)kHotTileFloats;  // the row of zeros, zero times
-          for (uint32_t e = 0; e < nh; e += HU * S) {
+          for (uint32_t e = 0; e < cnt; e += HU * S) {
             f32x4 v[HU];
             float m[HU];
 #pragma unroll
-            for (int q = 0; q < HU; ++q) {  // HU independent LDS reads in flight
-              const uint32_t pk = lane_entry<S>(mine, e + (uint32_t)(q * S), slot);
-              v[q] = loadf4(tile + (pk & 0xFFFFu) + cchunk * 4);
-              m[q] = (float)(pk >> 16);
+            for (int q = 0; q < HU; ++q) {
+              v[q] = loadf4(tile + lane_entry<S>(moff, e + (uint32_t)(q * S), slot) + cchunk * 4);
+              m[q] = u2f(lane_entry<S>(f2u(mw), e + (uint32_t)(q * S), slot));
             }
 #pragma unroll
             for (int q = 0; q < HU; ++q) {
@@ -301,13 +355,127 @@ __global__ __launch_bounds__(kThreads) void hot_rows_kernel(GroupArgs a, UpdArgs
       if (slot == 0 && col_ok) storef4(part + (size_t)g * u.d + chunk * 4, tot);
     }
   }
+  finish_table<G>(a, u, kind, k, base, nruns, ngroups);
+}
+
+
+// Few hot rows: the four wavefronts of the workgroup own a quarter of its bags each and gather every
+// distinct bag's gradient row of every run once (neighbouring entries of one bag are folded into a
+// multiplicity), U * 4 bags at a time; the wavefronts' sums are added in bag order.  Bound by the chain
+// search -> entries -> rows, so what counts is many wavefronts with few bags each (see hot_bag_groups):
+// with groups of 2048 bags as before and LDS tiles, 26 bf16 tables of up to 10 M rows, 1.06 M lookups,
+// 49 hot rows took 81 us, now 18 us with the rows updated (and the launch that did so gone).
+template <int NH>
+__device__ inline void sum_few_runs(const GroupArgs& a, const UpdArgs& u, int k, uint32_t base, uint32_t nruns, int ngroups,
+                                    int wb_lo, int wb_hi, uint32_t* lds) {
+  constexpr int U = NH == 1 ? 8 : NH == 2 ? 4 : 2;
+  const int lane = lane_id(), w = wave_id();
+  const int m = lane & 15, kk = lane >> 4;
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  const float* gk = u.dS + (int64_t)k * u.stride_k + 4 * m;
+  const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  float* red = reinterpret_cast<float*>(lds);               // [wavefront][run][d]
+  uint32_t* fold = lds + kNW * (kDenseFrom - 1) * 64 * NH + w * 2 * DLRM_WAVE;   // this wavefront's bags and multiplicities
+  // lane r keeps run r's state; every run's first 64 entries are requested together
+  uint32_t pos = 0, end = 0, src = 0;
+  if ((uint32_t)lane < nruns && wb_lo < wb_hi) {
+    const HugeRun hr = a.huge_runs[base + (uint32_t)lane];
+    pos = hr.start + lower_bag((hr.src ? a.vals[1] : a.vals[0]) + hr.start, hr.len, (uint32_t)wb_lo);
+    end = hr.start + hr.len;
+    src = hr.src;
+  }
+  uint32_t ent[kDenseFrom - 1];
+#pragma unroll
+  for (int q = 0; q < kDenseFrom - 1; ++q) {
+    const uint32_t pq = (uint32_t)__builtin_amdgcn_readlane((int)pos, q);
+    const uint32_t eq = (uint32_t)__builtin_amdgcn_readlane((int)end, q);
+    const uint32_t* lq = __builtin_amdgcn_readlane((int)src, q) ? a.vals[1] : a.vals[0];
+    ent[q] = 0xFFFFFFFFu;
+    if (pq + (uint32_t)lane < eq) ent[q] = lq[pq + (uint32_t)lane];
+  }
+#pragma unroll
+  for (int q = 0; q < kDenseFrom - 1; ++q) {
+    if ((uint32_t)q >= nruns) continue;  // uniform
+    uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)pos, q);
+    const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)end, q);
+    const uint32_t* lq = __builtin_amdgcn_readlane((int)src, q) ? a.vals[1] : a.vals[0];
+    f32x4 acc[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) acc[h] = zero;
+    uint32_t cur = ent[q];   // past the run's end: no bag
+    for (;;) {
+      const unsigned long long in = __ballot(cur < (uint32_t)wb_hi);   // ascending: a prefix of the lanes
+      const uint32_t cnt = (uint32_t)__popcll(in);
+      if (cnt == 0u) break;  // wave-uniform
+      const bool more = cnt == (uint32_t)DLRM_WAVE && c + (uint32_t)DLRM_WAVE < e;
+      uint32_t nxt = 0xFFFFFFFFu;
+      c += DLRM_WAVE;
+      if (more && c + (uint32_t)lane < e) nxt = lq[c + (uint32_t)lane];
+      // the first entry of each distinct bag carries how many follow
+      const uint32_t prev = (uint32_t)__shfl_up((int)cur, 1, DLRM_WAVE);
+      const bool head = (uint32_t)lane < cnt && (lane == 0 || cur != prev);
+      const unsigned long long hm = __ballot(head);
+      const uint32_t nh = (uint32_t)__popcll(hm);
+      const unsigned long long rest = (hm >> lane) >> 1;
+      const uint32_t nextp = rest ? (uint32_t)lane + (uint32_t)__ffsll((long long)rest) : cnt;
+      if (head) {
+        fold[__popcll(hm & lt)] = cur;
+        fold[DLRM_WAVE + __popcll(hm & lt)] = nextp - (uint32_t)lane;
+      }
+      for (uint32_t i0 = 0; i0 < nh; i0 += U * 4) {   // wave-uniform
+        f32x4 v[U][NH];
+        float mult[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const uint32_t i = i0 + (uint32_t)(j * 4 + kk);
+          const uint32_t bag = fold[i < nh ? i : nh - 1u];
+          mult[j] = (float)fold[DLRM_WAVE + (i < nh ? i : nh - 1u)];
+          const float* row = gk + (int64_t)bag * u.stride_b;
+#pragma unroll
+          for (int h = 0; h < NH; ++h) v[j][h] = loadf4(row + (64 * h + 4 * m < u.d ? 64 * h : -4 * m));
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          if (i0 + (uint32_t)(j * 4 + kk) < nh) {
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+              acc[h].x = fmaf(mult[j], v[j][h].x, acc[h].x);
+              acc[h].y = fmaf(mult[j], v[j][h].y, acc[h].y);
+              acc[h].z = fmaf(mult[j], v[j][h].z, acc[h].z);
+              acc[h].w = fmaf(mult[j], v[j][h].w, acc[h].w);
+            }
+          }
+        }
+      }
+      if (!more) break;  // wave-uniform
+      cur = nxt;
+    }
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+#pragma unroll
+      for (int o = 16; o < DLRM_WAVE; o <<= 1) {
+        acc[h].x += __shfl_xor(acc[h].x, o, DLRM_WAVE);
+        acc[h].y += __shfl_xor(acc[h].y, o, DLRM_WAVE);
+        acc[h].z += __shfl_xor(acc[h].z, o, DLRM_WAVE);
+        acc[h].w += __shfl_xor(acc[h].w, o, DLRM_WAVE);
+      }
+      if (kk == 0 && 64 * h + 4 * m < u.d) storef4(red + (w * (kDenseFrom - 1) + q) * u.d + 64 * h + 4 * m, acc[h]);
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x * 4; i < (int)nruns * u.d; i += kThreads * 4) {   // d is a multiple of 4
+    const int q = i / u.d, col = i - q * u.d;
+    f32x4 sum = loadf4(red + q * u.d + col);
+#pragma unroll
+    for (int x = 1; x < kNW; ++x) sum += loadf4(red + (x * (kDenseFrom - 1) + q) * u.d + col);
+    storef4(a.huge_part + ((size_t)(base + q) * ngroups + blockIdx.x) * u.d + col, sum);
+  }
 }
 
 
 // --- 5b. many hot rows in one table: the same pass as a dense product on the matrix cores -----------
-// With many hot rows per table (a skewed table: the hottest few are in nearly every bag) the kernel
-// above reads a gradient row from LDS once per (hot row, bag) that meets, and LDS reads are what it
-// spends its time on.  Here the multiplicities of kDenseRuns hot rows against a tile of bags are
+// With many hot rows per table (a skewed table: the hottest few are in nearly every bag) a gradient row
+// would be read once per (hot row, bag) that meets.  Here the multiplicities of kDenseRuns hot rows against a tile of bags are
 // first counted into a small matrix C[run][bag] in LDS (integer atomics: exact, order-free); then
 // G_hot[run][col] += sum_bag C[run][bag] * dS[bag][col] is a dense contraction over the bags of the
 // tile, done with v_mfma_f32_16x16x4_f32: runs are the M index (two blocks of 16), four bags per
@@ -324,8 +492,6 @@ __global__ __launch_bounds__(kThreads) void hot_rows_kernel(GroupArgs a, UpdArgs
 //   dS[bag k][64h + 4n .. 64h + 4n + 3] with one instruction (a bag row is read as contiguous 256-byte
 //   pieces) and component c of that load is the B operand of contraction (h, c), whose result
 //   column n is gradient column 64h + 4n + c.
-// The same bag groups, run lists and partial-sum layout as hot_rows_kernel (which keeps the
-// tables with few hot rows and the weighted batches); hot_finish_kernel follows.
 // A count of zero still multiplies the bag's gradient: a non-finite gradient entry of a bag reaches
 // every hot row of this pass, not only the rows the bag looked up.
 constexpr int kDenseRuns = 32;      // hot rows per pass of a workgroup
@@ -335,15 +501,16 @@ constexpr int kDensePre = 4;        // 4-bag steps of gradient rows in flight
 constexpr int kDenseHeavy = 4;      // the longest runs of a pass: 256 list entries per request instead of 64
 
 template <int NH>   // 64-column pieces of a gradient row
-__global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kernel(GroupArgs a, UpdArgs u, int ngroups,
-                                                                                   int group_bags) {
+__global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kernel(GroupArgs a, UpdArgs u, int kind,
+                                                                                   int ngroups, int group_bags) {
   constexpr int R = kDenseRuns, TB = kDenseTile, CS = kDenseCStride, PRE = NH <= 2 ? kDensePre : kDensePre / 2;
   static_assert(R * CS * kNW >= R * 64 * NH, "the reduction buffer aliases the count matrices");
+  static_assert(R * CS * kNW >= kNW * (kDenseFrom - 1) * 64 * NH + kNW * 2 * DLRM_WAVE, "and so do sum_few_runs' buffers");
   __shared__ __align__(16) uint32_t cmat[kNW][R * CS];   // per wavefront: multiplicity of run r in bag tb0 + b at [r * CS + b]
   const int k = blockIdx.y, g = blockIdx.x;
   const uint32_t nruns = a.hot_cnt[k];
-  if (nruns < (uint32_t)kDenseFrom) return;  // uniform: hot_rows_kernel has this table
-  const uint32_t base = hot_list_base(a, k);
+  if (nruns == 0u) return;  // uniform
+  const uint32_t base = hot_list_base_wave(a, k);
   const int lane = lane_id(), w = wave_id();
   const int m = lane & 15, kk = lane >> 4;
   // this wavefront's bags
@@ -351,6 +518,11 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
   int wb_lo = g * group_bags + w * quarter;
   wb_lo = wb_lo < a.B ? wb_lo : a.B;
   const int wb_hi = wb_lo + quarter < a.B ? wb_lo + quarter : a.B;
+  if (nruns < (uint32_t)kDenseFrom) {  // uniform
+    sum_few_runs<NH>(a, u, k, base, nruns, ngroups, wb_lo, wb_hi, &cmat[0][0]);
+    finish_table<16 * NH>(a, u, kind, k, base, nruns, ngroups);
+    return;
+  }
   const float* gk = u.dS + (int64_t)k * u.stride_k + 4 * m;
   // lanes whose columns lie past the row's end load piece 0 again (no branch around a load) and never store
   bool col_ok[NH];
@@ -385,12 +557,7 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
       rank = lane < R ? rank : (uint32_t)lane;
       uint32_t lo = 0;
       if (len != 0 && wb_lo < wb_hi) {
-        const uint32_t* bags = (hr.src ? a.vals[1] : a.vals[0]) + hr.start;
-        uint32_t hi = hr.len;
-        while (lo < hi) {
-          const uint32_t mid = (lo + hi) >> 1;
-          if (bags[mid] < (uint32_t)wb_lo) lo = mid + 1; else hi = mid;
-        }
+        lo = lower_bag((hr.src ? a.vals[1] : a.vals[0]) + hr.start, hr.len, (uint32_t)wb_lo);
       }
       const bool live = len != 0 && wb_lo < wb_hi;
       pos = (uint32_t)__builtin_amdgcn_ds_permute((int)(rank * 4), (int)(live ? hr.start + lo : 0u));
@@ -562,6 +729,7 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
             storef4(a.huge_part + ((size_t)(base + run) * ngroups + g) * u.d + 64 * h + 4 * m, out[mb][h][v]);
       }
   }
+  finish_table<16 * NH>(a, u, kind, k, base, nruns, ngroups);
 }
 
 
@@ -571,49 +739,61 @@ int launch_segment_sort(const GroupArgs& g, hipStream_t st) {
   return DLRM_OK;
 }
 
-// Bag groups of the dense kernel: as few as fill the machine once (gfx950: 256 compute units, three
-// resident workgroups each, two for rows above 128 columns), never more than the partial-sum layout
-// has room for; a wavefront's quarter of a group is whole tiles.
-static void dense_groups(int B, int K, int nh, int ngroups, int* group_bags, int* ngd) {
+// Bag groups of an unweighted batch: as many as fill the machine once (gfx950: 256 compute units, three
+// resident workgroups each, two for rows above 128 columns) if every table has hot rows, within the room
+// for partial sums; a wavefront's quarter of a group is whole tiles.
+static void hot_bag_groups(int B, int K, int nh, int64_t max_groups, int* group_bags, int* groups) {
   const int slots = 256 * (nh <= 2 ? 3 : 2);
-  int n = slots / (K > 0 ? K : 1);
-  n = n < 1 ? 1 : (n > ngroups ? ngroups : n);
+  int64_t n = slots / (K > 0 ? K : 1);
+  if (n > max_groups) n = max_groups;
+  if (n < 1) n = 1;
   const int unit = kNW * kDenseTile;
-  int gb = ((B + n - 1) / n + unit - 1) / unit * unit;
-  if (gb < unit) gb = unit;
-  *group_bags = gb;
-  *ngd = (B + gb - 1) / gb;
+  const int64_t gb = ((B + n - 1) / n + unit - 1) / unit * unit;
+  *group_bags = (int)gb;
+  *groups = (int)((B + gb - 1) / gb);
 }
 
+// Partial sums lie where nothing is left to read once the rows are grouped, if that holds more bag groups
+// than the array laid out for them: the two arrays of the exported grouping or, for a weighted batch (whose
+// records fill those), the partition's tile counts.
 template <int G>
-static int launch_hot(const GroupArgs& g, const UpdArgs& u, int K, int ngroups, int* ngd, hipStream_t st) {
-  *ngd = ngroups;
-  if (g.weights != nullptr) {
-    hipLaunchKernelGGL((hot_rows_kernel<G, true>), dim3(ngroups, K), dim3(kThreads), 0, st, g, u, ngroups, 0);
+static int launch_hot(GroupArgs g, const UpdArgs& u, int kind, hipStream_t st) {
+  constexpr int TB = kThreads / G * kHotStagePasses;    // bags of an LDS tile (weighted)
+  constexpr int NH = G <= 16 ? 1 : G == 32 ? 2 : 4;
+  const bool weighted = g.weights != nullptr;
+  const int64_t room = weighted ? (int64_t)kMaxBuckets * g.nt_max * 4 : g.nnz * 8;   // bytes
+  int64_t fit = room / (g.max_huge * u.d * 4);            // bag groups
+  if (fit > hot_groups(g.B, u.d))
+    g.huge_part = reinterpret_cast<float*>(weighted ? g.hist : g.seg_start);
+  else
+    fit = hot_groups(g.B, u.d);
+  if (weighted) {
+    // tiles per workgroup: enough workgroups for two per compute unit if every table has hot rows
+    const int64_t tiles = (g.B + TB - 1) / TB;
+    int64_t nt = (tiles * g.K + 511) / 512;
+    if (nt > kHotTilesPerGroup) nt = kHotTilesPerGroup;
+    while ((tiles + nt - 1) / nt > fit) ++nt;   // kHotTilesPerGroup tiles always fit
+    const int ng = (int)((tiles + nt - 1) / nt);
+    hipLaunchKernelGGL((hot_rows_weighted_kernel<G>), dim3(ng, g.K), dim3(kThreads), 0, st, g, u, kind, ng, (int)nt);
   } else {
-    // tables with many hot rows go through the dense kernel, the others through the entry-by-entry one
-    constexpr int NH = G <= 16 ? 1 : G == 32 ? 2 : 4;
-    int group_bags;
-    dense_groups(g.B, K, NH, ngroups, &group_bags, ngd);
-    hipLaunchKernelGGL((hot_rows_dense_kernel<NH>), dim3(*ngd, K), dim3(kThreads), 0, st, g, u, ngroups, group_bags);
-    DLRM_CHECK_LAUNCH();
-    hipLaunchKernelGGL((hot_rows_kernel<G, false>), dim3(ngroups, K), dim3(kThreads), 0, st, g, u, ngroups,
-                       kDenseFrom);
+    int group_bags, ng;
+    hot_bag_groups(g.B, g.K, NH, fit, &group_bags, &ng);
+    hipLaunchKernelGGL((hot_rows_dense_kernel<NH>), dim3(ng, g.K), dim3(kThreads), 0, st, g, u, kind, ng, group_bags);
   }
   DLRM_CHECK_LAUNCH();
   return DLRM_OK;
 }
 
-int launch_hot_rows(const GroupArgs& g, const UpdArgs& u, int G, int K, int ngroups, int* dense_groups_used,
-                    hipStream_t st) {
+int launch_hot_rows(const GroupArgs& g, const UpdArgs& u, int G, int dtype, int opt, hipStream_t st) {
+  const int kind = dtype * 2 + opt;
   switch (G) {
-    case 1: return launch_hot<1>(g, u, K, ngroups, dense_groups_used, st);
-    case 2: return launch_hot<2>(g, u, K, ngroups, dense_groups_used, st);
-    case 4: return launch_hot<4>(g, u, K, ngroups, dense_groups_used, st);
-    case 8: return launch_hot<8>(g, u, K, ngroups, dense_groups_used, st);
-    case 16: return launch_hot<16>(g, u, K, ngroups, dense_groups_used, st);
-    case 32: return launch_hot<32>(g, u, K, ngroups, dense_groups_used, st);
-    case 64: return launch_hot<64>(g, u, K, ngroups, dense_groups_used, st);
+    case 1: return launch_hot<1>(g, u, kind, st);
+    case 2: return launch_hot<2>(g, u, kind, st);
+    case 4: return launch_hot<4>(g, u, kind, st);
+    case 8: return launch_hot<8>(g, u, kind, st);
+    case 16: return launch_hot<16>(g, u, kind, st);
+    case 32: return launch_hot<32>(g, u, kind, st);
+    case 64: return launch_hot<64>(g, u, kind, st);
   }
   return DLRM_ERR_BAD_SHAPE;
 }

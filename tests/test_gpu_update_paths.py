@@ -9,7 +9,8 @@ import paper_1906_00091_amd as hot
 from oracle import oracle
 from workloads import gen
 
-from hotpath_util import DEV
+from hotpath_util import DEV, Compact, table_to_numpy
+from test_gpu_exact_counts import _assert_only_touched_rows_changed, _integer_dS, _integer_tables, _max_run, _pow2_weights, _run_update
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +71,80 @@ def test_lengths_to_offsets_is_exact_around_its_launch_limits(K, B):
     torch.cuda.synchronize()
     want_off, want_tbl = oracle.lengths_to_offsets(lengths)
     assert np.array_equal(off.cpu().numpy(), want_off) and np.array_equal(tbl.cpu().numpy(), want_tbl)
+
+
+def _assert_exact_update(b, dtype, weighted, modes):
+    """The update of batch b on exactly representable numbers equals the oracle's; returns the routes of the last mode."""
+    w = b.workload
+    wts = _pow2_weights(b) if weighted else None
+    dS = _integer_dS(w.B, w.K, w.d, max(_max_run(b), 1), 2.0 if weighted else 1.0)
+    lr = 0.5 if dtype == gen.F32 else 2.0 ** -8
+    start = _integer_tables(b.rows, w.d, dtype, seed=5)
+    comp = Compact(b, host_rows_of=lambda k, u: table_to_numpy(
+        start[k].index_select(0, torch.from_numpy(u).to(DEV)), dtype))
+    ref = [t.copy() for t in comp.tables]
+    if weighted:
+        oracle.emb_bag_bwd_weighted(ref, dtype, comp.indices, b.offsets, b.tbl_off, wts, dS, lr)
+    else:
+        oracle.emb_bag_bwd_sgd(ref, dtype, comp.indices, b.offsets, b.tbl_off, dS, lr)
+    dT = torch.zeros((w.B, w.K + 1, w.d), dtype=torch.float32, device=DEV)
+    dT[:, 1:, :] = torch.from_numpy(dS).to(DEV)
+    for mode in modes:
+        tables = [t.clone() for t in start]
+        counts = _run_update(b, tables, dT, lr, mode, weights=wts)
+        for k in range(w.K):
+            got = table_to_numpy(tables[k].index_select(0, torch.from_numpy(comp.uniq[k]).to(DEV)), dtype)
+            assert np.array_equal(got.view(np.uint8), ref[k].view(np.uint8)), (mode, k)
+            _assert_only_touched_rows_changed(start[k], tables[k], comp.uniq[k])
+    return counts
+
+
+# name, tables, bags, d, type, rows, lookups per bag: 1 .. 7 hot rows are gathered and 8 go to the matrix cores; bag
+# groups (256 bags and up) one short of full, full plus one, and many; one, two and four 64-column pieces; more than
+# 64 tables (whose hot lists' starts are summed by 64 lanes)
+HOT = [
+    ("one-row-255-bags", 1, 255, 4, gen.F32, 1, 300),
+    ("seven-rows-257-bags", 2, 257, 64, gen.F16, 7, 300),
+    ("eight-rows-257-bags", 2, 257, 64, gen.F16, 8, 300),
+    ("five-rows-two-pieces", 1, 1025, 136, gen.BF16, 5, 70),
+    ("three-rows-wide", 1, 4097, 256, gen.F32, 3, 40),
+    ("seventy-tables", 70, 513, 12, gen.F32, 2, 9),
+]
+
+
+@pytest.mark.parametrize("weighted", [False, True], ids=["sum", "pow2-weights"])
+@pytest.mark.parametrize("case", HOT, ids=[c[0] for c in HOT])
+def test_hot_rows_at_the_edges_of_bag_groups(case, weighted):
+    name, K, B, d, dtype, rows, bag = case
+    print("[case] hot rows %s weighted=%s" % (name, weighted), flush=True)
+    b = gen.make_batch(gen.custom_workload(name, K=K, B=B, d=d, dtype=dtype, rows=rows, bag=("fixed", bag), dist=("uniform",),
+                                           seed=31))
+    counts = _assert_exact_update(b, dtype, weighted, ("sort",))
+    assert counts["hot_rows"] == K * rows
+
+
+def test_hot_rows_with_little_room_for_partial_sums():
+    """One table with three hot rows among 300 tables of ten lookups: the arrays left over after the grouping hold
+    fewer bag groups than the array laid out for partial sums, which is then used."""
+    print("[case] hot rows, little room", flush=True)
+    B, K = 1500, 301
+    lengths = [[55] * B] + [[1] * 10 + [0] * (B - 10)] * (K - 1)
+    b = _batch(lengths, [3] + [40] * (K - 1), seed=4, d=256)
+    for weighted in (False, True):
+        assert _assert_exact_update(b, gen.F32, weighted, ("sort",))["hot_rows"] == 3
+
+
+def test_an_infinite_gradient_stays_with_the_hot_rows_it_belongs_to():
+    """Three hot rows, each in every bag but one: the gradient of a bag that does not name a row never meets it."""
+    print("[case] hot rows, infinite gradient", flush=True)
+    B, per = 3000, 30
+    bags = [[0] * per + [1] * per if i == 17 else [0] * per + [2] * per for i in range(B)]
+    b = gen.batch_from_lists([3], [bags], d=16, seed=2)
+    t = torch.zeros((3, 16), dtype=torch.float32, device=DEV)
+    dT = torch.ones((B, 2, 16), dtype=torch.float32, device=DEV)
+    dT[17, 1, 3] = float("inf")
+    counts = _run_update(b, [t], dT, 1.0, "sort")
+    assert counts["hot_rows"] == 2
+    want = -np.array([[per * B] * 16, [per] * 16, [per * (B - 1)] * 16], dtype=np.float32)
+    want[0, 3] = want[1, 3] = -np.inf
+    assert np.array_equal(t.cpu().numpy(), want)
