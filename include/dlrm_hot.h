@@ -292,8 +292,8 @@ int32_t dlrm_emb_bag_bwd_adagrad(const dlrm_sparse_batch* batch, void* const* st
  * and the interaction run, then call dlrm_emb_bag_bwd_sgd with
  * algo = DLRM_BWD_SORT_PREPARED, the same batch and the same workspace once both
  * streams have met (the caller orders the two calls, e.g. with an event; nothing
- * else may touch the workspace in between).  Prepare + prepared update perform the
- * same launches as one DLRM_BWD_SORT call and give the same bits.
+ * else may touch the workspace in between).  Prepare + prepared update give
+ * the same bits as one DLRM_BWD_SORT call (which leaves the partition out where a batch is small).
  * An update with DLRM_BWD_SORT_PREPARED on a workspace that was not prepared for
  * this batch is undefined (it is not detected).
  */

@@ -75,6 +75,12 @@ constexpr int kSegKeys = 1 << kSegMaxBits;
 constexpr int kSmallBatch = 65536;              // up to this many lookups the four launches that only
                                                 // serve oversized buckets and hot rows cost more (~16 us)
                                                 // than one workgroup doing that work in place ever could
+// Up to this many lookups per table on average a batch of at most kSmallBatch lookups is not partitioned at all: a
+// bucket's workgroup picks its pairs out of the table's lookups (direct_reduce_kernel).  Update with / without a
+// partition, one table of 1024, 4096, 16384, 60000 lookups (d = 64): 19.3 / 12.3, 20.3 / 14.7, 21.3 / 21.3, 27.5 / 45.6
+// us; four tables of 4096, 8192: 20.9 / 16.4, 21.8 / 23.9 us; 26 x 2048 one-hot (d = 16): 28.5 / 23.9 us.
+constexpr int kDirectPerTable = 4096;
+constexpr int kRouteWords = 8;                  // words a workgroup keeps its route counters in (GroupArgs::direct)
 constexpr int kCandMin = 128;                   // a row with this many of an oversized bucket's first
                                                 // kBktCap pairs is split off before any sorting
 constexpr int kCand = kBktCap / kCandMin;       // at most this many such rows
@@ -82,6 +88,10 @@ constexpr int kDenseFrom = 8;                   // tables with at least this man
                                                 // have them summed as a dense contraction on the matrix cores
 // Route counters of an update, kept behind the two segment counters in seg_meta (zeroed by the
 // partition, read back by dlrm_emb_bag_bwd_route_counts): how often each rarely taken route ran.
+constexpr int kRouteDirect = 2;                 // 1 after an update without a partition: the counters lie bucket by
+                                                // bucket in hist, kRouteWords words each, laid out like seg_meta
+                                                // (kRouteHeavy, kRouteOver: the bucket is heavy / oversized)
+constexpr int kRouteHeavy = 2, kRouteOver = 3;
 constexpr int kRouteSplit = 4;                  // oversized buckets that split off dominant rows
 constexpr int kRouteGlobalSort = 5;             // lists sorted by one workgroup through global memory
 constexpr int kRouteOneRow = 6;                 // oversized buckets holding a single row
@@ -101,7 +111,7 @@ struct WsLayout {
   size_t hot_cnt;            // uint32[K]: queued hot runs per table
   size_t over_list;          // uint32[nnz / kBigMin + 1]: heavy buckets, handed to the first workgroups
   size_t segs;               // SegInfo[nnz / kBktCap + 2]: those of them sorted by many workgroups
-  size_t seg_meta;           // uint32[8]: segment tiles, segments, -, -, route counters (kRoute*)
+  size_t seg_meta;           // uint32[8]: segment tiles, segments, kRouteDirect, -, route counters (kRoute*)
   size_t huge_runs;          // HugeRun[nnz / kHugeRun + K]: table k's list starts at sum_{j<k}(nnz_j/kHugeRun + 1)
   size_t huge_part;          // float[max_runs * bag groups * d], where more groups fit nowhere else (launch_hot)
   size_t total;
@@ -179,6 +189,7 @@ struct GroupArgs {            // everything the grouping kernels need
   int32_t top_bits;           // bits of the partition digit (0..kMaxTopBits)
   int32_t by_die;             // buckets dealt to the dies by table (bucket_id_of_block)
   int32_t fused_scan;         // 1: the scatter derives its offsets from the raw tile counts
+  int32_t direct;             // 1: no partition, every bucket's workgroup picks its pairs out of the batch
   int32_t no_tail;            // 1: small batch, the segment and hot-row launches are left out and
                               //    bucket_reduce handles whatever they would have taken
   uint32_t* keys[2];
@@ -546,6 +557,7 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   // buckets unless it has more tables than lookups, whose few tiles each the scatter may as well add up itself
   g.fused_scan = L.nt_max <= kFusedScanMaxTiles || ((int64_t)s->K << tb) > s->nnz_total ? 1 : 0;
   g.no_tail = s->nnz_total <= kSmallBatch ? 1 : 0;
+  g.direct = g.no_tail && s->nnz_total <= (int64_t)kDirectPerTable * s->K ? 1 : 0;
   for (int i = 0; i < 2; ++i) {
     g.keys[i] = reinterpret_cast<uint32_t*>(base + L.keys[i]);
     g.vals[i] = reinterpret_cast<uint32_t*>(base + L.vals[i]);

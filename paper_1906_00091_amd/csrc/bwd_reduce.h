@@ -618,6 +618,25 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
   reduce_runs<DT, G, OPT, WT>(a, u, rest, W, s.skey, s.sval, s.heads, 0u, nruns, s.longs, nlong, 0, part);
 }
 
+// A bucket of more than kBktCap pairs (pair buffer 1).
+template <int DT, int G, int OPT, bool WT>
+__device__ inline void reduce_beyond_lds(const GroupArgs& a, const UpdArgs& u, const Bucket& b, char* W, SortLds& s,
+                                         SplitLds& sp, float* part) {
+  if (b.low_bits == 0) {  // the bucket holds one row: a single run, already in position order
+    if (threadIdx.x == 0) {
+      s.heads[0] = 0;
+      s.heads[1] = b.n;
+      atomicAdd(&a.seg_meta[kRouteOneRow], 1u);
+    }
+    __syncthreads();
+    const uint32_t nlong = collect_long_runs(s, 1, long_run<G>());
+    reduce_runs<DT, G, OPT, WT>(a, u, b, W, a.keys[1] + b.start, a.vals[1] + b.start, s.heads, 0u, 1, s.longs, nlong, 1,
+                       part);
+    return;
+  }
+  reduce_oversized<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
+}
+
 template <int DT, int G, int OPT, bool WT>
 // register budget: 4 wavefronts per SIMD for 16-bit tables with SGD, 3 (168 registers) otherwise -- measured both ways
 // on the multi-hot and one-hot workloads (fp32: 3 is 2 % ahead) and on the hot-row one (fp16: 4 is 12 % ahead)
@@ -669,21 +688,233 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
     reduce_slabs<DT, G, OPT, WT>(u, b, W, s.skey, s.sval, b.n, part, s.heads, rw);
     return;
   }
-  if (b.low_bits == 0) {  // the bucket holds one row: a single run, already in position order
-    if (threadIdx.x == 0) {
-      s.heads[0] = 0;
-      s.heads[1] = b.n;
-      atomicAdd(&a.seg_meta[kRouteOneRow], 1u);
-    }
-    __syncthreads();
-    const uint32_t nlong = collect_long_runs(s, 1, long_run<G>());
-    reduce_runs<DT, G, OPT, WT>(a, u, b, W, a.keys[1] + b.start, a.vals[1] + b.start, s.heads, 0u, 1, s.longs, nlong, 1,
-                       part);
-    return;
-  }
-  reduce_oversized<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
+  reduce_beyond_lds<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
 }
 
+// --- 4, small batches: no partition --------------------------------------------------------------
+// Bag of a position of table k: binary search in kThreads evenly spaced offsets held in LDS, then
+// between two of them in memory (bags may be empty: the last bag that starts at or before the position).
+struct BagSearch {
+  const int64_t* off;   // offsets of the table, B + 1 of them
+  const uint32_t* smp;  // LDS: off[i * step], i < nsmp
+  uint32_t B, nsmp, step, fixed;   // fixed: lookups per bag if the count divides evenly, else 0
+  // N positions at once, so that their probes are in flight together; bags of one length need one guess each instead
+  // of a chain of probes
+  template <int N>
+  __device__ void find_all(const uint32_t* pos, uint32_t* bag) const {
+    if (step > 2 && fixed != 0) {   // uniform
+      uint32_t lo[N], hi[N];
+      bool good = true;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        bag[j] = fixed == 1 ? pos[j] : pos[j] / fixed;
+        lo[j] = (uint32_t)off[bag[j]];
+        hi[j] = (uint32_t)off[bag[j] + 1];
+      }
+#pragma unroll
+      for (int j = 0; j < N; ++j) good = good && lo[j] <= pos[j] && pos[j] < hi[j];
+      if (__all(good)) return;
+    }
+    uint32_t c[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) c[j] = 0;
+#pragma unroll
+    for (uint32_t w = kThreads / 2; w > 0; w >>= 1) {
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (c[j] + w < nsmp && smp[c[j] + w] <= pos[j]) c[j] += w;
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) bag[j] = c[j] * step;
+    for (uint32_t w = step >> 1; w > 0; w >>= 1) {
+      uint32_t v[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) v[j] = (uint32_t)off[bag[j] + w < B ? bag[j] + w : B];
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (bag[j] + w < B && v[j] <= pos[j]) bag[j] += w;
+    }
+  }
+};
+
+// Lookups [0, nk) of a table whose row has the partition digit dg, in position order: put(i, row, position)
+// for the i-th of them.  Wavefront w takes positions [w * 512, w * 512 + 512) of every 2048; the next 2048 row
+// ids are in flight while these are dealt with.  Returns their number; *less: how many rows this thread saw with a
+// smaller digit.  cnt: LDS, 2 * kNW words.  All threads call it.
+template <typename IT, typename PUT>
+__device__ inline uint32_t pick_lookups(const IT* idx, uint32_t nk, uint32_t dg, int shift, uint32_t* cnt, uint32_t* less,
+                                        PUT put) {
+  const int lane = lane_id(), w = wave_id();
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  const uint32_t first = (uint32_t)(w * (DLRM_WAVE * kBktItems) + lane);
+  uint32_t key[kBktItems], nxt[kBktItems], run = 0, below = 0, par = 0;
+#pragma unroll
+  for (int j = 0; j < kBktItems; ++j) {
+    const uint32_t p = first + j * DLRM_WAVE;
+    key[j] = (uint32_t)idx[p < nk ? p : nk - 1];
+  }
+  for (uint32_t c0 = 0; c0 < nk; c0 += kBktCap) {  // uniform
+    if (c0 + kBktCap < nk) {
+#pragma unroll
+      for (int j = 0; j < kBktItems; ++j) {
+        const uint32_t p = c0 + kBktCap + first + j * DLRM_WAVE;
+        nxt[j] = (uint32_t)idx[p < nk ? p : nk - 1];
+      }
+    }
+    uint32_t mine = 0, rank[kBktItems];
+    bool hit[kBktItems];
+#pragma unroll
+    for (int j = 0; j < kBktItems; ++j) {
+      const bool valid = c0 + first + j * DLRM_WAVE < nk;
+      const uint32_t kd = key[j] >> shift;
+      hit[j] = valid && kd == dg;
+      below += valid && kd < dg ? 1u : 0u;
+      const unsigned long long m = __ballot(hit[j]);
+      rank[j] = mine + (uint32_t)__popcll(m & lt);
+      mine += (uint32_t)__popcll(m);
+    }
+    if (lane == 0) cnt[par * kNW + w] = mine;
+    __syncthreads();   // the other half of cnt is written next: no second barrier
+    uint32_t before = run;
+#pragma unroll
+    for (int i = 0; i < kNW; ++i) {
+      const uint32_t c = cnt[par * kNW + i];
+      before += i < w ? c : 0u;
+      run += c;
+    }
+    par ^= 1u;
+#pragma unroll
+    for (int j = 0; j < kBktItems; ++j)
+      if (hit[j]) put(before + rank[j], key[j], c0 + first + j * DLRM_WAVE);
+#pragma unroll
+    for (int j = 0; j < kBktItems; ++j) key[j] = nxt[j];
+  }
+  *less = below;
+  return run;
+}
+
+// A batch of few lookups (GroupArgs::direct) has no steps 1-3: the workgroup of bucket (table, digit) reads all row ids
+// of the table and keeps its own.  The row ids are read once per bucket, from L2 (a few MB in all), in place of two
+// launches that move every pair through memory; sorted pairs, bags and sums are those of the partitioned path, bit for
+// bit.  Bound by the chain of latencies: row ids, sort, offsets, gradient and table rows.
+template <int DT, int G, int OPT, bool WT>
+__global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 : 4) void direct_reduce_kernel(GroupArgs a, UpdArgs u) {
+  __shared__ SortLds s;
+  __shared__ SplitLds sp;
+  __shared__ float part[kThreads * 4];
+  __shared__ float wext[WT ? kBktCap - kResolvedLo : 1];
+  const int tid = threadIdx.x;
+  const uint32_t id = blockIdx.x;
+  Bucket b;
+  b.k = (int)(id >> a.top_bits);
+  const uint32_t dg = id & ((1u << a.top_bits) - 1u);
+  if (tid == 0 && id == 0) a.seg_meta[kRouteDirect] = 1u;
+  a.seg_meta = a.hist + (size_t)id * kRouteWords;   // this workgroup's own counters
+  if (tid < kRouteWords) a.seg_meta[tid] = 0u;
+  const int64_t tbl = a.tbl_off[b.k];
+  const uint32_t nk = (uint32_t)(a.tbl_off[b.k + 1] - tbl);
+  const int shift = top_shift(a, b.k);
+  if (nk == 0 || ((int64_t)dg << shift) >= a.rows[b.k]) return;
+  BagSearch bags;
+  bags.off = a.offsets + (int64_t)b.k * (a.B + 1);
+  bags.B = (uint32_t)a.B;
+  bags.step = 1;
+  while (bags.step * kThreads < bags.B) bags.step <<= 1;
+  bags.nsmp = (bags.B + bags.step - 1) / bags.step;
+  bags.fixed = nk % bags.B == 0 ? nk / bags.B : 0u;
+  bags.smp = s.heads;
+  if ((uint32_t)tid < bags.nsmp) s.heads[tid] = (uint32_t)bags.off[(uint32_t)tid * bags.step];
+  auto keep = [&](uint32_t i, uint32_t row, uint32_t pos) {
+    if (i < (uint32_t)kBktCap) {
+      s.skey[i] = row;
+      s.sval[i] = pos;
+    }
+  };
+  uint32_t less;
+  b.n = a.idx32 ? pick_lookups(static_cast<const int32_t*>(a.indices) + tbl, nk, dg, shift, s.longs, &less, keep)
+                : pick_lookups(static_cast<const int64_t*>(a.indices) + tbl, nk, dg, shift, s.longs, &less, keep);
+  b.low_bits = shift;
+  b.start = 0;
+  if (b.n == 0) return;
+  char* W = static_cast<char*>(u.tables[b.k]);
+  if (tid == 0 && b.n > a.big) a.seg_meta[kRouteHeavy] = 1u;
+  __syncthreads();
+  if (b.n <= (uint32_t)kBktCap) {
+    sort_bucket_lds<true>(a, b, s);
+    uint32_t pos[kBktItems], bag[kBktItems];
+    float ew[WT ? kBktItems : 1];
+#pragma unroll
+    for (int j = 0; j < kBktItems; ++j) {
+      const uint32_t li = tid + j * kThreads;
+      pos[j] = s.sval[li < b.n ? li : 0];
+    }
+    __syncthreads();   // sval[0] may be read by every thread, and its owner rewrites it below
+    if constexpr (WT) {
+#pragma unroll
+      for (int j = 0; j < kBktItems; ++j) ew[j] = a.weights[tbl + pos[j]];
+    }
+    if (b.n <= (uint32_t)(2 * kThreads)) {
+      bags.find_all<2>(pos, bag);
+    } else {
+      bags.find_all<kBktItems>(pos, bag);
+    }
+    const ResolvedW rw{reinterpret_cast<float*>(&s.wcnt[0][0]), wext};
+#pragma unroll
+    for (int j = 0; j < kBktItems; ++j) {  // a thread rewrites only the slots it read
+      const uint32_t li = tid + j * kThreads;
+      if (li < b.n) {
+        s.sval[li] = bag[j];
+        if constexpr (WT) rw.at(li) = ew[j];
+      }
+    }
+    __syncthreads();
+    reduce_slabs<DT, G, OPT, WT>(u, b, W, s.skey, s.sval, b.n, part, s.heads, rw);
+    return;
+  }
+  // too many pairs for the LDS sort: the bucket is laid out in pair buffer 1 as the partition would
+  if (tid == 0) a.seg_meta[kRouteOver] = 1u;
+  {
+    uint32_t all;
+    block_exclusive_scan<kThreads>(less, s.smem, &all);
+    b.start = (uint32_t)tbl + all;
+  }
+  uint32_t* kout = a.keys[1] + b.start;
+  uint32_t* vout = a.vals[1] + b.start;
+  auto move = [&](uint32_t i, uint32_t row, uint32_t pos) {
+    kout[i] = row;
+    vout[i] = pos;
+  };
+  if (a.idx32)
+    pick_lookups(static_cast<const int32_t*>(a.indices) + tbl, nk, dg, shift, s.longs, &less, move);
+  else
+    pick_lookups(static_cast<const int64_t*>(a.indices) + tbl, nk, dg, shift, s.longs, &less, move);
+  __syncthreads();
+  for (uint32_t i0 = 0; i0 < b.n; i0 += kBktCap) {   // positions -> bags (weighted: bags and weights beside them)
+    uint32_t pos[kBktItems], bag[kBktItems];
+#pragma unroll
+    for (int j = 0; j < kBktItems; ++j) {
+      const uint32_t i = i0 + tid + j * kThreads;
+      pos[j] = vout[i < b.n ? i : b.n - 1];
+    }
+    if (i0 + kBktCap >= b.n) __syncthreads();   // uniform: the last entry has been read by all before its owner rewrites it
+    bags.find_all<kBktItems>(pos, bag);
+#pragma unroll
+    for (int j = 0; j < kBktItems; ++j) {
+      const uint32_t i = i0 + tid + j * kThreads;
+      if (i >= b.n) continue;
+      if constexpr (WT) {
+        PosEntry pe;
+        pe.bag = bag[j];
+        pe.w = a.weights[tbl + pos[j]];
+        a.pos_entry[tbl + pos[j]] = pe;
+      } else {
+        vout[i] = bag[j];
+      }
+    }
+  }
+  __syncthreads();
+  reduce_beyond_lds<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
+}
 
 template <int DT, int G, int OPT, bool WT>
 __global__ __launch_bounds__(kThreads) void segment_reduce_kernel(GroupArgs a, UpdArgs u) {
@@ -705,9 +936,13 @@ __global__ __launch_bounds__(kThreads) void segment_reduce_kernel(GroupArgs a, U
 
 template <int DT, int G, int OPT, bool WT>
 static int launch_reduce(const GroupArgs& g, const UpdArgs& u, int K, const dlrm_bwd_timing* tm, hipStream_t st) {
-  const unsigned blocks = ((unsigned)K << g.top_bits) + (unsigned)g.max_over;
+  const unsigned buckets = (unsigned)K << g.top_bits;
   if (tm && tm->ev_start && hipEventRecord(static_cast<hipEvent_t>(tm->ev_start), st) != hipSuccess) return DLRM_ERR_HIP;
-  hipLaunchKernelGGL((bucket_reduce_kernel<DT, G, OPT, WT>), dim3(blocks), dim3(kThreads), 0, st, g, u);
+  if (g.direct)
+    hipLaunchKernelGGL((direct_reduce_kernel<DT, G, OPT, WT>), dim3(buckets), dim3(kThreads), 0, st, g, u);
+  else
+    hipLaunchKernelGGL((bucket_reduce_kernel<DT, G, OPT, WT>), dim3(buckets + (unsigned)g.max_over), dim3(kThreads), 0, st,
+                       g, u);
   DLRM_CHECK_LAUNCH();
   if (tm && tm->ev_stop && hipEventRecord(static_cast<hipEvent_t>(tm->ev_stop), st) != hipSuccess) return DLRM_ERR_HIP;
   if (g.no_tail) return DLRM_OK;

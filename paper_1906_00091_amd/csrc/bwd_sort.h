@@ -56,13 +56,15 @@ struct SortLds {
 
 __device__ inline int pass_bits(int left, int passes_left) { return (left + passes_left - 1) / passes_left; }
 
-// Buckets of at most kBktCap pairs (read from pair buffer src): stable LSD passes entirely in
-// LDS.  The pairs end up in s.skey / s.sval in (row, position) order.  The bucket is dealt evenly to
-// the wavefronts, `per` = ceil(n / 256) items a lane (see rank_items).
+// Buckets of at most kBktCap pairs: stable LSD passes entirely in LDS.  The pairs end up in
+// s.skey / s.sval in (row, position) order.  The bucket is dealt evenly to the wavefronts,
+// `per` = ceil(n / 256) items a lane (see rank_items).  FROM_LDS: the n pairs already lie in s.skey /
+// s.sval in position order (after a barrier); else they are read from pair buffer src.
+template <bool FROM_LDS = false>
 __device__ inline void sort_bucket_lds(const GroupArgs& a, const Bucket& b, SortLds& s, int src = 1) {
   const int lane = lane_id(), w = wave_id(), tid = threadIdx.x;
-  const uint32_t* kin = a.keys[src] + b.start;
-  const uint32_t* vin = a.vals[src] + b.start;
+  const uint32_t* kin = FROM_LDS ? s.skey : a.keys[src] + b.start;
+  const uint32_t* vin = FROM_LDS ? s.sval : a.vals[src] + b.start;
   const int n = (int)b.n;
   const int per = (n + kThreads - 1) / kThreads;   // 1..kBktItems, uniform
   uint32_t key[kBktItems], val[kBktItems], dg[kBktItems], rnk[kBktItems];
@@ -76,6 +78,7 @@ __device__ inline void sort_bucket_lds(const GroupArgs& a, const Bucket& b, Sort
     dg[j] = 0;
     rnk[j] = 0;
   }
+  if (FROM_LDS && b.low_bits == 0) return;   // one row: in order where it lies
   const int passes = (b.low_bits + kSortBits - 1) / kSortBits;
   if (passes == 0) {  // a single row per bucket: already in position order
 #pragma unroll

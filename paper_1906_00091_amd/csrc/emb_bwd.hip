@@ -77,24 +77,37 @@ __global__ __launch_bounds__(256) void atomic_update_kernel(AtomArgs a) {
 // reduce launches with the row update OPT.
 __global__ void copy_u32_kernel(const uint32_t* src, uint32_t* dst) { *dst = src ? *src : 0u; }
 
-// One thread copies the counters an update left in the workspace (dlrm_emb_bag_bwd_route_counts).
-__global__ void route_counts_kernel(GroupArgs a, uint32_t* out) {
-  uint32_t hot = 0, dense = 0;
-  for (int k = 0; k < a.K; ++k) {
-    const uint32_t c = a.hot_cnt[k];
-    hot += c;
-    dense += (a.weights == nullptr && c >= (uint32_t)kDenseFrom) ? 1u : 0u;
+// One workgroup copies the counters an update left in the workspace (dlrm_emb_bag_bwd_route_counts): sums over the
+// tables' hot rows, or, after an update without a partition (which has no hot rows), over the buckets' own counters.
+__global__ __launch_bounds__(kThreads) void route_counts_kernel(GroupArgs a, uint32_t* out) {
+  __shared__ uint32_t sum[kRouteWords];
+  const int tid = threadIdx.x;
+  const bool direct = a.seg_meta[kRouteDirect] != 0u;
+  if (tid < kRouteWords) sum[tid] = 0u;
+  __syncthreads();
+  if (direct) {
+    for (uint32_t i = tid; i < ((uint32_t)a.K << a.top_bits) * kRouteWords; i += kThreads)
+      atomicAdd(&sum[i % kRouteWords], a.hist[i]);
+  } else {
+    for (int k = tid; k < a.K; k += kThreads) {
+      const uint32_t c = a.hot_cnt[k];
+      atomicAdd(&sum[0], c);
+      if (a.weights == nullptr && c >= (uint32_t)kDenseFrom) atomicAdd(&sum[1], 1u);
+    }
   }
-  out[0] = *a.list_cnt;
-  out[1] = *a.over_cnt;
-  out[2] = a.seg_meta[1];
-  out[3] = a.seg_meta[0];
-  out[4] = a.seg_meta[kRouteSplit];
-  out[5] = a.seg_meta[kRouteGlobalSort];
-  out[6] = a.seg_meta[kRouteOneRow];
-  out[7] = a.seg_meta[kRouteHugeInPlace];
-  out[8] = hot;
-  out[9] = dense;
+  __syncthreads();
+  if (tid != 0) return;
+  const uint32_t* route = direct ? sum : a.seg_meta;
+  out[0] = direct ? sum[kRouteHeavy] : *a.list_cnt;
+  out[1] = direct ? sum[kRouteOver] : *a.over_cnt;
+  out[2] = direct ? 0u : a.seg_meta[1];
+  out[3] = direct ? 0u : a.seg_meta[0];
+  out[4] = route[kRouteSplit];
+  out[5] = route[kRouteGlobalSort];
+  out[6] = route[kRouteOneRow];
+  out[7] = route[kRouteHugeInPlace];
+  out[8] = direct ? 0u : sum[0];
+  out[9] = direct ? 0u : sum[1];
 }
 
 template <int OPT>
@@ -109,7 +122,8 @@ static int run_sort_path(const dlrm_sparse_batch* s, const UpdArgs& u, void* wor
   if (s->nnz_total == 0) return DLRM_OK;
   GroupArgs g;
   fill_group_args(g, s, L, workspace);
-  if (!prepared) {
+  if (prepared) g.direct = 0;
+  if (!g.direct && !prepared) {
     st = enqueue_partition(s, g, hs);
     if (st != DLRM_OK) return st;
   }
@@ -288,7 +302,7 @@ extern "C" int32_t dlrm_emb_bag_bwd_route_counts(const dlrm_sparse_batch* s, voi
   if (s->nnz_total == 0) return DLRM_ERR_BAD_SHAPE;  // an empty batch never wrote the counters
   GroupArgs g;
   fill_group_args(g, s, L, workspace);
-  hipLaunchKernelGGL(route_counts_kernel, dim3(1), dim3(1), 0, static_cast<hipStream_t>(stream), g, counts);
+  hipLaunchKernelGGL(route_counts_kernel, dim3(1), dim3(kThreads), 0, static_cast<hipStream_t>(stream), g, counts);
   DLRM_CHECK_LAUNCH();
   return DLRM_OK;
 }

@@ -148,3 +148,62 @@ def test_an_infinite_gradient_stays_with_the_hot_rows_it_belongs_to():
     want = -np.array([[per * B] * 16, [per] * 16, [per * (B - 1)] * 16], dtype=np.float32)
     want[0, 3] = want[1, 3] = -np.inf
     assert np.array_equal(t.cpu().numpy(), want)
+
+
+# Batches of at most 65536 lookups, whose buckets pick their pairs out of the table's lookups.
+# name, lookups of every table, bags, rows: chunks of 2048 lookups one short, full and one over; bags of one length
+# (1, 3) and ragged ones with empty ones among them, fewer and more of them than the 256 sampled offsets; single-row
+# and few-row tables, whose buckets outgrow the LDS sort
+DIRECT = [
+    ("chunk-edges-ragged", [2047, 0, 2048, 2049, 1, 4097, 6143], 700, 5000),
+    ("one-lookup", [1], 1, 1),
+    ("one-hot", [2048] * 3, 2048, 1 << 20),
+    ("three-each", [3 * 1025] * 2, 1025, 3000),
+    ("one-bag", [2500, 7], 1, 90),
+    ("256-bags", [4096, 2048, 5], 256, 300),
+    ("257-bags-few-rows", [5000, 2100, 300], 257, 3),
+    ("one-row-tables", [3000, 2048, 0, 2049], 2000, 1),
+    ("mostly-empty-bags", [500, 40, 0, 2600], 9000, 777),
+]
+
+
+@pytest.mark.parametrize("weighted", [False, True], ids=["sum", "pow2-weights"])
+@pytest.mark.parametrize("case", DIRECT, ids=[c[0] for c in DIRECT])
+def test_small_batches_update_as_the_partitioned_path_does(case, weighted):
+    """Exact inputs: the oracle's rows and the routes of the partitioned path.  Any inputs: its bits, with both index
+    types and both optimizers."""
+    name, per_table, B, m = case
+    print("[case] direct %s weighted=%s" % (name, weighted), flush=True)
+    rng = np.random.default_rng([B, m])
+    lengths = [[n // B] * B if n % B == 0 else np.bincount(rng.integers(0, B, size=n), minlength=B).tolist() for n in per_table]
+    K, d = len(per_table), 24
+    b = _batch(lengths, [m] * K, seed=6, d=d)
+    routes = [_assert_exact_update(b, gen.F32, weighted, (mode,)) for mode in ("prepared", "sort")]
+    assert routes[0] == routes[1]
+
+    g = torch.Generator(device=DEV).manual_seed(B)
+    wts = torch.rand(b.nnz, generator=g, device=DEV) if weighted else None
+    dS = torch.randn((B, K, d), generator=g, device=DEV)
+    for dtype, tdt in ((gen.F32, torch.float32), (gen.BF16, torch.bfloat16)):
+        start = torch.randn((K, m, d), generator=g, device=DEV).to(tdt)
+        h0 = torch.rand((K, m, d), generator=g, device=DEV)
+        for itype in (np.int32, np.int64):
+            for adagrad in (False, True):
+                got = []
+                for prepared in (True, False):
+                    t, h = start.clone(), h0.clone()
+                    sb = hot.SparseBatch([t[k] for k in range(K)], dtype, torch.from_numpy(b.indices.astype(itype)).to(DEV),
+                                         torch.from_numpy(b.offsets).to(DEV), torch.from_numpy(b.tbl_off).to(DEV), b.nnz,
+                                         weights=wts)
+                    ws = hot.alloc_workspace(sb)
+                    ws.fill_(0xFF)   # nothing in the workspace is assumed to be zero
+                    if prepared:
+                        hot.dlrm_emb_bag_bwd_prepare(sb, ws)
+                    algo = hot.BWD_SORT_PREPARED if prepared else hot.BWD_SORT
+                    if adagrad:
+                        hot.dlrm_emb_bag_bwd_adagrad(sb, hot.state_pointers([h[k] for k in range(K)]), dS, K * d, d, 0.1, 1e-8,
+                                                     ws, algo=algo)
+                    else:
+                        hot.dlrm_emb_bag_bwd_sgd(sb, dS, K * d, d, 0.1, ws, algo=algo)
+                    got.append((t, h))
+                assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), (dtype, itype, adagrad)
