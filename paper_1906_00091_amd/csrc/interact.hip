@@ -163,10 +163,9 @@ __global__ __launch_bounds__(kIntThreads) void interact_bwd_kernel(const float* 
                                                                     float* __restrict__ dT, int B, int F,
                                                                     int d, int gstride) {
   constexpr int JS = 4 * NB;  // contraction steps of 4 embedding rows
-  // columns per lane and round: 4 (64-column groups) while the operand registers allow three
-  // wavefronts per SIMD (up to 4 row blocks: 144 registers; measured on 65 rows of 128 columns, batch 16384:
-  // 0.348 ms with 2 columns, 0.317 ms with 4), else 2 -- a lane then owns CW consecutive columns of 4 rows
-  constexpr int CW = NB <= 4 ? 4 : 2;
+  // columns per lane and round: 4 (64-column groups; measured on 65 rows of 128 columns, batch 16384: 0.348 ms with 2
+  // columns, 0.317 ms with 4) -- a lane then owns CW consecutive columns of 4 rows
+  constexpr int CW = 4;
   extern __shared__ float lds[];
   const int lane = lane_id();
   const int b = blockIdx.x * kIntWaves + wave_id();
@@ -274,6 +273,180 @@ __global__ __launch_bounds__(kIntThreads) void interact_bwd_kernel(const float* 
   }
 }
 
+// The same contraction, instructions and order with a workgroup of WPS wavefronts per sample: they share one copy of G
+// and take every WPS-th row block each; the last one, which never has more blocks, adds the dense row.
+// G lies in LDS as the 16 x 16 tiles on and below the diagonal of its embedding part (rows of 17 words; the diagonal
+// tiles whole, rows past the last one zero) and its dense column: the A operand of (ib, step s) is one word per lane at
+// a lane offset plus a constant, read along or across a tile, where the triangle as dR stores it costs a dozen address
+// instructions per operand.  dR is fetched in 16-byte pieces, all in flight at once.
+// Taken from five row blocks on (a wavefront per sample there: one wavefront per SIMD, a copy of G each) and up to
+// kSplitBelow samples (SIMDs with one wavefront or none): 101 rows of 64 columns, batch 64 / 1024 / 8192: 54.7 / 60.8 /
+// 295 us with a wavefront per sample, 17.2 / 39.3 / 260 us here; 65 rows of 128: 31.7 / 38.6 / 171 and 11.1 / 28.1 / 182
+// us; 27 rows of 64: 6.1 / 7.2 / 28.5 and 4.7 / 6.3 / 30.4 us.  Bound by the chain of one sample at small batches, by the
+// matrix cores (about half of the time) at large ones.
+constexpr int kGRow = 17, kGTile = 16 * kGRow;
+__host__ __device__ constexpr int g_words(int NB) { return NB * (NB + 1) / 2 * kGTile + 16 * NB; }
+
+template <int NB, int WPS>
+__global__ __launch_bounds__(WPS * DLRM_WAVE) void interact_bwd_tiled_kernel(
+    const float* __restrict__ T, const float* __restrict__ dR, float* __restrict__ dT, int F, int d) {
+  constexpr int JS = 4 * NB;  // contraction steps of 4 embedding rows
+  constexpr int CW = NB <= 4 ? 4 : 2;
+  extern __shared__ __align__(16) float lds[];
+  const int lane = lane_id();
+  const int sub = wave_id();
+  const int b = blockIdx.x;
+  const int x_ = lane & 15, h_ = lane >> 4;
+  const int K = F - 1;
+  const int P = F * (F - 1) / 2;
+  const float* Tb = T + (int64_t)b * F * d;
+  const float* gR = dR + (int64_t)b * ((int64_t)d + P);
+  float* dTb = dT + (int64_t)b * F * d;
+  float* gs = lds;
+  float* gd0 = gs + NB * (NB + 1) / 2 * kGTile;   // g(e + 1, 0)
+  constexpr int NT = WPS * DLRM_WAVE;
+  const int tl = sub * DLRM_WAVE + lane;
+  // pair gradients in 16-byte pieces (dR's rows start anywhere), all requested before anything is waited for;
+  // the pieces that would reach past the sample's last pair are left to single loads
+  const float* gP = gR + d;
+  const int mis = (int)((reinterpret_cast<uintptr_t>(gP) >> 2) & 3);
+  const float* gA = gP - mis;   // aligned; at most 3 words back, which the dense part of dR holds
+  const int nq = (P + mis) >> 2;
+  constexpr int GL = ((16 * NB + 1) * 16 * NB / 8 + NT) / NT;   // pieces per lane
+  f32x4 v[GL];
+#pragma unroll
+  for (int q = 0; q < GL; ++q) {
+    const int t = q * NT + tl;
+    v[q] = loadf4(gA + (t < nq ? t : 0) * 4);
+  }
+  const int tail = nq * 4 - mis + tl;
+  const float vt = tail < P ? gP[tail < 0 ? 0 : tail] : 0.0f;
+  // pair (i, j), i > j, sits at i(i-1)/2 + j; as embedding rows: (i - 1, j - 1), j = 0 the dense row
+  auto put = [&](int e, int f, float val) {
+    const int I = e >> 4, J = f >> 4;
+    const int r = e & 15, c = f & 15;
+    float* tile = gs + (I * (I + 1) / 2 + J) * kGTile;
+    if (f < 0) {
+      gd0[e] = val;
+    } else {
+      tile[r * kGRow + c] = val;
+      if (I == J) tile[c * kGRow + r] = val;
+    }
+  };
+  auto row_of = [](int idx) {
+    int i = (int)((1.0f + sqrtf((float)(8 * idx + 1))) * 0.5f);
+    i -= i * (i - 1) / 2 > idx ? 1 : 0;
+    i += i * (i + 1) / 2 <= idx ? 1 : 0;
+    return i;
+  };
+  float tb[JS][CW], t0v[CW];
+  auto load_rows = [&](int x, int h, int g0) {
+    const int col = g0 + CW * x;
+    const bool cok = col < d;
+    const int ccol = cok ? col : 0;
+    load_cols<CW>(Tb + ccol, cok, t0v);
+#pragma unroll
+    for (int s = 0; s < JS; ++s) {
+      const int e = 4 * s + h;
+      load_cols<CW>(Tb + (int64_t)((e < K ? e : K - 1) + 1) * d + ccol, e < K && cok, tb[s]);
+    }
+  };
+  for (int t = tl * 4; t < g_words(NB); t += NT * 4) storef4(gs + t, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < GL; ++q) {
+    const int t = q * NT + tl, first = 4 * t - mis;
+    if (t >= nq) continue;
+    int i = row_of(first < 0 ? 0 : first), jj = (first < 0 ? 0 : first) - i * (i - 1) / 2;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (first + c < 0) continue;
+      put(i - 1, jj - 1, v[q][c]);
+      if (++jj == i) {
+        ++i;
+        jj = 0;
+      }
+    }
+  }
+  if (tail >= 0 && tail < P && tl < 4) {
+    const int i = row_of(tail);
+    put(i - 1, tail - i * (i - 1) / 2 - 1, vt);
+  }
+  load_rows(x_, h_, 0);
+  __syncthreads();
+  for (int g0 = 0; g0 < d; g0 += 16 * CW) {
+    // opaque copies: without them every row offset, LDS index and validity mask below is
+    // hoisted out of this loop and held in registers, which halves the occupancy
+    int x = x_, h = h_;
+    asm volatile("" : "+v"(x), "+v"(h));
+    const int col = g0 + CW * x;
+    const bool cok = col < d;
+    if (g0 > 0) load_rows(x, h, g0);
+    // gradient of the dense row: dR[0:d] + sum_e g(e+1, 0) S_e
+    if (sub == WPS - 1) {   // uniform
+      float a0[CW];
+#pragma unroll
+      for (int c = 0; c < CW; ++c) a0[c] = 0.0f;
+#pragma unroll
+      for (int s = 0; s < JS; ++s) {
+        const float g0e = gd0[4 * s + h];
+#pragma unroll
+        for (int c = 0; c < CW; ++c) a0[c] = fmaf(g0e, tb[s][c], a0[c]);
+      }
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        a0[c] += __shfl_xor(a0[c], 16, DLRM_WAVE);
+        a0[c] += __shfl_xor(a0[c], 32, DLRM_WAVE);
+      }
+      if (h == 0 && cok) {
+#pragma unroll
+        for (int c = 0; c < CW; ++c) a0[c] += gR[col + c];
+        store_cols<CW>(dTb + col, a0);
+      }
+    }
+    const float* along = gs + x * kGRow + h;
+    const float* across = gs + h * kGRow + x;
+#pragma unroll 1
+    for (int ib = sub; ib < NB; ib += WPS) {  // one row block at a time keeps the register count down
+      if (ib * 16 >= K) break;  // uniform
+      float ga[JS];
+#pragma unroll
+      for (int J = 0; J < NB; ++J) {
+        if (J <= ib) {  // uniform
+          const float* t = along + (ib * (ib + 1) / 2 + J) * kGTile;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) ga[4 * J + q] = t[4 * q];
+        } else {
+          const float* t = across + (J * (J + 1) / 2 + ib) * kGTile;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) ga[4 * J + q] = t[4 * q * kGRow];
+        }
+      }
+      const f32x4 gd = loadf4(gd0 + ib * 16 + 4 * h);   // g(row, 0) of this lane's 4 output rows
+      f32x4 acc[CW];
+#pragma unroll
+      for (int u = 0; u < CW; ++u) acc[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int s = 0; s < JS; ++s) {
+        if (4 * s < K) {  // uniform
+#pragma unroll
+          for (int u = 0; u < CW; ++u) acc[u] = mfma16(ga[s], tb[s][u], acc[u]);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int ei = ib * 16 + 4 * h + v;
+        if (ei < K && cok) {
+          float o[CW];
+#pragma unroll
+          for (int u = 0; u < CW; ++u) o[u] = fmaf(gd[v], t0v[u], acc[u][v]);
+          store_cols<CW>(dTb + (int64_t)(ei + 1) * d + col, o);
+        }
+      }
+    }
+  }
+}
+
 static int check_interact(const void* a, const void* b, int B, int F, int d) {
   if (!a || !b) return DLRM_ERR_NULL;
   if (B < 1 || F < 1 || F > DLRM_MAX_INTERACT_F || d < 4 || (d & 3)) return DLRM_ERR_BAD_SHAPE;
@@ -302,15 +475,24 @@ static int launch_fwd(const float* T, float* R, int B, int F, int d, hipStream_t
   return DLRM_OK;
 }
 
+constexpr int kSplitBelow = 1024;   // samples: one wavefront for each of the machine's SIMDs
+template <int NB>
+static int launch_bwd_tiled(const float* T, const float* dR, float* dT, int B, int F, int d, hipStream_t st) {
+  constexpr int WPS = NB >= 4 ? 4 : NB;
+  constexpr size_t lds = (size_t)g_words(NB) * 4;
+  static_assert(lds <= 64 * 1024, "no more LDS than a launch gets without asking");
+  hipLaunchKernelGGL((interact_bwd_tiled_kernel<NB, WPS>), dim3(B), dim3(WPS * DLRM_WAVE), lds, st, T, dR, dT, F, d);
+  DLRM_CHECK_LAUNCH();
+  return DLRM_OK;
+}
 template <int NB>
 static int launch_bwd(const float* T, const float* dR, float* dT, int B, int F, int d, hipStream_t st) {
-  const int gstride = pair_stride(F);
-  const size_t lds = (size_t)kIntWaves * gstride * 4;
-  if (lds > 64 * 1024) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(interact_bwd_kernel<NB>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return DLRM_ERR_HIP;
+  static_assert(NB <= 4, "more row blocks always take the tiled kernel");
+  if constexpr (NB > 1) {
+    if (B <= kSplitBelow) return launch_bwd_tiled<NB>(T, dR, dT, B, F, d, st);
   }
+  const int gstride = pair_stride(F);
+  const size_t lds = (size_t)kIntWaves * gstride * 4;   // <= 33 KB
   hipLaunchKernelGGL((interact_bwd_kernel<NB>), dim3(div_up(B, kIntWaves)), dim3(kIntThreads), lds, st, T, dR,
                      dT, B, F, d, gstride);
   DLRM_CHECK_LAUNCH();
@@ -353,10 +535,10 @@ extern "C" int32_t dlrm_interact_dot_bwd(const float* T, const float* dR, int32_
     case 2: return launch_bwd<2>(T, dR, dT, B, F, d, hs);
     case 3: return launch_bwd<3>(T, dR, dT, B, F, d, hs);
     case 4: return launch_bwd<4>(T, dR, dT, B, F, d, hs);
-    case 5: return launch_bwd<5>(T, dR, dT, B, F, d, hs);
-    case 6: return launch_bwd<6>(T, dR, dT, B, F, d, hs);
-    case 7: return launch_bwd<7>(T, dR, dT, B, F, d, hs);
-    case 8: return launch_bwd<8>(T, dR, dT, B, F, d, hs);
+    case 5: return launch_bwd_tiled<5>(T, dR, dT, B, F, d, hs);
+    case 6: return launch_bwd_tiled<6>(T, dR, dT, B, F, d, hs);
+    case 7: return launch_bwd_tiled<7>(T, dR, dT, B, F, d, hs);
+    case 8: return launch_bwd_tiled<8>(T, dR, dT, B, F, d, hs);
   }
   return DLRM_ERR_BAD_SHAPE;
 }

@@ -207,3 +207,27 @@ def test_small_batches_update_as_the_partitioned_path_does(case, weighted):
                         hot.dlrm_emb_bag_bwd_sgd(sb, dS, K * d, d, 0.1, ws, algo=algo)
                     got.append((t, h))
                 assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), (dtype, itype, adagrad)
+
+
+# two, three and four row blocks on either side of the batch size up to which wavefronts share a sample; rows of dR at
+# every alignment (d + P odd) and at one
+@pytest.mark.parametrize("F,d", [(18, 20), (33, 128), (34, 36), (50, 72), (65, 16), (65, 68)])
+def test_interaction_backward_gives_the_same_bits_at_any_batch_size(F, d):
+    print("[case] interaction backward F=%d d=%d" % (F, d), flush=True)
+    g = torch.Generator(device=DEV).manual_seed(F)
+    B, P = 1025, F * (F - 1) // 2
+    T = torch.randn((B, F, d), generator=g, device=DEV)
+    dR = torch.randn((B, d + P), generator=g, device=DEV)
+    whole, parts = torch.full_like(T, -5.0), torch.full_like(T, -5.0)
+    hot.dlrm_interact_dot_bwd(T, dR, whole)
+    for b0, b1 in ((0, 1024), (1024, 1025)):
+        hot.dlrm_interact_dot_bwd(T[b0:b1], dR[b0:b1], parts[b0:b1])
+    assert torch.equal(whole, parts)
+    Z = torch.zeros((3, F, F), dtype=torch.float64)
+    i, j = torch.tril_indices(F, F, -1)
+    Z[:, i, j] = dR[:3, d:].double().cpu()
+    want = (Z + Z.transpose(1, 2)) @ T[:3].double().cpu()
+    want[:, 0] += dR[:3, :d].double().cpu()
+    scale = (Z.abs() + Z.abs().transpose(1, 2)) @ T[:3].double().cpu().abs() + 1.0
+    # F + 1 terms, each rounded a few times in fp32: far below 1e-5 of the sum of magnitudes
+    assert ((whole[:3].double().cpu() - want).abs() / scale).max() <= 1e-5
