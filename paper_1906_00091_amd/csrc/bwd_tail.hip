@@ -93,10 +93,13 @@ __global__ __launch_bounds__(kThreads) void segment_sort_kernel(GroupArgs a) {
 // --- the update of the hot rows -----------------------------------------------------------------
 // The workgroup (bag group) of table k that leaves its partial sums last adds them up and updates the
 // rows: a counter per table (zeroed by the reduce kernel of the same call) tells it so, and nobody waits.
-// The barrier puts every thread's partial sums before thread 0's release; its acquire and the second
-// barrier put everybody's before the reads.  Uniform answer; all threads call it.
+// Every wavefront waits until its own partial sums have reached the L2 (a barrier alone does not wait for
+// stores, and thread 0's write-back covers only what lies in the L2 by then); the barrier puts them before
+// thread 0's release; its acquire and the second barrier put everybody's before the reads.  Uniform answer;
+// all threads call it.
 __device__ inline bool last_of_table(const GroupArgs& a, int k, uint32_t groups) {
   __shared__ uint32_t is_last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0)
     is_last = __hip_atomic_fetch_add(&a.hot_done[k], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == groups - 1u;
