@@ -645,8 +645,6 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   __shared__ SplitLds sp;
   __shared__ float part[kThreads * 4];
   __shared__ float wext[WT ? kBktCap - kResolvedLo : 1];
-  if (blockIdx.x == 0)
-    for (int k = threadIdx.x; k < a.K; k += kThreads) a.hot_done[k] = 0u;   // for the hot-row launch of this call
   uint32_t bid;
   bool listed;
   if (!bucket_id_of_block(a, &bid, &listed)) return;
