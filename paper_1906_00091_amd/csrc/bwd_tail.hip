@@ -530,14 +530,15 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
     finish_table<16 * NH>(a, u, kind, k, base, nruns, ngroups);
     return;
   }
-  const float* gk = u.dS + (int64_t)k * u.stride_k + 4 * m;
-  // lanes whose columns lie past the row's end load piece 0 again (no branch around a load) and never store
+  const float* gk = u.dS + (int64_t)k * u.stride_k;
+  // lanes whose columns lie past the row's end load its first four columns (no branch around a load; the
+  // addresses right behind the last row of dS may not be mapped) and never store
   bool col_ok[NH];
   int hoff[NH];
 #pragma unroll
   for (int h = 0; h < NH; ++h) {
     col_ok[h] = 64 * h + 4 * m < u.d;
-    hoff[h] = col_ok[h] ? 64 * h : 0;
+    hoff[h] = col_ok[h] ? 64 * h + 4 * m : 0;
   }
   uint32_t* cm = cmat[w];
   float* red = reinterpret_cast<float*>(&cmat[0][0]);

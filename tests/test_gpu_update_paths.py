@@ -123,6 +123,20 @@ def test_hot_rows_at_the_edges_of_bag_groups(case, weighted):
     assert counts["hot_rows"] == K * rows
 
 
+# rows narrower than a 64-column piece; dT fills whole 2 MiB pages, the last row of the last table ends with them
+@pytest.mark.parametrize("B,d", [(262144, 4), (65536, 32), (131072, 36)])
+def test_dense_hot_rows_read_nothing_behind_the_gradients(B, d):
+    """Nothing is mapped behind an allocation of whole pages: a lane that read past the last row would fault."""
+    print("[case] dense hot rows, narrow B=%d d=%d" % (B, d), flush=True)
+    K = 2
+    assert B * (K + 1) * d * 4 % (2 << 20) == 0 and B * (K + 1) * d * 4 >= 10 << 20
+    torch.cuda.empty_cache()
+    b = gen.make_batch(gen.custom_workload("narrow", K=K, B=B, d=d, dtype=gen.F32, rows=9, bag=("fixed", 1), dist=("uniform",),
+                                           seed=8))
+    counts = _assert_exact_update(b, gen.F32, False, ("sort",))
+    assert counts["hot_rows"] == 9 * K and counts["dense_hot_tables"] == K
+
+
 def test_hot_rows_with_little_room_for_partial_sums():
     """One table with three hot rows among 300 tables of ten lookups: the arrays left over after the grouping hold
     fewer bag groups than the array laid out for partial sums, which is then used."""
