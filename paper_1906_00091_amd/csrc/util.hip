@@ -83,13 +83,15 @@ __global__ __launch_bounds__(kLenThreads) void lengths_scan_kernel(const int32_t
   int64_t* off = offsets + (int64_t)k * (B + 1);
   int64_t carry = 0;
   if (threadIdx.x == 0) off[0] = 0;
-  for (int32_t b0 = 0; b0 < B; b0 += kLenThreads * kLenItems) {
-    const int32_t b = b0 + threadIdx.x * kLenItems;
+  // unsigned: B may come within a round of 2^31, which the last b0 and b then exceed
+  const uint32_t nb = (uint32_t)B;
+  for (uint32_t b0 = 0; b0 < nb; b0 += kLenThreads * kLenItems) {
+    const uint32_t b = b0 + threadIdx.x * kLenItems;
     uint64_t v[kLenItems], sum = 0;
 #pragma unroll
     for (int q = 0; q < kLenItems; ++q) {
-      const uint64_t x = (uint32_t)len[b + q < B ? b + q : B - 1];
-      v[q] = b + q < B ? x : 0u;
+      const uint64_t x = (uint32_t)len[b + q < nb ? b + q : nb - 1];
+      v[q] = b + q < nb ? x : 0u;
       sum += v[q];
     }
     uint64_t total;
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(kLenThreads) void lengths_scan_kernel(const int32_t
 #pragma unroll
     for (int q = 0; q < kLenItems; ++q) {
       run += (int64_t)v[q];
-      if (b + q < B) off[b + q + 1] = run;
+      if (b + q < nb) off[b + q + 1] = run;
     }
     carry += (int64_t)total;
   }

@@ -73,6 +73,25 @@ def test_lengths_to_offsets_is_exact_around_its_launch_limits(K, B):
     assert np.array_equal(off.cpu().numpy(), want_off) and np.array_equal(tbl.cpu().numpy(), want_tbl)
 
 
+@pytest.mark.parametrize("B", [2 ** 31 - 4095, 2 ** 31 - 2])
+def test_lengths_to_offsets_up_to_the_largest_batch(B):
+    """K * (B + 1) up to DLRM_MAX_NNZ: a scan round of 4096 bags ends beyond 2^31."""
+    print("[case] lengths K=1 B=%d" % B, flush=True)
+    if torch.cuda.mem_get_info()[0] < 40 << 30:
+        pytest.skip("needs 26 GB of device memory for lengths and offsets")
+    g = torch.Generator(device=DEV).manual_seed(1)
+    lengths = torch.randint(0, 3, (1, B), generator=g, device=DEV, dtype=torch.int32)
+    off = torch.full((1, B + 1), -7, dtype=torch.int64, device=DEV)
+    tbl = torch.full((2,), -7, dtype=torch.int64, device=DEV)
+    hot.dlrm_lengths_to_offsets(lengths, off, tbl)
+    assert off[0, 0].item() == 0 and tbl.tolist() == [0, off[0, B].item()]
+    for b0 in range(0, B, 1 << 28):
+        n = min(1 << 28, B - b0)
+        assert torch.equal(off[0, b0 + 1:b0 + n + 1] - off[0, b0:b0 + n], lengths[0, b0:b0 + n].long())
+    del lengths, off
+    torch.cuda.empty_cache()
+
+
 def _assert_exact_update(b, dtype, weighted, modes):
     """The update of batch b on exactly representable numbers equals the oracle's; returns the routes of the last mode."""
     w = b.workload
