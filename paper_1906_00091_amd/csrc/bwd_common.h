@@ -144,7 +144,7 @@ inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 inline int hot_group_bags(int d) { return kThreads / pow2_ceil(d / 4) * kHotStagePasses * kHotTilesPerGroup; }
 inline int hot_groups(int B, int d) {
   const int gb = hot_group_bags(d);
-  return (B + gb - 1) / gb;
+  return (int)(((int64_t)B + gb - 1) / gb);
 }
 
 inline WsLayout ws_layout(int32_t K, int32_t B, int32_t d, int64_t nnz) {

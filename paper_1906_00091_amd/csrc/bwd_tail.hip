@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
   constexpr int NG = kThreads / G;                // gradient rows staged per pass of the workgroup
   constexpr int NP = kHotStagePasses;
   constexpr int TB = NG * NP;                     // bags per tile: TB * d <= kHotTileFloats
-  const int GB = TB * ntiles;                     // bags per workgroup, ntiles <= NT
+  const uint32_t GB = (uint32_t)(TB * ntiles);    // bags per workgroup, ntiles <= NT
   __shared__ float tile[kHotTileFloats + kHotZeroRow];  // gradient rows of a bag tile, then a row of zeros
   __shared__ uint32_t cursor[kNW * MR][NT + 1];  // first entry of a run at or after every tile boundary
   __shared__ uint32_t rsrc[kNW * MR];            // pair buffer holding the run
@@ -237,8 +237,9 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
   const int grp = tid / G;
   const bool col_ok = chunk * 4 < u.d;
   const int cchunk = col_ok ? chunk : 0;  // lanes past the last column shadow column group 0, never store
-  const int bag_lo = g * GB;
-  const int bag_hi = bag_lo + GB < a.B ? bag_lo + GB : a.B;
+  // unsigned: the last group may end beyond 2^31
+  const uint32_t bag_lo = (uint32_t)g * GB;
+  const uint32_t bag_hi = bag_lo + GB < (uint32_t)a.B ? bag_lo + GB : (uint32_t)a.B;
   const float* gk = u.dS + (int64_t)k * u.stride_k + cchunk * 4;
   for (int i = tid; i < kHotZeroRow; i += kThreads) tile[kHotTileFloats + i] = 0.0f;
   for (uint32_t r0 = 0; r0 < nruns; r0 += kNW * MR) {  // uniform
@@ -250,8 +251,8 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
       if (r < nruns) {
         const HugeRun hr = a.huge_runs[base + r];
         const uint32_t* bags = (hr.src ? a.vals[1] : a.vals[0]) + hr.start;
-        const int bnd = bag_lo + tb * TB;
-        const uint32_t bound = (uint32_t)(bnd < bag_hi ? bnd : bag_hi);
+        const uint32_t bnd = bag_lo + (uint32_t)(tb * TB);
+        const uint32_t bound = bnd < bag_hi ? bnd : bag_hi;
         uint32_t lo = 0, hi = hr.len;
         while (lo < hi) {
           const uint32_t mid = (lo + hi) >> 1;
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
     // end repeat its last row and are never stored)
     f32x4 stage[NP];
     {
-      const int nb = bag_hi - bag_lo < TB ? bag_hi - bag_lo : TB;
+      const int nb = bag_hi - bag_lo < (uint32_t)TB ? (int)(bag_hi - bag_lo) : TB;
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
         const int bb = p * NG + grp < nb ? p * NG + grp : nb - 1;
@@ -283,8 +284,8 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
       }
     }
     int t = 0;
-    for (int tb0 = bag_lo; tb0 < bag_hi; tb0 += TB, ++t) {  // uniform
-      const int nb = bag_hi - tb0 < TB ? bag_hi - tb0 : TB;
+    for (uint32_t tb0 = bag_lo; tb0 < bag_hi; tb0 += TB, ++t) {  // uniform
+      const int nb = bag_hi - tb0 < (uint32_t)TB ? (int)(bag_hi - tb0) : TB;
       // the first 64 bags of every run of this wave are requested before the tile is stored
       uint32_t first[MR];
 #pragma unroll
@@ -301,7 +302,7 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
       }
       __syncthreads();
       if (tb0 + TB < bag_hi) {  // uniform: the next tile travels while this one is summed
-        const int nn = bag_hi - (tb0 + TB) < TB ? bag_hi - (tb0 + TB) : TB;
+        const int nn = bag_hi - (tb0 + TB) < (uint32_t)TB ? (int)(bag_hi - (tb0 + TB)) : TB;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
           const int bb = p * NG + grp < nn ? p * NG + grp : nn - 1;
@@ -323,7 +324,7 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
           float mw = 0.0f;
           if ((uint32_t)lane < cnt) {
             const PosEntry pe = a.pos_entry[tbl + cur];
-            moff = (pe.bag - (uint32_t)tb0) * (uint32_t)u.d;
+            moff = (pe.bag - tb0) * (uint32_t)u.d;
             mw = pe.w;
           }
           for (uint32_t e = 0; e < cnt; e += HU * S) {
@@ -374,7 +375,7 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
 // 49 hot rows took 81 us, now 18 us with the rows updated (and the launch that did so gone).
 template <int NH>
 __device__ inline void sum_few_runs(const GroupArgs& a, const UpdArgs& u, int k, uint32_t base, uint32_t nruns, int ngroups,
-                                    int wb_lo, int wb_hi, uint32_t* lds) {
+                                    uint32_t wb_lo, uint32_t wb_hi, uint32_t* lds) {
   constexpr int U = NH == 1 ? 8 : NH == 2 ? 4 : 2;
   const int lane = lane_id(), w = wave_id();
   const int m = lane & 15, kk = lane >> 4;
@@ -387,7 +388,7 @@ __device__ inline void sum_few_runs(const GroupArgs& a, const UpdArgs& u, int k,
   uint32_t pos = 0, end = 0, src = 0;
   if ((uint32_t)lane < nruns && wb_lo < wb_hi) {
     const HugeRun hr = a.huge_runs[base + (uint32_t)lane];
-    pos = hr.start + lower_bag((hr.src ? a.vals[1] : a.vals[0]) + hr.start, hr.len, (uint32_t)wb_lo);
+    pos = hr.start + lower_bag((hr.src ? a.vals[1] : a.vals[0]) + hr.start, hr.len, wb_lo);
     end = hr.start + hr.len;
     src = hr.src;
   }
@@ -411,7 +412,7 @@ __device__ inline void sum_few_runs(const GroupArgs& a, const UpdArgs& u, int k,
     for (int h = 0; h < NH; ++h) acc[h] = zero;
     uint32_t cur = ent[q];   // past the run's end: no bag
     for (;;) {
-      const unsigned long long in = __ballot(cur < (uint32_t)wb_hi);   // ascending: a prefix of the lanes
+      const unsigned long long in = __ballot(cur < wb_hi);   // ascending: a prefix of the lanes
       const uint32_t cnt = (uint32_t)__popcll(in);
       if (cnt == 0u) break;  // wave-uniform
       const bool more = cnt == (uint32_t)DLRM_WAVE && c + (uint32_t)DLRM_WAVE < e;
@@ -520,11 +521,11 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
   const uint32_t base = hot_list_base_wave(a, k);
   const int lane = lane_id(), w = wave_id();
   const int m = lane & 15, kk = lane >> 4;
-  // this wavefront's bags
-  const int quarter = group_bags / kNW;
-  int wb_lo = g * group_bags + w * quarter;
-  wb_lo = wb_lo < a.B ? wb_lo : a.B;
-  const int wb_hi = wb_lo + quarter < a.B ? wb_lo + quarter : a.B;
+  // this wavefront's bags (unsigned: the last group may end beyond 2^31)
+  const uint32_t nbags = (uint32_t)a.B, quarter = (uint32_t)group_bags / kNW;
+  uint32_t wb_lo = (uint32_t)g * (uint32_t)group_bags + (uint32_t)w * quarter;
+  wb_lo = wb_lo < nbags ? wb_lo : nbags;
+  const uint32_t wb_hi = wb_lo + quarter < nbags ? wb_lo + quarter : nbags;
   if (nruns < (uint32_t)kDenseFrom) {  // uniform
     sum_few_runs<NH>(a, u, k, base, nruns, ngroups, wb_lo, wb_hi, &cmat[0][0]);
     finish_table<16 * NH>(a, u, kind, k, base, nruns, ngroups);
@@ -565,7 +566,7 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
       rank = lane < R ? rank : (uint32_t)lane;
       uint32_t lo = 0;
       if (len != 0 && wb_lo < wb_hi) {
-        lo = lower_bag((hr.src ? a.vals[1] : a.vals[0]) + hr.start, hr.len, (uint32_t)wb_lo);
+        lo = lower_bag((hr.src ? a.vals[1] : a.vals[0]) + hr.start, hr.len, wb_lo);
       }
       const bool live = len != 0 && wb_lo < wb_hi;
       pos = (uint32_t)__builtin_amdgcn_ds_permute((int)(rank * 4), (int)(live ? hr.start + lo : 0u));
@@ -580,9 +581,8 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[0][h][c] = acc[1][h][c] = zero;
 #pragma unroll 1
-    for (int tb0 = wb_lo; tb0 < wb_hi; tb0 += TB) {  // wave-uniform
-      const int nb = wb_hi - tb0 < TB ? wb_hi - tb0 : TB;
-      const uint32_t bound = (uint32_t)(tb0 + nb);
+    for (uint32_t tb0 = wb_lo; tb0 < wb_hi; tb0 += TB) {  // wave-uniform
+      const uint32_t bound = wb_hi - tb0 < (uint32_t)TB ? wb_hi : tb0 + TB;
       f32x4 bq[PRE][NH];
       for (int i = lane; i < R * CS / 4; i += DLRM_WAVE) reinterpret_cast<u32x4*>(cm)[i] = u32x4{0u, 0u, 0u, 0u};
       // count: the entries of every run that fall into this tile are a prefix of what is left of it
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
             // the end repeat the last one; their counts stay zero)
 #pragma unroll
             for (int s = 0; s < PRE; ++s) {
-              const int bag = tb0 + 4 * s + kk < wb_hi ? tb0 + 4 * s + kk : wb_hi - 1;
+              const uint32_t bag = tb0 + 4 * s + kk < wb_hi ? tb0 + 4 * s + kk : wb_hi - 1u;
 #pragma unroll
               for (int h = 0; h < NH; ++h) bq[s][h] = loadf4(gk + (int64_t)bag * u.stride_b + hoff[h]);
             }
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kern
 #pragma unroll
         for (int h = 0; h < NH; ++h) cur[h] = bq[s % PRE][h];
         if (s + PRE < TB / 4) {
-          const int bag = tb0 + 4 * (s + PRE) + kk < wb_hi ? tb0 + 4 * (s + PRE) + kk : wb_hi - 1;
+          const uint32_t bag = tb0 + 4 * (s + PRE) + kk < wb_hi ? tb0 + 4 * (s + PRE) + kk : wb_hi - 1u;
 #pragma unroll
           for (int h = 0; h < NH; ++h) bq[s % PRE][h] = loadf4(gk + (int64_t)bag * u.stride_b + hoff[h]);
         }
@@ -777,7 +777,7 @@ static int launch_hot(GroupArgs g, const UpdArgs& u, int kind, hipStream_t st) {
     fit = hot_groups(g.B, u.d);
   if (weighted) {
     // tiles per workgroup: enough workgroups for two per compute unit if every table has hot rows
-    const int64_t tiles = (g.B + TB - 1) / TB;
+    const int64_t tiles = ((int64_t)g.B + TB - 1) / TB;
     int64_t nt = (tiles * g.K + 511) / 512;
     if (nt > kHotTilesPerGroup) nt = kHotTilesPerGroup;
     while ((tiles + nt - 1) / nt > fit) ++nt;   // kHotTilesPerGroup tiles always fit

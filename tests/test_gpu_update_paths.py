@@ -167,6 +167,30 @@ def test_hot_rows_with_little_room_for_partial_sums():
         assert _assert_exact_update(b, gen.F32, weighted, ("sort",))["hot_rows"] == 3
 
 
+# one table whose last bag group ends beyond 2^31: 3 rows are gathered, 9 go to the matrix cores
+@pytest.mark.parametrize("weighted", [False, True], ids=["sum", "weighted"])
+@pytest.mark.parametrize("rows", [3, 9])
+def test_hot_rows_of_a_batch_close_to_the_largest(rows, weighted):
+    """Lookups spread evenly over the bags, every bag with the same gradient: each row moves by its count."""
+    B, nnz = 2 ** 31 - 65536, 10000 * 9
+    print("[case] hot rows B=%d rows=%d weighted=%s" % (B, rows, weighted), flush=True)
+    if torch.cuda.mem_get_info()[0] < 40 << 30:
+        pytest.skip("needs 17 GB of device memory for the offsets")
+    off = torch.empty((1, B + 1), dtype=torch.int64, device=DEV)
+    for b0 in range(0, B + 1, 1 << 27):
+        n = min(1 << 27, B + 1 - b0)
+        off[0, b0:b0 + n] = torch.arange(b0, b0 + n, device=DEV) * nnz // B
+    t = torch.zeros((rows, 4), dtype=torch.float32, device=DEV)
+    sb = hot.SparseBatch([t], gen.F32, torch.arange(nnz, device=DEV) % rows, off,
+                         torch.tensor([0, nnz], dtype=torch.int64, device=DEV), nnz,
+                         weights=torch.ones(nnz, device=DEV) if weighted else None)
+    g = torch.tensor([[1.0, -2.0, 3.0, 4.0]], device=DEV)
+    hot.dlrm_emb_bag_bwd_sgd(sb, g, 0, 4, 1.0, hot.alloc_workspace(sb), algo=hot.BWD_SORT)
+    assert torch.equal(t, -(nnz // rows) * g.expand(rows, 4))
+    del off, sb
+    torch.cuda.empty_cache()
+
+
 def test_an_infinite_gradient_stays_with_the_hot_rows_it_belongs_to():
     """Three hot rows, each in every bag but one: the gradient of a bag that does not name a row never meets it."""
     print("[case] hot rows, infinite gradient", flush=True)
