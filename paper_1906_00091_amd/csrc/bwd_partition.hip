@@ -192,25 +192,27 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(GroupArgs a) {
   // b0 = the bag holding the tile's first position: last b with off[b] <= P0.
   const int64_t* off = a.offsets + (int64_t)ti.k * (a.B + 1);
   const int64_t P0 = ti.start - ti.tbl_start;
-  int lo = 0, hi = a.B;  // off[lo] <= P0 (off[0] = 0); the answer lies in [lo, hi)
-  while (hi - lo > 1) {   // 256-ary search, uniform
-    const int step = (hi - lo + kThreads - 1) / kThreads;
-    const int q = lo + (tid + 1) * step;
+  // (bags in unsigned 32 bits: a probe or a round may end beyond 2^31)
+  const uint32_t nbags = (uint32_t)a.B;
+  uint32_t lo = 0, hi = nbags;  // off[lo] <= P0 (off[0] = 0); the answer lies in [lo, hi)
+  while (hi - lo > 1u) {   // 256-ary search, uniform
+    const uint32_t step = (hi - lo + kThreads - 1u) / kThreads;
+    const uint32_t q = lo + (tid + 1u) * step;
     const int pred = (q < hi && off[q] <= P0) ? 1 : 0;
-    const int cnt = __syncthreads_count(pred);   // offsets are monotone: the first cnt probes pass
-    const int nlo = lo + cnt * step;
-    const int nhi = nlo + step < hi ? nlo + step : hi;
+    const uint32_t cnt = (uint32_t)__syncthreads_count(pred);   // offsets are monotone: the first cnt probes pass
+    const uint32_t nlo = lo + cnt * step;
+    const uint32_t nhi = nlo + step < hi ? nlo + step : hi;
     lo = nlo;
     hi = nhi;
   }
-  const int b0 = lo;
+  const uint32_t b0 = lo;
   for (int i = tid; i < TILE; i += kThreads) skey[i] = 0;  // skey doubles as the bag-start counters
   for (int i = tid; i < kNW * kMaxBuckets; i += kThreads) (&wcnt[0][0])[i] = 0;
   __syncthreads();
-  for (int base = b0 + 1;; base += kThreads) {  // bags that start inside the tile (after P0)
-    const int b = base + tid;
-    if (tid == 0) sflag[0] = (b >= a.B || off[b] >= P0 + ti.count) ? 1 : 0;
-    if (b < a.B) {
+  for (uint32_t base = b0 + 1u;; base += kThreads) {  // bags that start inside the tile (after P0)
+    const uint32_t b = base + tid;
+    if (tid == 0) sflag[0] = (b >= nbags || off[b] >= P0 + ti.count) ? 1 : 0;
+    if (b < nbags) {
       const int64_t ob = off[b];
       if (ob < P0 + ti.count) atomicAdd(&skey[(int)(ob - P0)], 1u);
     }
@@ -233,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(GroupArgs a) {
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
       run += c[j];
-      sval[tid * ITEMS + j] = (uint32_t)b0 + run;
+      sval[tid * ITEMS + j] = b0 + run;
     }
   }
   __syncthreads();

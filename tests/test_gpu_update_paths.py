@@ -167,12 +167,14 @@ def test_hot_rows_with_little_room_for_partial_sums():
         assert _assert_exact_update(b, gen.F32, weighted, ("sort",))["hot_rows"] == 3
 
 
-# one table whose last bag group ends beyond 2^31: 3 rows are gathered, 9 go to the matrix cores
+# one table whose last bag group (2^31 - 65536) and whose bag search too (2^31 - 2) end beyond 2^31: 3 rows are
+# gathered, 9 go to the matrix cores
 @pytest.mark.parametrize("weighted", [False, True], ids=["sum", "weighted"])
 @pytest.mark.parametrize("rows", [3, 9])
-def test_hot_rows_of_a_batch_close_to_the_largest(rows, weighted):
+@pytest.mark.parametrize("B", [2 ** 31 - 65536, 2 ** 31 - 2])
+def test_hot_rows_of_a_batch_close_to_the_largest(B, rows, weighted):
     """Lookups spread evenly over the bags, every bag with the same gradient: each row moves by its count."""
-    B, nnz = 2 ** 31 - 65536, 10000 * 9
+    nnz = 10000 * 9
     print("[case] hot rows B=%d rows=%d weighted=%s" % (B, rows, weighted), flush=True)
     if torch.cuda.mem_get_info()[0] < 40 << 30:
         pytest.skip("needs 17 GB of device memory for the offsets")
