@@ -350,6 +350,7 @@ struct Bucket {
   int k;
   uint32_t start, n;   // global position of the bucket's first pair, pairs in the bucket
   int low_bits;        // row-id bits below the partition digit
+  uint32_t* route;     // route counters of its workgroup (kRoute*)
 };
 
 // Heavy buckets (hot rows: long runs, or more pairs than the LDS sort holds) take much longer than
@@ -388,6 +389,7 @@ __device__ inline Bucket bucket_of_block(const GroupArgs& a, uint32_t id) {
   b.start = 0;
   b.n = 0;
   b.low_bits = 0;
+  b.route = a.seg_meta;
   if (a.tbl_off[b.k + 1] == a.tbl_off[b.k]) return b;  // no lookups: its bucket_start is never written
   b.start = a.bucket_start[(size_t)b.k * nb + dg];
   const uint32_t end = dg + 1 < nb ? a.bucket_start[(size_t)b.k * nb + dg + 1] : (uint32_t)a.tbl_off[b.k + 1];

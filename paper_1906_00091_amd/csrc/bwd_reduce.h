@@ -134,7 +134,7 @@ __device__ inline void reduce_runs(const GroupArgs& a, const UpdArgs& u, const B
     const uint32_t r = longs[q];
     const uint32_t i0 = heads[r] - h0, i1 = heads[r + 1] - h0;
     const uint32_t len = i1 - i0;
-    if (len > (uint32_t)kHugeRun && a.no_tail && threadIdx.x == 0) atomicAdd(&a.seg_meta[kRouteHugeInPlace], 1u);
+    if (len > (uint32_t)kHugeRun && a.no_tail && threadIdx.x == 0) atomicAdd(&b.route[kRouteHugeInPlace], 1u);
     if (len > (uint32_t)kHugeRun && !a.no_tail) {  // queue for the multi-workgroup pass
       if (threadIdx.x == 0) {
         HugeRun hr;
@@ -424,7 +424,7 @@ __device__ inline void sort_reduce_large(const GroupArgs& a, const UpdArgs& u, c
     }
     return;
   }
-  if (threadIdx.x == 0) atomicAdd(&a.seg_meta[kRouteGlobalSort], 1u);
+  if (threadIdx.x == 0) atomicAdd(&bk.route[kRouteGlobalSort], 1u);
   const int res = sort_bucket_global(a, bk, s, src);
   __syncthreads();
   const uint32_t* keys = a.keys[res] + bk.start;
@@ -466,7 +466,7 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
     sort_reduce_large<DT, G, OPT, WT>(a, u, b, W, 1, s, part);
     return;
   }
-  if (tid == 0) atomicAdd(&a.seg_meta[kRouteSplit], 1u);
+  if (tid == 0) atomicAdd(&b.route[kRouteSplit], 1u);
   uint32_t cd[kCand];
 #pragma unroll
   for (int c = 0; c < kCand; ++c) cd[c] = sp.cand[c];
@@ -626,7 +626,7 @@ __device__ inline void reduce_beyond_lds(const GroupArgs& a, const UpdArgs& u, c
     if (threadIdx.x == 0) {
       s.heads[0] = 0;
       s.heads[1] = b.n;
-      atomicAdd(&a.seg_meta[kRouteOneRow], 1u);
+      atomicAdd(&b.route[kRouteOneRow], 1u);
     }
     __syncthreads();
     const uint32_t nlong = collect_long_runs(s, 1, long_run<G>());
@@ -807,8 +807,8 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   b.k = (int)(id >> a.top_bits);
   const uint32_t dg = id & ((1u << a.top_bits) - 1u);
   if (tid == 0 && id == 0) a.seg_meta[kRouteDirect] = 1u;
-  a.seg_meta = a.hist + (size_t)id * kRouteWords;   // this workgroup's own counters
-  if (tid < kRouteWords) a.seg_meta[tid] = 0u;
+  b.route = a.hist + (size_t)id * kRouteWords;   // this workgroup's own counters
+  if (tid < kRouteWords) b.route[tid] = 0u;
   const int64_t tbl = a.tbl_off[b.k];
   const uint32_t nk = (uint32_t)(a.tbl_off[b.k + 1] - tbl);
   const int shift = top_shift(a, b.k);
@@ -835,7 +835,7 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   b.start = 0;
   if (b.n == 0) return;
   char* W = static_cast<char*>(u.tables[b.k]);
-  if (tid == 0 && b.n > a.big) a.seg_meta[kRouteHeavy] = 1u;
+  if (tid == 0 && b.n > a.big) b.route[kRouteHeavy] = 1u;
   __syncthreads();
   if (b.n <= (uint32_t)kBktCap) {
     sort_bucket_lds<true>(a, b, s);
@@ -870,7 +870,7 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
     return;
   }
   // too many pairs for the LDS sort: the bucket is laid out in pair buffer 1 as the partition would
-  if (tid == 0) a.seg_meta[kRouteOver] = 1u;
+  if (tid == 0) b.route[kRouteOver] = 1u;
   {
     uint32_t all;
     block_exclusive_scan<kThreads>(less, s.smem, &all);
@@ -926,6 +926,7 @@ __global__ __launch_bounds__(kThreads) void segment_reduce_kernel(GroupArgs a, U
   b.start = sg.start;
   b.n = sg.n;
   b.low_bits = 0;
+  b.route = a.seg_meta;
   char* W = static_cast<char*>(u.tables[b.k]);
   const int dst = (int)(sg.src ^ 1u);
   reduce_window<DT, G, OPT, WT>(a, u, b, W, a.keys[dst] + sg.start, a.vals[dst] + sg.start, t * kBktCap, dst, s, part);
