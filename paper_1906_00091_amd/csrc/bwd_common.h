@@ -92,6 +92,7 @@ constexpr int kRouteDirect = 2;                 // 1 after an update without a p
                                                 // bucket in hist, kRouteWords words each, laid out like seg_meta
                                                 // (kRouteHeavy, kRouteOver: the bucket is heavy / oversized)
 constexpr int kRouteHeavy = 2, kRouteOver = 3;
+constexpr int kHotTables = 3;                   // with a partition: tables with hot rows
 constexpr int kRouteSplit = 4;                  // oversized buckets that split off dominant rows
 constexpr int kRouteGlobalSort = 5;             // lists sorted by one workgroup through global memory
 constexpr int kRouteOneRow = 6;                 // oversized buckets holding a single row
@@ -111,7 +112,7 @@ struct WsLayout {
   size_t hot_cnt;            // uint32[K]: queued hot runs per table
   size_t over_list;          // uint32[nnz / kBigMin + 1]: heavy buckets, handed to the first workgroups
   size_t segs;               // SegInfo[nnz / kBktCap + 2]: those of them sorted by many workgroups
-  size_t seg_meta;           // uint32[8]: segment tiles, segments, kRouteDirect, -, route counters (kRoute*)
+  size_t seg_meta;           // uint32[8]: segment tiles, segments, kRouteDirect, kHotTables, route counters (kRoute*)
   size_t huge_runs;          // HugeRun[nnz / kHugeRun + K]: table k's list starts at sum_{j<k}(nnz_j/kHugeRun + 1)
   size_t huge_part;          // float[max_runs * bag groups * d], where more groups fit nowhere else (launch_hot)
   size_t total;

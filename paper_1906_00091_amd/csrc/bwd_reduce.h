@@ -144,7 +144,9 @@ __device__ inline void reduce_runs(const GroupArgs& a, const UpdArgs& u, const B
         hr.len = len;
         hr.src = (uint32_t)src;
         hr.pad0 = hr.pad1 = hr.pad2 = 0;
-        a.huge_runs[hot_list_base(a, b.k) + atomicAdd(&a.hot_cnt[b.k], 1u)] = hr;
+        const uint32_t nth = atomicAdd(&a.hot_cnt[b.k], 1u);
+        if (nth == 0u) atomicAdd(&a.seg_meta[kHotTables], 1u);
+        a.huge_runs[hot_list_base(a, b.k) + nth] = hr;
       }
       continue;
     }

@@ -374,8 +374,8 @@ __global__ __launch_bounds__(kThreads) void hot_rows_weighted_kernel(GroupArgs a
 // with groups of 2048 bags as before and LDS tiles, 26 bf16 tables of up to 10 M rows, 1.06 M lookups,
 // 49 hot rows took 81 us, now 18 us with the rows updated (and the launch that did so gone).
 template <int NH>
-__device__ inline void sum_few_runs(const GroupArgs& a, const UpdArgs& u, int k, uint32_t base, uint32_t nruns, int ngroups,
-                                    uint32_t wb_lo, uint32_t wb_hi, uint32_t* lds) {
+__device__ inline void sum_few_runs(const GroupArgs& a, const UpdArgs& u, int k, int g, uint32_t base, uint32_t nruns,
+                                    int ngroups, uint32_t wb_lo, uint32_t wb_hi, uint32_t* lds) {
   constexpr int U = NH == 1 ? 8 : NH == 2 ? 4 : 2;
   const int lane = lane_id(), w = wave_id();
   const int m = lane & 15, kk = lane >> 4;
@@ -476,7 +476,7 @@ __device__ inline void sum_few_runs(const GroupArgs& a, const UpdArgs& u, int k,
     f32x4 sum = loadf4(red + q * u.d + col);
 #pragma unroll
     for (int x = 1; x < kNW; ++x) sum += loadf4(red + (x * (kDenseFrom - 1) + q) * u.d + col);
-    storef4(a.huge_part + ((size_t)(base + q) * ngroups + blockIdx.x) * u.d + col, sum);
+    storef4(a.huge_part + ((size_t)(base + q) * ngroups + g) * u.d + col, sum);
   }
 }
 
@@ -508,26 +508,47 @@ constexpr int kDenseCStride = 68;   // words per run of the count matrix: 4m + k
 constexpr int kDensePre = 4;        // 4-bag steps of gradient rows in flight
 constexpr int kDenseHeavy = 4;      // the longest runs of a pass: 256 list entries per request instead of 64
 
+// Bag groups of an unweighted batch: as many as fill the machine once (gfx950: 256 compute units, three resident
+// workgroups each, two for rows above 128 columns) with the tables that do have hot rows, which only the device knows;
+// a wavefront's quarter of a group is whole tiles.  With the groups that fill it if every table has hot rows, one table
+// of 3 hot rows (20 lookups a bag, batch 16384, d = 64) among 300 / 800 / 2000 (batch 8192) tables: update
+// 1346 / 3098 / 3047 us; with these: 671 / 1624 / 2258 us; one such table among 26, batch 65536: 398 and 311 us; every
+// table such a one, one lookup a bag, 100 tables: 182 and 184 us.
+constexpr int hot_slots(int nh) { return 256 * (nh <= 2 ? 3 : 2); }
+constexpr int kHotUnit = kNW * kDenseTile;
+constexpr int kHotGroupMin = 512;   // bags of a group that more workgroups than all tables' share may be launched for
+
 template <int NH>   // 64-column pieces of a gradient row
-__global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kernel(GroupArgs a, UpdArgs u, int kind,
-                                                                                   int ngroups, int group_bags) {
+__global__ __launch_bounds__(kThreads, NH <= 2 ? 3 : 2) void hot_rows_dense_kernel(GroupArgs a, UpdArgs u, int kind) {
   constexpr int R = kDenseRuns, TB = kDenseTile, CS = kDenseCStride, PRE = NH <= 2 ? kDensePre : kDensePre / 2;
   static_assert(R * CS * kNW >= R * 64 * NH, "the reduction buffer aliases the count matrices");
   static_assert(R * CS * kNW >= kNW * (kDenseFrom - 1) * 64 * NH + kNW * 2 * DLRM_WAVE, "and so do sum_few_runs' buffers");
   __shared__ __align__(16) uint32_t cmat[kNW][R * CS];   // per wavefront: multiplicity of run r in bag tb0 + b at [r * CS + b]
-  const int k = blockIdx.y, g = blockIdx.x;
+  const uint32_t hot_tables = a.seg_meta[kHotTables];
+  if (hot_tables == 0u) return;  // uniform, as is all up to the bags
+  uint32_t want = (uint32_t)hot_slots(NH) / hot_tables;
+  want = want < gridDim.x ? (want > 1u ? want : 1u) : gridDim.x;
+  // (unsigned: the last group may end beyond 2^31)
+  const uint32_t nbags = (uint32_t)a.B;
+  const uint32_t group_bags = ((nbags + want - 1u) / want + (uint32_t)kHotUnit - 1u) / (uint32_t)kHotUnit * (uint32_t)kHotUnit;
+  const int ngroups = (int)((nbags + group_bags - 1u) / group_bags);   // <= want
+  // the first K * ngroups workgroups in launch order are the ones at work: neighbours go to different dies, whereas
+  // the first ngroups of every gridDim.x may all go to one
+  const int64_t id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (id >= (int64_t)a.K * ngroups) return;
+  const int k = (int)(id / ngroups), g = (int)(id - (int64_t)k * ngroups);
   const uint32_t nruns = a.hot_cnt[k];
-  if (nruns == 0u) return;  // uniform
+  if (nruns == 0u) return;
   const uint32_t base = hot_list_base_wave(a, k);
   const int lane = lane_id(), w = wave_id();
   const int m = lane & 15, kk = lane >> 4;
-  // this wavefront's bags (unsigned: the last group may end beyond 2^31)
-  const uint32_t nbags = (uint32_t)a.B, quarter = (uint32_t)group_bags / kNW;
-  uint32_t wb_lo = (uint32_t)g * (uint32_t)group_bags + (uint32_t)w * quarter;
+  // this wavefront's bags
+  const uint32_t quarter = group_bags / kNW;
+  uint32_t wb_lo = (uint32_t)g * group_bags + (uint32_t)w * quarter;
   wb_lo = wb_lo < nbags ? wb_lo : nbags;
   const uint32_t wb_hi = wb_lo + quarter < nbags ? wb_lo + quarter : nbags;
   if (nruns < (uint32_t)kDenseFrom) {  // uniform
-    sum_few_runs<NH>(a, u, k, base, nruns, ngroups, wb_lo, wb_hi, &cmat[0][0]);
+    sum_few_runs<NH>(a, u, k, g, base, nruns, ngroups, wb_lo, wb_hi, &cmat[0][0]);
     finish_table<16 * NH>(a, u, kind, k, base, nruns, ngroups);
     return;
   }
@@ -747,20 +768,6 @@ int launch_segment_sort(const GroupArgs& g, hipStream_t st) {
   return DLRM_OK;
 }
 
-// Bag groups of an unweighted batch: as many as fill the machine once (gfx950: 256 compute units, three
-// resident workgroups each, two for rows above 128 columns) if every table has hot rows, within the room
-// for partial sums; a wavefront's quarter of a group is whole tiles.
-static void hot_bag_groups(int B, int K, int nh, int64_t max_groups, int* group_bags, int* groups) {
-  const int slots = 256 * (nh <= 2 ? 3 : 2);
-  int64_t n = slots / (K > 0 ? K : 1);
-  if (n > max_groups) n = max_groups;
-  if (n < 1) n = 1;
-  const int unit = kNW * kDenseTile;
-  const int64_t gb = ((B + n - 1) / n + unit - 1) / unit * unit;
-  *group_bags = (int)gb;
-  *groups = (int)((B + gb - 1) / gb);
-}
-
 // Partial sums lie where nothing is left to read once the rows are grouped, if that holds more bag groups
 // than the array laid out for them: the two arrays of the exported grouping or, for a weighted batch (whose
 // records fill those), the partition's tile counts.
@@ -784,9 +791,14 @@ static int launch_hot(GroupArgs g, const UpdArgs& u, int kind, hipStream_t st) {
     const int ng = (int)((tiles + nt - 1) / nt);
     hipLaunchKernelGGL((hot_rows_weighted_kernel<G>), dim3(ng, g.K), dim3(kThreads), 0, st, g, u, kind, ng, (int)nt);
   } else {
-    int group_bags, ng;
-    hot_bag_groups(g.B, g.K, NH, fit, &group_bags, &ng);
-    hipLaunchKernelGGL((hot_rows_dense_kernel<NH>), dim3(ng, g.K), dim3(kThreads), 0, st, g, u, kind, ng, group_bags);
+    // bag groups at most: every table's share of the machine or groups of kHotGroupMin bags, within the room
+    int64_t most = hot_slots(NH) / g.K;
+    const int64_t small = ((int64_t)g.B + kHotGroupMin - 1) / kHotGroupMin, units = ((int64_t)g.B + kHotUnit - 1) / kHotUnit;
+    if (most < small) most = small;
+    if (most > hot_slots(NH)) most = hot_slots(NH);
+    if (most > units) most = units;
+    if (most > fit) most = fit;
+    hipLaunchKernelGGL((hot_rows_dense_kernel<NH>), dim3((unsigned)most, g.K), dim3(kThreads), 0, st, g, u, kind);
   }
   DLRM_CHECK_LAUNCH();
   return DLRM_OK;

@@ -156,6 +156,19 @@ def test_dense_hot_rows_read_nothing_behind_the_gradients(B, d):
     assert counts["hot_rows"] == 9 * K and counts["dense_hot_tables"] == K
 
 
+# one and two tables with hot rows among others: their bag groups are cut by the number of such tables (batch 5000:
+# ten groups of 512 bags for one among 128 tables, whose share of the machine would be six), 3 rows gathered, 9 dense
+@pytest.mark.parametrize("d", [4, 132])
+@pytest.mark.parametrize("hot_at", [(77,), (0, 127)])
+@pytest.mark.parametrize("rows", [3, 9])
+def test_hot_rows_in_few_of_many_tables(rows, hot_at, d):
+    print("[case] hot rows in few tables rows=%d at=%s d=%d" % (rows, hot_at, d), flush=True)
+    B, K = 5000, 128
+    lengths = [[5] * B if k in hot_at else [1 if (b + k) % 9 == 0 else 0 for b in range(B)] for k in range(K)]
+    b = _batch(lengths, [rows if k in hot_at else 400 + k for k in range(K)], seed=rows, d=d)
+    assert _assert_exact_update(b, gen.F32, False, ("sort", "prepared"))["hot_rows"] == rows * len(hot_at)
+
+
 def test_hot_rows_with_little_room_for_partial_sums():
     """One table with three hot rows among 300 tables of ten lookups: the arrays left over after the grouping hold
     fewer bag groups than the array laid out for partial sums, which is then used."""
