@@ -476,13 +476,19 @@ static int launch_fwd(const float* T, float* R, int B, int F, int d, hipStream_t
 }
 
 constexpr int kSplitBelow = 1024;   // samples: one wavefront for each of the machine's SIMDs
+constexpr int kTiledPerLaunch = 1 << 23;   // samples: a launch holds fewer than 2^32 threads
 template <int NB>
 static int launch_bwd_tiled(const float* T, const float* dR, float* dT, int B, int F, int d, hipStream_t st) {
   constexpr int WPS = NB >= 4 ? 4 : NB;
   constexpr size_t lds = (size_t)g_words(NB) * 4;
   static_assert(lds <= 64 * 1024, "no more LDS than a launch gets without asking");
-  hipLaunchKernelGGL((interact_bwd_tiled_kernel<NB, WPS>), dim3(B), dim3(WPS * DLRM_WAVE), lds, st, T, dR, dT, F, d);
-  DLRM_CHECK_LAUNCH();
+  const int64_t row = (int64_t)F * d, grad = (int64_t)d + F * (F - 1) / 2;
+  for (int64_t b0 = 0; b0 < B; b0 += kTiledPerLaunch) {
+    const int n = (int)(B - b0 < kTiledPerLaunch ? B - b0 : kTiledPerLaunch);
+    hipLaunchKernelGGL((interact_bwd_tiled_kernel<NB, WPS>), dim3(n), dim3(WPS * DLRM_WAVE), lds, st, T + b0 * row,
+                       dR + b0 * grad, dT + b0 * row, F, d);
+    DLRM_CHECK_LAUNCH();
+  }
   return DLRM_OK;
 }
 template <int NB>

@@ -303,3 +303,26 @@ def test_interaction_backward_gives_the_same_bits_at_any_batch_size(F, d):
     scale = (Z.abs() + Z.abs().transpose(1, 2)) @ T[:3].double().cpu().abs() + 1.0
     # F + 1 terms, each rounded a few times in fp32: far below 1e-5 of the sum of magnitudes
     assert ((whole[:3].double().cpu() - want).abs() / scale).max() <= 1e-5
+
+
+def test_interaction_backward_beyond_one_launch():
+    """2^24 samples of 82 rows, a workgroup of 256 threads each: more threads than one launch holds.  The samples repeat,
+    so the gradients must too."""
+    print("[case] interaction backward F=82 B=2^24+64", flush=True)
+    F, d, n = 82, 4, 64
+    P, B = F * (F - 1) // 2, (1 << 24) + n
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < B * (2 * F * d + d + P) * 4 + (8 << 30):
+        pytest.skip("needs 275 GB of device memory")
+    g = torch.Generator(device=DEV).manual_seed(F)
+    T, dR = torch.empty((B, F, d), device=DEV), torch.empty((B, d + P), device=DEV)
+    dT = torch.full((B, F, d), -5.0, device=DEV)
+    T.view(-1, n, F, d).copy_(torch.randn((n, F, d), generator=g, device=DEV).expand(B // n, n, F, d))
+    dR.view(-1, n, d + P).copy_(torch.randn((n, d + P), generator=g, device=DEV).expand(B // n, n, d + P))
+    want = torch.empty((n, F, d), device=DEV)
+    hot.dlrm_interact_dot_bwd(T[:n], dR[:n], want)
+    hot.dlrm_interact_dot_bwd(T, dR, dT)
+    for part in dT.view(-1, n, F, d).split(1 << 14):
+        assert (part == want).all()
+    del T, dR, dT, part
+    torch.cuda.empty_cache()
