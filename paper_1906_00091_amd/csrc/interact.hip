@@ -163,9 +163,10 @@ __global__ __launch_bounds__(kIntThreads) void interact_bwd_kernel(const float* 
                                                                     float* __restrict__ dT, int B, int F,
                                                                     int d, int gstride) {
   constexpr int JS = 4 * NB;  // contraction steps of 4 embedding rows
-  // columns per lane and round: 4 (64-column groups; measured on 65 rows of 128 columns, batch 16384: 0.348 ms with 2
-  // columns, 0.317 ms with 4) -- a lane then owns CW consecutive columns of 4 rows
-  constexpr int CW = 4;
+  // columns per lane and round: 4 (64-column groups) while the operand registers allow three
+  // wavefronts per SIMD (up to 4 row blocks: 144 registers; measured on 65 rows of 128 columns, batch 16384:
+  // 0.348 ms with 2 columns, 0.317 ms with 4), else 2 -- a lane then owns CW consecutive columns of 4 rows
+  constexpr int CW = NB <= 4 ? 4 : 2;
   extern __shared__ float lds[];
   const int lane = lane_id();
   const int b = blockIdx.x * kIntWaves + wave_id();
@@ -279,8 +280,8 @@ __global__ __launch_bounds__(kIntThreads) void interact_bwd_kernel(const float* 
 // tiles whole, rows past the last one zero) and its dense column: the A operand of (ib, step s) is one word per lane at
 // a lane offset plus a constant, read along or across a tile, where the triangle as dR stores it costs a dozen address
 // instructions per operand.  dR is fetched in 16-byte pieces, all in flight at once.
-// Taken from five row blocks on (a wavefront per sample there: one wavefront per SIMD, a copy of G each) and up to
-// kSplitBelow samples (SIMDs with one wavefront or none): 101 rows of 64 columns, batch 64 / 1024 / 8192: 54.7 / 60.8 /
+// Taken from six row blocks on (a wavefront per sample there: one wavefront per SIMD, a copy of G each), with five by
+// batch and columns (kSplitBelow5), and with fewer up to kSplitBelow samples (SIMDs with one wavefront or none): 101 rows of 64 columns, batch 64 / 1024 / 8192: 54.7 / 60.8 /
 // 295 us with a wavefront per sample, 17.2 / 39.3 / 260 us here; 65 rows of 128: 31.7 / 38.6 / 171 and 11.1 / 28.1 / 182
 // us; 27 rows of 64: 6.1 / 7.2 / 28.5 and 4.7 / 6.3 / 30.4 us.  Bound by the chain of one sample at small batches, by the
 // matrix cores (about half of the time) at large ones.
@@ -476,6 +477,12 @@ static int launch_fwd(const float* T, float* R, int B, int F, int d, hipStream_t
 }
 
 constexpr int kSplitBelow = 1024;   // samples: one wavefront for each of the machine's SIMDs
+// Five row blocks, where laying G out as tiles is a larger part of the work the fewer the columns: 73 rows of 16 columns,
+// batch 4096 / 6000 / 16384 / 32768: 42.7 / 56.1 / 137 / 263 us with a wavefront per sample, 44.4 / 63.2 / 167 / 328 us
+// with tiles; of 64 columns: 79.0 / 106 / 263 / 501 and 72.3 / 107 / 281 / 551 us; of 128 columns, 4096 / 12000 / 16384:
+// 148 / 377 / 496 and 133 / 371 / 502 us.  From six blocks on tiles are level (90 rows of 4 to 16 columns: 241 and 245 us
+// at batch 16384) or ahead everywhere.
+constexpr int kSplitBelow5 = 4096, kSplitBelow5Wide = 12288;
 constexpr int kTiledPerLaunch = 1 << 23;   // samples: a launch holds fewer than 2^32 threads
 template <int NB>
 static int launch_bwd_tiled(const float* T, const float* dR, float* dT, int B, int F, int d, hipStream_t st) {
@@ -493,12 +500,13 @@ static int launch_bwd_tiled(const float* T, const float* dR, float* dT, int B, i
 }
 template <int NB>
 static int launch_bwd(const float* T, const float* dR, float* dT, int B, int F, int d, hipStream_t st) {
-  static_assert(NB <= 4, "more row blocks always take the tiled kernel");
+  static_assert(NB <= 5, "more row blocks always take the tiled kernel");
   if constexpr (NB > 1) {
-    if (B <= kSplitBelow) return launch_bwd_tiled<NB>(T, dR, dT, B, F, d, st);
+    const int below = NB < 5 ? kSplitBelow : d > 64 ? kSplitBelow5Wide : kSplitBelow5;
+    if (B <= below) return launch_bwd_tiled<NB>(T, dR, dT, B, F, d, st);
   }
   const int gstride = pair_stride(F);
-  const size_t lds = (size_t)kIntWaves * gstride * 4;   // <= 33 KB
+  const size_t lds = (size_t)kIntWaves * gstride * 4;   // <= 52 KB
   hipLaunchKernelGGL((interact_bwd_kernel<NB>), dim3(div_up(B, kIntWaves)), dim3(kIntThreads), lds, st, T, dR,
                      dT, B, F, d, gstride);
   DLRM_CHECK_LAUNCH();
@@ -541,7 +549,7 @@ extern "C" int32_t dlrm_interact_dot_bwd(const float* T, const float* dR, int32_
     case 2: return launch_bwd<2>(T, dR, dT, B, F, d, hs);
     case 3: return launch_bwd<3>(T, dR, dT, B, F, d, hs);
     case 4: return launch_bwd<4>(T, dR, dT, B, F, d, hs);
-    case 5: return launch_bwd_tiled<5>(T, dR, dT, B, F, d, hs);
+    case 5: return launch_bwd<5>(T, dR, dT, B, F, d, hs);
     case 6: return launch_bwd_tiled<6>(T, dR, dT, B, F, d, hs);
     case 7: return launch_bwd_tiled<7>(T, dR, dT, B, F, d, hs);
     case 8: return launch_bwd_tiled<8>(T, dR, dT, B, F, d, hs);

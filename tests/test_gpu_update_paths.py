@@ -281,18 +281,19 @@ def test_small_batches_update_as_the_partitioned_path_does(case, weighted):
                 assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), (dtype, itype, adagrad)
 
 
-# two, three and four row blocks on either side of the batch size up to which wavefronts share a sample; rows of dR at
+# two to five row blocks on either side of the batch size up to which wavefronts share a sample; rows of dR at
 # every alignment (d + P odd) and at one
-@pytest.mark.parametrize("F,d", [(18, 20), (33, 128), (34, 36), (50, 72), (65, 16), (65, 68)])
-def test_interaction_backward_gives_the_same_bits_at_any_batch_size(F, d):
+@pytest.mark.parametrize("F,d,below", [(18, 20, 1024), (33, 128, 1024), (34, 36, 1024), (50, 72, 1024), (65, 16, 1024),
+                                       (65, 68, 1024), (66, 4, 4096), (70, 64, 4096), (81, 68, 12288)])
+def test_interaction_backward_gives_the_same_bits_at_any_batch_size(F, d, below):
     print("[case] interaction backward F=%d d=%d" % (F, d), flush=True)
     g = torch.Generator(device=DEV).manual_seed(F)
-    B, P = 1025, F * (F - 1) // 2
+    B, P = below + 1, F * (F - 1) // 2
     T = torch.randn((B, F, d), generator=g, device=DEV)
     dR = torch.randn((B, d + P), generator=g, device=DEV)
     whole, parts = torch.full_like(T, -5.0), torch.full_like(T, -5.0)
     hot.dlrm_interact_dot_bwd(T, dR, whole)
-    for b0, b1 in ((0, 1024), (1024, 1025)):
+    for b0, b1 in ((0, below), (below, B)):
         hot.dlrm_interact_dot_bwd(T[b0:b1], dR[b0:b1], parts[b0:b1])
     assert torch.equal(whole, parts)
     Z = torch.zeros((3, F, F), dtype=torch.float64)
