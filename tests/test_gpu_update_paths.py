@@ -173,9 +173,12 @@ def test_hot_rows_with_little_room_for_partial_sums():
     """One table with three hot rows among 300 tables of ten lookups: the arrays left over after the grouping hold
     fewer bag groups than the array laid out for partial sums, which is then used."""
     print("[case] hot rows, little room", flush=True)
-    B, K = 1500, 301
-    lengths = [[55] * B] + [[1] * 10 + [0] * (B - 10)] * (K - 1)
-    b = _batch(lengths, [3] + [40] * (K - 1), seed=4, d=256)
+    B, K, d = 3000, 301, 256
+    lengths = [[28] * B] + [[1] * 10 + [0] * (B - 10)] * (K - 1)
+    b = _batch(lengths, [3] + [40] * (K - 1), seed=4, d=d)
+    # groups of 8 LDS tiles of 64 bags laid out; bytes of the leftover arrays: 8 a lookup, or (weighted) 1024 counts a tile
+    laid_out, sums = -(-B // 512), (b.nnz // 2048 + K) * d * 4
+    assert b.nnz * 8 // sums < laid_out and 1024 * 4 * ((b.nnz >> 10) + K) // sums < laid_out
     for weighted in (False, True):
         assert _assert_exact_update(b, gen.F32, weighted, ("sort",))["hot_rows"] == 3
 
@@ -222,34 +225,10 @@ def test_an_infinite_gradient_stays_with_the_hot_rows_it_belongs_to():
     assert np.array_equal(t.cpu().numpy(), want)
 
 
-# Batches of at most 65536 lookups, whose buckets pick their pairs out of the table's lookups.
-# name, lookups of every table, bags, rows: chunks of 2048 lookups one short, full and one over; bags of one length
-# (1, 3) and ragged ones with empty ones among them, fewer and more of them than the 256 sampled offsets; single-row
-# and few-row tables, whose buckets outgrow the LDS sort
-DIRECT = [
-    ("chunk-edges-ragged", [2047, 0, 2048, 2049, 1, 4097, 6143], 700, 5000),
-    ("one-lookup", [1], 1, 1),
-    ("one-hot", [2048] * 3, 2048, 1 << 20),
-    ("three-each", [3 * 1025] * 2, 1025, 3000),
-    ("one-bag", [2500, 7], 1, 90),
-    ("256-bags", [4096, 2048, 5], 256, 300),
-    ("257-bags-few-rows", [5000, 2100, 300], 257, 3),
-    ("one-row-tables", [3000, 2048, 0, 2049], 2000, 1),
-    ("mostly-empty-bags", [500, 40, 0, 2600], 9000, 777),
-]
-
-
-@pytest.mark.parametrize("weighted", [False, True], ids=["sum", "pow2-weights"])
-@pytest.mark.parametrize("case", DIRECT, ids=[c[0] for c in DIRECT])
-def test_small_batches_update_as_the_partitioned_path_does(case, weighted):
+def _assert_as_partitioned(b, m, weighted):
     """Exact inputs: the oracle's rows and the routes of the partitioned path.  Any inputs: its bits, with both index
-    types and both optimizers."""
-    name, per_table, B, m = case
-    print("[case] direct %s weighted=%s" % (name, weighted), flush=True)
-    rng = np.random.default_rng([B, m])
-    lengths = [[n // B] * B if n % B == 0 else np.bincount(rng.integers(0, B, size=n), minlength=B).tolist() for n in per_table]
-    K, d = len(per_table), 24
-    b = _batch(lengths, [m] * K, seed=6, d=d)
+    types and both optimizers.  Tables of m rows; returns the routes."""
+    K, B, d = b.workload.K, b.workload.B, b.workload.d
     routes = [_assert_exact_update(b, gen.F32, weighted, (mode,)) for mode in ("prepared", "sort")]
     assert routes[0] == routes[1]
 
@@ -279,6 +258,62 @@ def test_small_batches_update_as_the_partitioned_path_does(case, weighted):
                         hot.dlrm_emb_bag_bwd_sgd(sb, dS, K * d, d, 0.1, ws, algo=algo)
                     got.append((t, h))
                 assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), (dtype, itype, adagrad)
+    return routes[0]
+
+
+# Batches of at most 65536 lookups, whose buckets pick their pairs out of the table's lookups.
+# name, lookups of every table, bags, rows: chunks of 2048 lookups one short, full and one over; bags of one length
+# (1, 3) and ragged ones with empty ones among them, fewer and more of them than the 256 sampled offsets; single-row
+# tables, whose buckets outgrow the LDS sort, and tables of three rows
+DIRECT = [
+    ("chunk-edges-ragged", [2047, 0, 2048, 2049, 1, 4097, 6143], 700, 5000),
+    ("one-lookup", [1], 1, 1),
+    ("one-hot", [2048] * 3, 2048, 1 << 20),
+    ("three-each", [3 * 1025] * 2, 1025, 3000),
+    ("one-bag", [2500, 7], 1, 90),
+    ("256-bags", [4096, 2048, 5], 256, 300),
+    ("257-bags-few-rows", [5000, 2100, 300], 257, 3),
+    ("one-row-tables", [3000, 2048, 0, 2049], 2000, 1),
+    ("mostly-empty-bags", [500, 40, 0, 2600], 9000, 777),
+]
+
+
+@pytest.mark.parametrize("weighted", [False, True], ids=["sum", "pow2-weights"])
+@pytest.mark.parametrize("case", DIRECT, ids=[c[0] for c in DIRECT])
+def test_small_batches_update_as_the_partitioned_path_does(case, weighted):
+    name, per_table, B, m = case
+    print("[case] direct %s weighted=%s" % (name, weighted), flush=True)
+    rng = np.random.default_rng([B, m])
+    lengths = [[n // B] * B if n % B == 0 else np.bincount(rng.integers(0, B, size=n), minlength=B).tolist() for n in per_table]
+    _assert_as_partitioned(_batch(lengths, [m] * len(per_table), seed=6, d=24), m, weighted)
+
+
+# One long table (its share of the rows' range a digit of 128 rows) among short ones.  name, its lookups by row (or by
+# range of rows) and the route counters of its buckets: rows that dominate their buckets and are split off, beside fewer
+# and more others than the LDS sort takes; ranges without such rows, sorted through global memory; both
+SKEWED = [
+    ("dominant-rows", [(700, 701, 5000), (701, 702, 3000), (2500, 2501, 2500), (640, 768, 900), (0, 4000, 3000)],
+     {"oversized_ranges": 2, "dominant_row_splits": 2, "global_sorts": 0, "huge_runs_in_place": 3}),
+    ("dominant-row-and-long-rest", [(1300, 1301, 6000), (1280, 1408, 4000), (3900, 4000, 4500), (0, 4000, 2000)],
+     {"oversized_ranges": 2, "dominant_row_splits": 1, "global_sorts": 2, "huge_runs_in_place": 1}),
+    ("no-dominant-row", [(1280, 1408, 9000), (2560, 2688, 8000), (3968, 4000, 2700), (0, 128, 2049)],
+     {"oversized_ranges": 4, "dominant_row_splits": 0, "global_sorts": 4, "huge_runs_in_place": 0}),
+]
+
+
+@pytest.mark.parametrize("weighted", [False, True], ids=["sum", "pow2-weights"])
+@pytest.mark.parametrize("case", SKEWED, ids=[c[0] for c in SKEWED])
+def test_small_batches_with_one_long_table(case, weighted):
+    name, parts, want = case
+    print("[case] direct, skewed %s weighted=%s" % (name, weighted), flush=True)
+    rng = np.random.default_rng(len(name))
+    B, m, K = 600, 4000, 8
+    ids = rng.permutation(np.concatenate([rng.integers(lo, hi, size=n) for lo, hi, n in parts]))
+    long = [x.tolist() for x in np.split(ids, np.sort(rng.integers(0, len(ids) + 1, size=B - 1)))]
+    short = [[[int(i) for i in rng.integers(0, m, size=n)] for n in rng.integers(0, 3, size=B)] for _ in range(K - 1)]
+    b = gen.batch_from_lists([m] * K, short[:2] + [long] + short[2:], d=24, seed=6)
+    counts = _assert_as_partitioned(b, m, weighted)
+    assert {n: counts[n] for n in want} == want
 
 
 # two to five row blocks on either side of the batch size up to which wavefronts share a sample; rows of dR at
