@@ -255,8 +255,8 @@ int32_t dlrm_emb_bag_bwd_sgd(const dlrm_sparse_batch* batch, const float* dS, in
  * batches up to ~2.5 M lookups fit); nothing is launched then.
  * All calls on one GPU share that GPU's array: two calls that overlap in time (different streams,
  * or different host threads without stream order between them) race on it -- the caller orders
- * them.  The array keeps the previous call's contents; the first kernel of every call resets the
- * counters the later ones read, nothing else needs to start at zero.
+ * them.  The array keeps the previous call's contents; every call resets the counters it reads
+ * itself, nothing needs to start at zero.
  * The per-GPU address of the array is looked up on the first call on that GPU and kept (the one piece
  * of state the library holds).
  */

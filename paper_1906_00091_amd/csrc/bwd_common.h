@@ -72,13 +72,17 @@ constexpr int kFusedScanMaxTiles = 512;         // fold the scan into the scatte
 constexpr int kSegMaxBits = 13;                 // oversized buckets with at most this many low bits are
                                                 // sorted by many workgroups (per-row counters in LDS)
 constexpr int kSegKeys = 1 << kSegMaxBits;
-constexpr int kSmallBatch = 65536;              // up to this many lookups the four launches that only
-                                                // serve oversized buckets and hot rows cost more (~16 us)
-                                                // than one workgroup doing that work in place ever could
+constexpr int kSmallBatch = 65536;              // up to this many lookups the three launches that only serve
+                                                // oversized buckets and hot rows (4.5 us each with nothing to
+                                                // do) are left out: a workgroup does that work in place
 // Up to this many lookups per table on average a batch of at most kSmallBatch lookups is not partitioned at all: a
 // bucket's workgroup picks its pairs out of the table's lookups (direct_reduce_kernel).  Update with / without a
 // partition, one table of 1024, 4096, 16384, 60000 lookups (d = 64): 19.3 / 12.3, 20.3 / 14.7, 21.3 / 21.3, 27.5 / 45.6
 // us; four tables of 4096, 8192: 20.9 / 16.4, 21.8 / 23.9 us; 26 x 2048 one-hot (d = 16): 28.5 / 23.9 us.
+// The rule sees the mean only (the host does not know the tables' counts), the cost is that of the longest table.  Batches
+// with one long table among short ones, partitioned / not (d = 64): 26 x 2048 with 10240 in one 34 / 24 us, 8 x 512 with
+// 28000 42 / 38 us, 16 x 1000 with 45000 57 / 57 us; where the long table's buckets outgrow the LDS sort as well the
+// partition is ahead: 16 x 100 with 60000 128 / 153 us, 64 x 256 with 40000 325 / 415 us, 300 x 64 with 45000 1716 / 1897 us.
 constexpr int kDirectPerTable = 4096;
 constexpr int kRouteWords = 8;                  // words a workgroup keeps its route counters in (GroupArgs::direct)
 constexpr int kCandMin = 128;                   // a row with this many of an oversized bucket's first
@@ -99,14 +103,19 @@ constexpr int kRouteOneRow = 6;                 // oversized buckets holding a s
 constexpr int kRouteHugeInPlace = 7;            // runs above kHugeRun summed by one workgroup (no tail launches)
 
 // ---------------------------------------------------------------------------
-// Workspace layout (all offsets 256-byte aligned)
+// Workspace layout (all offsets 256-byte aligned).  Arrays with several users hold, in the order of an update:
+//   keys[0]            partition: digit_total from the column scan to the scatter; reduce: pair buffer 0
+//   hist               partition: tile counts; update without a partition: route counters; weighted hot rows: partial sums
+//   tile_heads         segment sort and hot rows: hot_done
+//   seg_start, seg_tbl weighted: PosEntry records, all update long; unweighted hot rows: partial sums
+// The exported grouping uses the last three as named, and runs no reduce.
 struct WsLayout {
   size_t keys[2], vals[2];   // uint32[nnz] ping-pong: row ids / bag ids
   size_t hist;               // uint32[nt_max][1 << top_bits] (room for kMaxBuckets): per-tile digit counts / offsets
   size_t bucket_start;       // uint32[K * kMaxBuckets + 1]
-  size_t tile_heads;         // uint32[nt_max + 1]   (export only)
-  size_t seg_start;          // uint32[nnz + 1]      (export only; a weighted update keeps its nnz
-  size_t seg_tbl;            // uint32[nnz]           8-byte PosEntry records across these two)
+  size_t tile_heads;         // uint32[nt_max + 1]
+  size_t seg_start;          // uint32[nnz + 1]
+  size_t seg_tbl;            // uint32[nnz], adjacent: seg_start and seg_tbl also serve as one array of nnz 8-byte entries
   size_t n_seg;              // uint32[4]            (export only)
   size_t huge_ctr;           // uint32[4]: [2] = listed (heavy) buckets, [3] = oversized buckets among them
   size_t hot_cnt;            // uint32[K]: queued hot runs per table
@@ -594,8 +603,6 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   g.huge_runs = reinterpret_cast<HugeRun*>(base + L.huge_runs);
   g.huge_part = reinterpret_cast<float*>(base + L.huge_part);
 }
-
-// Enqueues steps 1-3: afterwards keys[1]/vals[1] hold the pairs partitioned into buckets and
 
 inline int check_ws(const dlrm_sparse_batch* s, void* ws, size_t bytes, WsLayout* L) {
   *L = ws_layout(s->K, s->B, s->d, s->nnz_total);

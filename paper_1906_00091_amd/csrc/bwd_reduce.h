@@ -692,6 +692,10 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
 }
 
 // --- 4, small batches: no partition --------------------------------------------------------------
+// A value that is the same in all lanes, though the compiler cannot see it (it came out of LDS, or from threadIdx): loops and addresses that
+// depend on it are scalar.
+__device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
 // Bag of a position of table k: binary search in kThreads evenly spaced offsets held in LDS, then
 // between two of them in memory (bags may be empty: the last bag that starts at or before the position).
 struct BagSearch {
@@ -720,9 +724,11 @@ struct BagSearch {
     for (int j = 0; j < N; ++j) c[j] = 0;
 #pragma unroll
     for (uint32_t w = kThreads / 2; w > 0; w >>= 1) {
+      uint32_t v[N];
 #pragma unroll
-      for (int j = 0; j < N; ++j)
-        if (c[j] + w < nsmp && smp[c[j] + w] <= pos[j]) c[j] += w;
+      for (int j = 0; j < N; ++j) v[j] = smp[c[j] + w < nsmp ? c[j] + w : nsmp - 1];
+#pragma unroll
+      for (int j = 0; j < N; ++j) c[j] += c[j] + w < nsmp && v[j] <= pos[j] ? w : 0u;
     }
 #pragma unroll
     for (int j = 0; j < N; ++j) bag[j] = c[j] * step;
@@ -732,65 +738,129 @@ struct BagSearch {
       for (int j = 0; j < N; ++j) v[j] = (uint32_t)off[bag[j] + w < B ? bag[j] + w : B];
 #pragma unroll
       for (int j = 0; j < N; ++j)
-        if (bag[j] + w < B && v[j] <= pos[j]) bag[j] += w;
+        bag[j] += bag[j] + w < B && v[j] <= pos[j] ? w : 0u;
     }
   }
 };
 
-// Lookups [0, nk) of a table whose row has the partition digit dg, in position order: put(i, row, position)
-// for the i-th of them.  Wavefront w takes positions [w * 512, w * 512 + 512) of every 2048; the next 2048 row
-// ids are in flight while these are dealt with.  Returns their number; *less: how many rows this thread saw with a
-// smaller digit.  cnt: LDS, 2 * kNW words.  All threads call it.
-template <typename IT, typename PUT>
-__device__ inline uint32_t pick_lookups(const IT* idx, uint32_t nk, uint32_t dg, int shift, uint32_t* cnt, uint32_t* less,
-                                        PUT put) {
+// Lookups [0, nk) of a table, nk <= kBktCap, whose row has the partition digit dg: rows and positions to s.skey / s.sval in
+// position order.  Wavefront w takes positions [w * 512, w * 512 + 512).  Returns their number.  All threads call it.
+template <typename IT>
+__device__ inline uint32_t pick_lookups(const IT* idx, uint32_t nk, uint32_t dg, int shift, SortLds& s) {
   const int lane = lane_id(), w = wave_id();
   const unsigned long long lt = (1ull << lane) - 1ull;
   const uint32_t first = (uint32_t)(w * (DLRM_WAVE * kBktItems) + lane);
-  uint32_t key[kBktItems], nxt[kBktItems], run = 0, below = 0, par = 0;
+  uint32_t key[kBktItems], rank[kBktItems], mine = 0, before = 0, all = 0;
+  bool hit[kBktItems];
 #pragma unroll
   for (int j = 0; j < kBktItems; ++j) {
     const uint32_t p = first + j * DLRM_WAVE;
     key[j] = (uint32_t)idx[p < nk ? p : nk - 1];
   }
-  for (uint32_t c0 = 0; c0 < nk; c0 += kBktCap) {  // uniform
-    if (c0 + kBktCap < nk) {
 #pragma unroll
-      for (int j = 0; j < kBktItems; ++j) {
-        const uint32_t p = c0 + kBktCap + first + j * DLRM_WAVE;
-        nxt[j] = (uint32_t)idx[p < nk ? p : nk - 1];
-      }
-    }
-    uint32_t mine = 0, rank[kBktItems];
-    bool hit[kBktItems];
+  for (int j = 0; j < kBktItems; ++j) {
+    hit[j] = first + j * DLRM_WAVE < nk && key[j] >> shift == dg;
+    const unsigned long long m = __ballot(hit[j]);
+    rank[j] = mine + (uint32_t)__popcll(m & lt);
+    mine += (uint32_t)__popcll(m);
+  }
+  if (lane == 0) s.longs[w] = mine;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kNW; ++i) {
+    const uint32_t c = s.longs[i];
+    before += i < w ? c : 0u;
+    all += c;
+  }
+#pragma unroll
+  for (int j = 0; j < kBktItems; ++j) {
+    if (!hit[j]) continue;
+    s.skey[before + rank[j]] = key[j];
+    s.sval[before + rank[j]] = first + j * DLRM_WAVE;
+  }
+  return all;
+}
+
+// The same for any number of lookups up to kSmallBatch, in two steps: mark_lookups sets a bit per lookup in s.skey, without
+// barriers and with kMarkItems loads of a lane in flight; marked_positions turns the bits into positions.  Bound by the
+// issue of one wavefront per SIMD: 1 us per 4096 lookups (twice the loads in flight: slower).  Passing the row ids 2048 at
+// a time instead, with a barrier each, and twice where the bucket outgrows the LDS sort, took 46 / 66 / 206 us where this
+// takes 38 / 57 / 155 us (updates of 8, 16, 16 tables with 28000, 45000, 60000 lookups in one of them, d = 64).
+constexpr int kMarkItems = 16;
+static_assert(kSmallBatch <= kBktCap * 32 && kSmallBatch % (DLRM_WAVE * kMarkItems) == 0, "a bit per lookup in SortLds::skey");
+
+// One wavefront's share of a round, kMarkItems words from word c0 on; FULL: none of its lookups lies beyond nk.  Bits beyond
+// nk stay clear.  Returns how many rows have a smaller digit.
+template <bool FULL, typename IT>
+__device__ inline uint32_t mark_words(const IT* idx, uint32_t nk, uint32_t c0, uint32_t dg, int shift,
+                                      unsigned long long* mask) {
+  const uint32_t lane = (uint32_t)lane_id(), left = nk - c0 * DLRM_WAVE;
+  const IT* from = idx + c0 * DLRM_WAVE;
+  uint32_t key[kMarkItems], below = 0, lo = 0, hi = 0;
+#pragma unroll
+  for (int j = 0; j < kMarkItems; ++j) {
+    const uint32_t p = j * DLRM_WAVE + lane;
+    key[j] = (uint32_t)from[FULL || p < left ? p : left - 1];
+  }
+#pragma unroll
+  for (int j = 0; j < kMarkItems; ++j) {
+    const bool valid = FULL || j * DLRM_WAVE + lane < left;
+    const uint32_t kd = key[j] >> shift;
+    const unsigned long long m = __ballot(valid && kd == dg);
+    below += (uint32_t)__popcll(__ballot(valid && kd < dg));
+    lo = lane == (uint32_t)j ? (uint32_t)m : lo;
+    hi = lane == (uint32_t)j ? (uint32_t)(m >> 32) : hi;
+  }
+  if (lane < (uint32_t)kMarkItems) mask[c0 + lane] = ((unsigned long long)hi << 32) | lo;
+  return below;
+}
+
+// Returns how many rows with a smaller digit this wavefront saw.
+template <typename IT>
+__device__ inline uint32_t mark_lookups(const IT* idx, uint32_t nk, uint32_t dg, int shift, unsigned long long* mask) {
+  uint32_t below = 0;
+  for (uint32_t c0 = uniform(wave_id()) * kMarkItems; c0 * DLRM_WAVE < nk; c0 += kNW * kMarkItems) {
+    below += (c0 + kMarkItems) * DLRM_WAVE <= nk ? mark_words<true>(idx, nk, c0, dg, shift, mask)
+                                                 : mark_words<false>(idx, nk, c0, dg, shift, mask);
+  }
+  return below;
+}
+
+// A thread takes consecutive words of the mask: their set bits, and put(before + i, position) for the i-th of them.
+__device__ inline uint32_t marked_words(uint32_t nk) { return ((nk + DLRM_WAVE - 1) / DLRM_WAVE + kThreads - 1) / kThreads; }
+__device__ inline uint32_t count_marked(const unsigned long long* mask, uint32_t nk) {
+  const uint32_t words = (nk + DLRM_WAVE - 1) / DLRM_WAVE, per = marked_words(nk);
+  uint32_t n = 0;
+  for (uint32_t q = threadIdx.x * per; q < (threadIdx.x + 1) * per && q < words; ++q) n += (uint32_t)__popcll(mask[q]);
+  return n;
+}
+template <typename PUT>
+__device__ inline void marked_positions(const unsigned long long* mask, uint32_t nk, uint32_t before, PUT put) {
+  const uint32_t words = (nk + DLRM_WAVE - 1) / DLRM_WAVE, per = marked_words(nk);
+  for (uint32_t q = threadIdx.x * per; q < (threadIdx.x + 1) * per && q < words; ++q) {
+    for (unsigned long long m = mask[q]; m != 0ull; m &= m - 1ull)
+      put(before++, q * DLRM_WAVE + (uint32_t)__ffsll((long long)m) - 1u);
+  }
+}
+
+// rows[i] = idx[pos[i]], i < n
+template <typename IT>
+__device__ inline void rows_of_positions(const IT* idx, const uint32_t* pos, uint32_t n, uint32_t* rows) {
+  for (uint32_t i0 = 0; i0 < n; i0 += kBktCap) {
+    uint32_t p[kBktItems], row[kBktItems];
 #pragma unroll
     for (int j = 0; j < kBktItems; ++j) {
-      const bool valid = c0 + first + j * DLRM_WAVE < nk;
-      const uint32_t kd = key[j] >> shift;
-      hit[j] = valid && kd == dg;
-      below += valid && kd < dg ? 1u : 0u;
-      const unsigned long long m = __ballot(hit[j]);
-      rank[j] = mine + (uint32_t)__popcll(m & lt);
-      mine += (uint32_t)__popcll(m);
+      const uint32_t i = i0 + threadIdx.x + j * kThreads;
+      p[j] = pos[i < n ? i : n - 1];
     }
-    if (lane == 0) cnt[par * kNW + w] = mine;
-    __syncthreads();   // the other half of cnt is written next: no second barrier
-    uint32_t before = run;
 #pragma unroll
-    for (int i = 0; i < kNW; ++i) {
-      const uint32_t c = cnt[par * kNW + i];
-      before += i < w ? c : 0u;
-      run += c;
+    for (int j = 0; j < kBktItems; ++j) row[j] = (uint32_t)idx[p[j]];
+#pragma unroll
+    for (int j = 0; j < kBktItems; ++j) {
+      const uint32_t i = i0 + threadIdx.x + j * kThreads;
+      if (i < n) rows[i] = row[j];
     }
-    par ^= 1u;
-#pragma unroll
-    for (int j = 0; j < kBktItems; ++j)
-      if (hit[j]) put(before + rank[j], key[j], c0 + first + j * DLRM_WAVE);
-#pragma unroll
-    for (int j = 0; j < kBktItems; ++j) key[j] = nxt[j];
   }
-  *less = below;
-  return run;
 }
 
 // A batch of few lookups (GroupArgs::direct) has no steps 1-3: the workgroup of bucket (table, digit) reads all row ids
@@ -824,22 +894,33 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   bags.fixed = nk % bags.B == 0 ? nk / bags.B : 0u;
   bags.smp = s.heads;
   if ((uint32_t)tid < bags.nsmp) s.heads[tid] = (uint32_t)bags.off[(uint32_t)tid * bags.step];
-  auto keep = [&](uint32_t i, uint32_t row, uint32_t pos) {
-    if (i < (uint32_t)kBktCap) {
-      s.skey[i] = row;
-      s.sval[i] = pos;
-    }
-  };
-  uint32_t less;
-  b.n = a.idx32 ? pick_lookups(static_cast<const int32_t*>(a.indices) + tbl, nk, dg, shift, s.longs, &less, keep)
-                : pick_lookups(static_cast<const int64_t*>(a.indices) + tbl, nk, dg, shift, s.longs, &less, keep);
+  const int32_t* const idx4 = static_cast<const int32_t*>(a.indices) + tbl;
+  const int64_t* const idx8 = static_cast<const int64_t*>(a.indices) + tbl;
+  unsigned long long* const mask = reinterpret_cast<unsigned long long*>(s.skey);
+  uint32_t less = 0, before = 0;
+  if (nk <= (uint32_t)kBktCap) {   // uniform
+    b.n = a.idx32 ? pick_lookups(idx4, nk, dg, shift, s) : pick_lookups(idx8, nk, dg, shift, s);
+  } else {
+    less = a.idx32 ? mark_lookups(idx4, nk, dg, shift, mask) : mark_lookups(idx8, nk, dg, shift, mask);
+    __syncthreads();
+    before = block_exclusive_scan<kThreads>(count_marked(mask, nk), s.smem, &b.n);
+  }
+  b.n = uniform(b.n);
   b.low_bits = shift;
   b.start = 0;
   if (b.n == 0) return;
   char* W = static_cast<char*>(u.tables[b.k]);
   if (tid == 0 && b.n > a.big) b.route[kRouteHeavy] = 1u;
-  __syncthreads();
   if (b.n <= (uint32_t)kBktCap) {
+    if (nk > (uint32_t)kBktCap) {   // uniform
+      marked_positions(mask, nk, before, [&](uint32_t i, uint32_t pos) { s.sval[i] = pos; });
+      __syncthreads();
+      if (a.idx32)
+        rows_of_positions(idx4, s.sval, b.n, s.skey);
+      else
+        rows_of_positions(idx8, s.sval, b.n, s.skey);
+    }
+    __syncthreads();
     sort_bucket_lds<true>(a, b, s);
     uint32_t pos[kBktItems], bag[kBktItems];
     float ew[WT ? kBktItems : 1];
@@ -875,41 +956,38 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   if (tid == 0) b.route[kRouteOver] = 1u;
   {
     uint32_t all;
-    block_exclusive_scan<kThreads>(less, s.smem, &all);
-    b.start = (uint32_t)tbl + all;
+    block_exclusive_scan<kThreads>(lane_id() == 0 ? less : 0u, s.smem, &all);
+    b.start = uniform((uint32_t)tbl + all);
   }
   uint32_t* kout = a.keys[1] + b.start;
   uint32_t* vout = a.vals[1] + b.start;
-  auto move = [&](uint32_t i, uint32_t row, uint32_t pos) {
-    kout[i] = row;
-    vout[i] = pos;
-  };
-  if (a.idx32)
-    pick_lookups(static_cast<const int32_t*>(a.indices) + tbl, nk, dg, shift, s.longs, &less, move);
-  else
-    pick_lookups(static_cast<const int64_t*>(a.indices) + tbl, nk, dg, shift, s.longs, &less, move);
+  marked_positions(mask, nk, before, [&](uint32_t i, uint32_t pos) { vout[i] = pos; });
   __syncthreads();
-  for (uint32_t i0 = 0; i0 < b.n; i0 += kBktCap) {   // positions -> bags (weighted: bags and weights beside them)
-    uint32_t pos[kBktItems], bag[kBktItems];
+  if (a.idx32)
+    rows_of_positions(idx4, vout, b.n, kout);
+  else
+    rows_of_positions(idx8, vout, b.n, kout);
+  constexpr int N = kBktItems / 2;
+  for (uint32_t i0 = 0; i0 < b.n; i0 += N * kThreads) {   // positions -> bags (weighted: bags and weights beside them)
+    uint32_t pos[N], bag[N];
 #pragma unroll
-    for (int j = 0; j < kBktItems; ++j) {
+    for (int j = 0; j < N; ++j) {
       const uint32_t i = i0 + tid + j * kThreads;
       pos[j] = vout[i < b.n ? i : b.n - 1];
     }
-    if (i0 + kBktCap >= b.n) __syncthreads();   // uniform: the last entry has been read by all before its owner rewrites it
-    bags.find_all<kBktItems>(pos, bag);
+    if (i0 + N * kThreads >= b.n) __syncthreads();   // uniform: the last entry has been read by all before its owner rewrites it
+    bags.find_all<N>(pos, bag);
+    if constexpr (WT) {
+      float w[N];
 #pragma unroll
-    for (int j = 0; j < kBktItems; ++j) {
-      const uint32_t i = i0 + tid + j * kThreads;
-      if (i >= b.n) continue;
-      if constexpr (WT) {
-        PosEntry pe;
-        pe.bag = bag[j];
-        pe.w = a.weights[tbl + pos[j]];
-        a.pos_entry[tbl + pos[j]] = pe;
-      } else {
-        vout[i] = bag[j];
-      }
+      for (int j = 0; j < N; ++j) w[j] = a.weights[tbl + pos[j]];
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (i0 + tid + j * kThreads < b.n) a.pos_entry[tbl + pos[j]] = PosEntry{bag[j], w[j]};
+    } else {
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (i0 + tid + j * kThreads < b.n) vout[i0 + tid + j * kThreads] = bag[j];
     }
   }
   __syncthreads();

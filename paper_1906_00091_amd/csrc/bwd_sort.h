@@ -45,7 +45,7 @@ __device__ inline void prepare_segments(const GroupArgs& a, uint32_t* smem) {
 
 struct SortLds {
   uint32_t wcnt[kNW][kSortBuckets];
-  uint32_t skey[kBktCap];
+  alignas(8) uint32_t skey[kBktCap];   // (8: also a bit mask of 64-bit words, mark_lookups)
   uint32_t sval[kBktCap];
   uint32_t heads[kBktCap + 1];
   uint32_t base[kSortBuckets];
@@ -212,10 +212,5 @@ __device__ inline bool find_segment_tile(const GroupArgs& a, SegInfo* sg, uint32
   *t = blockIdx.x - sg->tile0;
   return true;
 }
-
-// Every workgroup counts, per row of the segment, the pairs in the tiles before its own and in
-// the whole segment (the segment's keys stream through L2), sorts its own tile in LDS, and
-// writes each pair to  segment start + rows before + same row in earlier tiles + rank in tile:
-// the segment ends up fully sorted by (row, position) in the other pair buffer.
 
 }  // namespace dlrm

@@ -5,6 +5,10 @@
 
 namespace dlrm {
 
+// Every workgroup counts, per row of the segment, the pairs in the tiles before its own and in
+// the whole segment (the segment's keys stream through L2), sorts its own tile in LDS, and
+// writes each pair to  segment start + rows before + same row in earlier tiles + rank in tile:
+// the segment ends up fully sorted by (row, position) in the other pair buffer.
 __global__ __launch_bounds__(kThreads) void segment_sort_kernel(GroupArgs a) {
   __shared__ SortLds s;
   __shared__ uint32_t before[kSegKeys];

@@ -236,7 +236,7 @@ extern "C" int32_t dlrm_emb_bag_bwd_sgd_noalloc(const dlrm_sparse_batch* s, cons
   void* ws = nullptr;
   st = scratch_base(&ws);
   if (st != DLRM_OK) return st;
-  // every counter the update reads is zeroed by the first kernel of the grouping: nothing to clear here
+  // every counter the update reads is zeroed by an earlier kernel, or earlier in the same one: nothing to clear here
   return dlrm_emb_bag_bwd_sgd(s, dS, stride_b, stride_k, lr, ws, (size_t)DLRM_NOALLOC_SCRATCH_BYTES, DLRM_BWD_SORT,
                               stream);
 }

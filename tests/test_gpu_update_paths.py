@@ -264,7 +264,8 @@ def _assert_as_partitioned(b, m, weighted):
 # Batches of at most 65536 lookups, whose buckets pick their pairs out of the table's lookups.
 # name, lookups of every table, bags, rows: chunks of 2048 lookups one short, full and one over; bags of one length
 # (1, 3) and ragged ones with empty ones among them, fewer and more of them than the 256 sampled offsets; single-row
-# tables, whose buckets outgrow the LDS sort, and tables of three rows
+# tables, whose buckets outgrow the LDS sort, and tables of three rows; one table with all but a few of 65536 lookups
+# (buckets beyond LDS), one with 30000 (buckets within it)
 DIRECT = [
     ("chunk-edges-ragged", [2047, 0, 2048, 2049, 1, 4097, 6143], 700, 5000),
     ("one-lookup", [1], 1, 1),
@@ -275,6 +276,8 @@ DIRECT = [
     ("257-bags-few-rows", [5000, 2100, 300], 257, 3),
     ("one-row-tables", [3000, 2048, 0, 2049], 2000, 1),
     ("mostly-empty-bags", [500, 40, 0, 2600], 9000, 777),
+    ("65536-mostly-in-one-table", [1] * 7 + [65521] + [1] * 8, 900, 5000),
+    ("long-table-within-lds", [30000] + [300] * 7, 700, 4000),
 ]
 
 
