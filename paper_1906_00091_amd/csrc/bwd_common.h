@@ -77,8 +77,9 @@ constexpr int kSmallBatch = 65536;              // up to this many lookups the t
                                                 // do) are left out: a workgroup does that work in place
 // Up to this many lookups per table on average a batch of at most kSmallBatch lookups is not partitioned at all: a
 // bucket's workgroup picks its pairs out of the table's lookups (direct_reduce_kernel).  Update with / without a
-// partition, one table of 1024, 4096, 16384, 60000 lookups (d = 64): 19.3 / 12.3, 20.3 / 14.7, 21.3 / 21.3, 27.5 / 45.6
-// us; four tables of 4096, 8192: 20.9 / 16.4, 21.8 / 23.9 us; 26 x 2048 one-hot (d = 16): 28.5 / 23.9 us.
+// partition, one table of 1024, 4096 lookups (d = 64): 23.1 / 12.2, 23.0 / 14.1 us; 4 and 16 tables of 4096: 23.8 / 14.7,
+// 28.4 / 20.3 us; 26 x 2048 one-hot (d = 16): 24.7 / 12.5 us.  The line was drawn where a single table's cost crossed
+// (16384 lookups, row ids then passed 2048 at a time: 21.3 / 21.3 us), with room for tables above the mean.
 // The rule sees the mean only (the host does not know the tables' counts), the cost is that of the longest table.  Batches
 // with one long table among short ones, partitioned / not (d = 64): 26 x 2048 with 10240 in one 34 / 24 us, 8 x 512 with
 // 28000 42 / 38 us, 16 x 1000 with 45000 57 / 57 us; where the long table's buckets outgrow the LDS sort as well the
