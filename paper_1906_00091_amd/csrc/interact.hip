@@ -281,10 +281,11 @@ __global__ __launch_bounds__(kIntThreads) void interact_bwd_kernel(const float* 
 // a lane offset plus a constant, read along or across a tile, where the triangle as dR stores it costs a dozen address
 // instructions per operand.  dR is fetched in 16-byte pieces, all in flight at once.
 // Taken from six row blocks on (a wavefront per sample there: one wavefront per SIMD, a copy of G each), with five by
-// batch and columns (kSplitBelow5), and with fewer up to kSplitBelow samples (SIMDs with one wavefront or none): 101 rows of 64 columns, batch 64 / 1024 / 8192: 54.7 / 60.8 /
-// 295 us with a wavefront per sample, 17.2 / 39.3 / 260 us here; 65 rows of 128: 31.7 / 38.6 / 171 and 11.1 / 28.1 / 182
-// us; 27 rows of 64: 6.1 / 7.2 / 28.5 and 4.7 / 6.3 / 30.4 us.  Bound by the chain of one sample at small batches, by the
-// matrix cores (about half of the time) at large ones.
+// batch and columns (kSplitBelow5), and with fewer up to kSplitBelow samples (SIMDs with one wavefront or none): 101 rows
+// of 64 columns, batch 64 / 1024 / 8192: 54.7 / 60.8 / 295 us with a wavefront per sample, 17.2 / 39.3 / 260 us here; 65
+// rows of 128: 31.7 / 38.6 / 171 and 11.1 / 28.1 / 182 us; 27 rows of 64: 6.1 / 7.2 / 28.5 and 4.7 / 6.3 / 30.4 us.
+// Bound by the chain of one sample at small batches (101 rows of 32 columns, batch 1024: matrix cores busy 16 % of 28 us);
+// at large ones the matrix cores, 700 instructions of 32 cycles a sample, are busy for 75 of the 260 us.
 constexpr int kGRow = 17, kGTile = 16 * kGRow;
 __host__ __device__ constexpr int g_words(int NB) { return NB * (NB + 1) / 2 * kGTile + 16 * NB; }
 
