@@ -423,6 +423,21 @@ struct UpdArgs {
 //   kAdagrad : h <- h + g*g (fp32 state), W <- W - lr * g / (sqrt(h) + eps), element-wise
 constexpr int kSgd = 0, kAdagrad = 1;
 
+// Narrow rows that are not whole 64-byte sectors: a sector holds parts of two or more rows and a bucket's rows are
+// neighbours, so plain loads find in the L2 what streaming ones fetch once per row.  Lookup + update, 8 tables of 1M rows,
+// 1.6M lookups, three sets of tables in turn, streaming / plain loads, us: fp32 SGD, d = 12 180 / 177, 28 264 / 244,
+// 36 294 / 290; Adagrad, d = 4 293 / 225, 36 524 / 468, 60 662 / 626; fp16 SGD, d = 24 182 / 183, 56 274 / 266 (0.2M
+// lookups of 16 bytes: 72 / 62).  With plain stores as well: d = 28 250, 36 293, Adagrad 36 474, 60 657; whole sectors
+// (d = 48 fp32, stores too): 259 / 303.  The limits leave out what was slower (plain stores too): fp32 SGD d = 52
+// 341 / 356, 16-bit d = 72 306 / 313, 16-bit Adagrad d = 56 475 / 488.
+constexpr int keep_below(int dtype, int opt) {   // bytes of a row
+  return dtype == DLRM_F32 ? (opt == kAdagrad ? 256 : 160) : (opt == kAdagrad ? 96 : 128);
+}
+inline bool rows_share_sectors(int d, int dtype, int opt) {
+  const int bytes = d * elem_bytes(dtype);
+  return bytes % 64 != 0 && bytes < keep_below(dtype, opt);
+}
+
 // The 4 columns [chunk*4, chunk*4+4) of a table row: raw load, and update + store
 // (fp32: W - lr*g; fp16/bf16: widen, update in fp32, one round-to-nearest-even).
 // W: base of the table, read from the pointer array ONCE per workgroup -- the row stores below
@@ -432,12 +447,13 @@ template <int DT>
 __device__ inline char* row_chunk_ptr(char* W, int d, uint32_t row, int chunk) {
   return W + ((int64_t)row * d + chunk * 4) * Tab<DT>::EB;
 }
-template <int DT>
+// KEEP: plain loads that stay in the caches, for narrow rows that share 64-byte sectors (rows_share_sectors); else streaming.
+template <int DT, bool KEEP = false>
 __device__ inline u32x4 row_chunk_load(const char* p) {
   if constexpr (DT == DLRM_F32) {
-    return load16_stream(p);
+    return KEEP ? load16(p) : load16_stream(p);
   } else {
-    const u32x2 b = load8_stream(p);
+    const u32x2 b = KEEP ? *reinterpret_cast<const u32x2*>(p) : load8_stream(p);
     return u32x4{b.x, b.y, 0u, 0u};
   }
 }
@@ -491,13 +507,13 @@ __device__ inline RowRef row_ref(char* W, float* H, int d, uint32_t row, int chu
   r.h = OPT == kAdagrad ? H + e : nullptr;
   return r;
 }
-template <int DT, int OPT>
+template <int DT, int OPT, bool KEEP = false>
 __device__ inline RowVal row_load(const RowRef& r) {
   RowVal v;
-  v.w = row_chunk_load<DT>(r.w);
+  v.w = row_chunk_load<DT, KEEP>(r.w);
   v.h = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   if constexpr (OPT == kAdagrad) {
-    const u32x4 hb = load16_stream(r.h);
+    const u32x4 hb = KEEP ? load16(r.h) : load16_stream(r.h);
     v.h = f32x4{u2f(hb.x), u2f(hb.y), u2f(hb.z), u2f(hb.w)};
   }
   return v;
@@ -519,11 +535,6 @@ __device__ inline void row_update_store(const RowRef& r, const RowVal& v, f32x4 
   } else {
     row_chunk_update_store<DT>(r.w, v.w, g, u.lr);
   }
-}
-template <int DT, int OPT>
-__device__ inline void row_update(char* W, float* H, const UpdArgs& u, uint32_t row, int chunk, f32x4 g) {
-  const RowRef r = row_ref<DT, OPT>(W, H, u.d, row, chunk);
-  row_update_store<DT, OPT>(r, row_load<DT, OPT>(r), g, u);
 }
 // base of table k's optimizer state (read once per workgroup, like the table base)
 template <int OPT>

@@ -188,7 +188,7 @@ __device__ inline void reduce_runs(const GroupArgs& a, const UpdArgs& u, const B
 // inside each slab and the slabs in order: a fixed order, the same on every call.  No list of run
 // heads is needed, and a run of any length inside the bucket is covered.
 // WT: sval holds the resolved bags and rw the weights a of Eq. (2) of the sorted entries.
-template <int DT, int G, int OPT, bool WT = false>
+template <int DT, int G, int OPT, bool WT = false, bool KEEP = false>
 __device__ inline void reduce_slabs(const UpdArgs& u, const Bucket& b, char* W, const uint32_t* skey,
                                     const uint32_t* sval, uint32_t n, float* part, uint32_t* flags,
                                     const ResolvedW& rw = ResolvedW{nullptr, nullptr}) {
@@ -235,7 +235,7 @@ __device__ inline void reduce_slabs(const UpdArgs& u, const Bucket& b, char* W, 
       if constexpr (DT == DLRM_F32) whi[j] = u32x2{0u, 0u};
       if constexpr (OPT == kAdagrad) wh[j] = zero;
       if (hd[j]) {
-        const RowVal t = row_load<DT, OPT>(row_ref<DT, OPT>(W, H, u.d, key[j], cchunk));
+        const RowVal t = row_load<DT, OPT, KEEP>(row_ref<DT, OPT>(W, H, u.d, key[j], cchunk));
         wlo[j] = u32x2{t.w.x, t.w.y};
         if constexpr (DT == DLRM_F32) whi[j] = u32x2{t.w.z, t.w.w};
         if constexpr (OPT == kAdagrad) wh[j] = t.h;
@@ -639,7 +639,7 @@ __device__ inline void reduce_beyond_lds(const GroupArgs& a, const UpdArgs& u, c
   reduce_oversized<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
 }
 
-template <int DT, int G, int OPT, bool WT>
+template <int DT, int G, int OPT, bool WT, bool KEEP>
 // register budget: 4 wavefronts per SIMD for 16-bit tables with SGD, 3 (168 registers) otherwise -- measured both ways
 // on the multi-hot and one-hot workloads (fp32: 3 is 2 % ahead) and on the hot-row one (fp16: 4 is 12 % ahead)
 __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 : 4) void bucket_reduce_kernel(GroupArgs a, UpdArgs u) {
@@ -656,7 +656,7 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   if (b.n <= (uint32_t)kBktCap) {
     sort_bucket_lds(a, b, s);
     if constexpr (!WT) {
-      reduce_slabs<DT, G, OPT>(u, b, W, s.skey, s.sval, b.n, part, s.heads);
+      reduce_slabs<DT, G, OPT, false, KEEP>(u, b, W, s.skey, s.sval, b.n, part, s.heads);
       return;
     }
     // weighted: every sorted entry is resolved (position -> bag, weight) once, by all threads at the same time
@@ -685,7 +685,7 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
       }
       __syncthreads();
     }
-    reduce_slabs<DT, G, OPT, WT>(u, b, W, s.skey, s.sval, b.n, part, s.heads, rw);
+    reduce_slabs<DT, G, OPT, WT, KEEP>(u, b, W, s.skey, s.sval, b.n, part, s.heads, rw);
     return;
   }
   reduce_beyond_lds<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
@@ -867,7 +867,7 @@ __device__ inline void rows_of_positions(const IT* idx, const uint32_t* pos, uin
 // of the table and keeps its own.  The row ids are read once per bucket, from L2 (a few MB in all), in place of two
 // launches that move every pair through memory; sorted pairs, bags and sums are those of the partitioned path, bit for
 // bit.  Bound by the chain of latencies: row ids, sort, offsets, gradient and table rows.
-template <int DT, int G, int OPT, bool WT>
+template <int DT, int G, int OPT, bool WT, bool KEEP>
 __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 : 4) void direct_reduce_kernel(GroupArgs a, UpdArgs u) {
   __shared__ SortLds s;
   __shared__ SplitLds sp;
@@ -949,7 +949,7 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
       }
     }
     __syncthreads();
-    reduce_slabs<DT, G, OPT, WT>(u, b, W, s.skey, s.sval, b.n, part, s.heads, rw);
+    reduce_slabs<DT, G, OPT, WT, KEEP>(u, b, W, s.skey, s.sval, b.n, part, s.heads, rw);
     return;
   }
   // too many pairs for the LDS sort: the bucket is laid out in pair buffer 1 as the partition would
@@ -1013,15 +1013,28 @@ __global__ __launch_bounds__(kThreads) void segment_reduce_kernel(GroupArgs a, U
 }
 
 
+template <int DT, int G, int OPT, bool WT, bool KEEP>
+static void launch_buckets(const GroupArgs& g, const UpdArgs& u, int K, hipStream_t st) {
+  const unsigned buckets = (unsigned)K << g.top_bits;
+  if (g.direct)
+    hipLaunchKernelGGL((direct_reduce_kernel<DT, G, OPT, WT, KEEP>), dim3(buckets), dim3(kThreads), 0, st, g, u);
+  else
+    hipLaunchKernelGGL((bucket_reduce_kernel<DT, G, OPT, WT, KEEP>), dim3(buckets + (unsigned)g.max_over), dim3(kThreads),
+                       0, st, g, u);
+}
+
 template <int DT, int G, int OPT, bool WT>
 static int launch_reduce(const GroupArgs& g, const UpdArgs& u, int K, const dlrm_bwd_timing* tm, hipStream_t st) {
-  const unsigned buckets = (unsigned)K << g.top_bits;
   if (tm && tm->ev_start && hipEventRecord(static_cast<hipEvent_t>(tm->ev_start), st) != hipSuccess) return DLRM_ERR_HIP;
-  if (g.direct)
-    hipLaunchKernelGGL((direct_reduce_kernel<DT, G, OPT, WT>), dim3(buckets), dim3(kThreads), 0, st, g, u);
-  else
-    hipLaunchKernelGGL((bucket_reduce_kernel<DT, G, OPT, WT>), dim3(buckets + (unsigned)g.max_over), dim3(kThreads), 0, st,
-                       g, u);
+  constexpr int narrowest = (G > 1 ? 2 * G + 4 : 4) * Tab<DT>::EB;   // bytes of the narrowest row of G lanes
+  if constexpr (narrowest < keep_below(DT, OPT)) {
+    if (rows_share_sectors(u.d, DT, OPT))
+      launch_buckets<DT, G, OPT, WT, true>(g, u, K, st);
+    else
+      launch_buckets<DT, G, OPT, WT, false>(g, u, K, st);
+  } else {
+    launch_buckets<DT, G, OPT, WT, false>(g, u, K, st);
+  }
   DLRM_CHECK_LAUNCH();
   if (tm && tm->ev_stop && hipEventRecord(static_cast<hipEvent_t>(tm->ev_stop), st) != hipSuccess) return DLRM_ERR_HIP;
   if (g.no_tail) return DLRM_OK;

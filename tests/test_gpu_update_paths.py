@@ -319,6 +319,31 @@ def test_small_batches_with_one_long_table(case, weighted):
     assert {n: counts[n] for n in want} == want
 
 
+# rows on either side of the widths up to which the update keeps rows that share 64-byte sectors in the caches (fp32: SGD
+# below 160 bytes, Adagrad below 256; 16-bit: 128 and 96), and whole sectors; buckets of neighbouring rows
+@pytest.mark.parametrize("dtype,d", [(gen.F32, 4), (gen.F32, 36), (gen.F32, 44), (gen.F32, 60), (gen.F32, 64), (gen.F16, 8),
+                                     (gen.BF16, 40), (gen.F16, 56), (gen.BF16, 72)])
+def test_updates_of_rows_that_share_sectors(dtype, d):
+    print("[case] shared sectors dtype=%s d=%d" % (dtype, d), flush=True)
+    B, m = 900, 700
+    for longest in (8, 160):   # 3600 and 72000 lookups a table: without and with a partition
+        b = gen.make_batch(gen.custom_workload("sectors", K=2, B=B, d=d, dtype=dtype, rows=m, bag=("uniform", 0, longest),
+                                               dist=("uniform",), seed=d))
+        for weighted in (False, True):
+            _assert_exact_update(b, dtype, weighted, ("sort", "prepared"))
+        # Adagrad: h + g * g of small integers, rounded once on both sides
+        dS = _integer_dS(B, 2, d, _max_run(b))
+        g = [np.zeros((m, d), dtype=np.float32) for _ in range(2)]
+        oracle.emb_bag_bwd_sgd(g, gen.F32, b.indices, b.offsets, b.tbl_off, dS, -1.0)
+        dT = torch.zeros((B, 3, d), dtype=torch.float32, device=DEV)
+        dT[:, 1:, :] = torch.from_numpy(dS).to(DEV)
+        state = [torch.full((m, d), 3.0, device=DEV) for _ in range(2)]
+        _run_update(b, _integer_tables(b.rows, d, dtype, seed=5), dT, 0.05, "sort", state=state, eps=1e-8)
+        for k in range(2):
+            want = (3.0 + g[k].astype(np.float64) ** 2).astype(np.float32)
+            assert np.array_equal(state[k].cpu().numpy(), want), k
+
+
 # two to five row blocks on either side of the batch size up to which wavefronts share a sample; rows of dR at
 # every alignment (d + P odd) and at one
 @pytest.mark.parametrize("F,d,below", [(18, 20, 1024), (33, 128, 1024), (34, 36, 1024), (50, 72, 1024), (65, 16, 1024),
