@@ -294,26 +294,47 @@ __device__ inline bool find_tile(const GroupArgs& a, int tile, TileInfo& ti, uin
 // in LDS give the order across waves.
 // On return rnk[j] is the item's rank among the items of its wave with the same digit that
 // precede it, and wcnt[w][digit] the wave's count.  wcnt must be zero on entry.
-template <int ITEMS, int NBK>
+// Bound by latency (a wavefront or three per SIMD): CH items are matched side by side, bit by bit, and no
+// step of an item waits for an answer that the next item's needs: all lanes read the count of their digit
+// before the first lane of each digit adds to it (LDS operations of a wavefront run in order), instead of one
+// lane adding, waiting and passing the old count on (7.7 us of a 4096-position tile's 21).  Step before / after: 8 tables of
+// 205 K lookups, pooling + update 276 / 270 us; 64 fp16 tables of 524 K lookups 2979 / 2901 us.
+template <int ITEMS, int NBK, int CH = 4>
 __device__ inline void rank_items(const uint32_t* dg, const bool* ok, int bits,
                                   uint32_t (*wcnt)[NBK], uint32_t* rnk, int items = ITEMS) {
-  const int lane = lane_id(), w = wave_id();
-  const unsigned long long lt = (1ull << lane) - 1ull;
+  static_assert(ITEMS % CH == 0, "whole chunks");
+  uint32_t* cnt = wcnt[wave_id()];
 #pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    if (j >= items) break;  // uniform
-    unsigned long long m = __ballot(ok[j]);
-    for (int bit = 0; bit < bits; ++bit) {
-      const bool one = (dg[j] >> bit) & 1u;
-      const unsigned long long bal = __ballot(one);
-      m &= one ? bal : ~bal;
+  for (int j0 = 0; j0 < ITEMS; j0 += CH) {
+    if (j0 >= items) break;  // uniform
+    // lo, hi: lanes of this wave holding the same digit in the item (meaningful where ok)
+    uint32_t lo[CH], hi[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const unsigned long long v = __ballot(ok[j0 + c]);
+      lo[c] = (uint32_t)v;
+      hi[c] = (uint32_t)(v >> 32);
     }
-    // m: valid lanes of this wave holding the same digit in item j (meaningful where ok)
-    uint32_t prev = 0;
-    const int leader = ok[j] ? (__ffsll((long long)m) - 1) : lane;
-    if (ok[j] && lane == leader) prev = atomicAdd(&wcnt[w][dg[j]], (uint32_t)__popcll(m));
-    prev = __shfl(prev, leader, DLRM_WAVE);
-    rnk[j] = prev + (uint32_t)__popcll(m & lt);
+    for (int bit = 0; bit < bits; ++bit) {
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const uint32_t one = (uint32_t)__builtin_amdgcn_sbfe((int)dg[j0 + c], (unsigned)bit, 1u);   // all bits set if it is
+        const unsigned long long bal = __ballot(one != 0u);
+        lo[c] &= ~((uint32_t)bal ^ one);
+        hi[c] &= ~((uint32_t)(bal >> 32) ^ one);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi[c], __builtin_amdgcn_mbcnt_lo(lo[c], 0u));
+      uint32_t* slot = cnt + dg[j0 + c];
+      rnk[j0 + c] = before + __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __builtin_amdgcn_wave_barrier();   // every lane has read before the first of each digit adds
+      if (ok[j0 + c] && before == 0u)
+        __hip_atomic_fetch_add(slot, (uint32_t)(__popc(lo[c]) + __popc(hi[c])), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+      __builtin_amdgcn_wave_barrier();
+    }
   }
 }
 

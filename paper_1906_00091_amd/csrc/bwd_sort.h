@@ -101,7 +101,7 @@ __device__ inline void sort_bucket_lds(const GroupArgs& a, const Bucket& b, Sort
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kBktItems; ++j) dg[j] = (key[j] >> shift) & mask;
-    rank_items<kBktItems, kSortBuckets>(dg, ok, bits, s.wcnt, rnk, per);
+    rank_items<kBktItems, kSortBuckets, 2>(dg, ok, bits, s.wcnt, rnk, per);
     __syncthreads();
     uint32_t lofs, tot;
     digit_offsets<kSortBuckets>(nb, s.wcnt, s.smem, &lofs, &tot);
@@ -124,8 +124,7 @@ __device__ inline void sort_bucket_lds(const GroupArgs& a, const Bucket& b, Sort
           key[j] = s.skey[li];
           val[j] = s.sval[li];
         }
-      }
-      __syncthreads();
+      }   // (the next pass writes here again after three barriers)
     }
   }
 }

@@ -165,6 +165,18 @@ __device__ inline void stamp_start(uint32_t* stamp, uint32_t value) {
 __device__ inline int lane_id() { return threadIdx.x & (DLRM_WAVE - 1); }
 __device__ inline int wave_id() { return threadIdx.x >> 6; }
 
+// ---- inclusive scan of one 32-bit value per lane over the wavefront, lane shifts within the vector ALU ----
+// (an addition each; the same scan with lane permutes through the LDS unit waits for six of them in a row)
+__device__ inline uint32_t wave_inclusive_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);   // row_shr:1 (rows of 16 lanes)
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);   // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);   // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);   // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // ---- block-wide exclusive scan of one integer per thread (THREADS multiple of 64) ----
 // smem: at least THREADS/64 + 1 elements.  Returns the exclusive prefix; *total = block sum.
 template <int THREADS, typename T = uint32_t>
@@ -172,10 +184,14 @@ __device__ inline T block_exclusive_scan(T v, T* smem, T* total) {
   constexpr int NW = THREADS / DLRM_WAVE;
   const int lane = lane_id(), w = wave_id();
   T inc = v;
+  if constexpr (sizeof(T) == 4) {
+    inc = (T)wave_inclusive_scan((uint32_t)v);
+  } else {
 #pragma unroll
-  for (int o = 1; o < DLRM_WAVE; o <<= 1) {
-    T t = __shfl_up(inc, o, DLRM_WAVE);
-    if (lane >= o) inc += t;
+    for (int o = 1; o < DLRM_WAVE; o <<= 1) {
+      T t = __shfl_up(inc, o, DLRM_WAVE);
+      if (lane >= o) inc += t;
+    }
   }
   __syncthreads();  // smem may still be read from a previous call
   if (lane == DLRM_WAVE - 1) smem[w] = inc;
