@@ -95,7 +95,7 @@ __device__ inline void reduce_runs(const GroupArgs& a, const UpdArgs& u, const B
   // row of all RU runs are requested before any of them is consumed
   constexpr int RU = OPT == kAdagrad ? 2 : 4;  // Adagrad also holds the state rows
   const int cchunk = col_ok ? chunk : 0;
-  float* H = state_base<OPT>(u, b.k);
+  float* const H = b.H;
   const int64_t tbl = WT ? a.tbl_off[b.k] : 0;
   for (uint32_t r0 = (uint32_t)grp * RU; r0 < nruns; r0 += NG * RU) {
     uint32_t i0[RU], i1[RU];
@@ -203,7 +203,7 @@ __device__ inline void reduce_slabs(const UpdArgs& u, const Bucket& b, char* W, 
   const bool col_ok = chunk * 4 < u.d;
   const int cchunk = col_ok ? chunk : 0;  // lanes past the last column shadow column group 0 and never write
   const float* g = u.dS + (int64_t)b.k * u.stride_k + cchunk * 4;
-  float* H = state_base<OPT>(u, b.k);
+  float* const H = b.H;
   const uint32_t E = (n + NG - 1) / NG;
   const uint32_t p0 = (uint32_t)grp * E < n ? (uint32_t)grp * E : n;
   const uint32_t p1 = p0 + E < n ? p0 + E : n;
@@ -650,9 +650,10 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   uint32_t bid;
   bool listed;
   if (!bucket_id_of_block(a, &bid, &listed)) return;
-  const Bucket b = bucket_of_block(a, bid);
+  Bucket b = bucket_of_block(a, bid);
   if (b.n == 0 || (!listed && b.n > a.big)) return;   // a heavy bucket belongs to one of the first workgroups
   char* W = static_cast<char*>(u.tables[b.k]);
+  b.H = state_base<OPT>(u, b.k);
   if (b.n <= (uint32_t)kBktCap) {
     sort_bucket_lds(a, b, s);
     if constexpr (!WT) {
@@ -884,6 +885,8 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   const int64_t tbl = a.tbl_off[b.k];
   const uint32_t nk = (uint32_t)(a.tbl_off[b.k + 1] - tbl);
   const int shift = top_shift(a, b.k);
+  char* W = static_cast<char*>(u.tables[b.k]);
+  b.H = state_base<OPT>(u, b.k);
   if (nk == 0 || ((int64_t)dg << shift) >= a.rows[b.k]) return;
   BagSearch bags;
   bags.off = a.offsets + (int64_t)b.k * (a.B + 1);
@@ -909,7 +912,6 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   b.low_bits = shift;
   b.start = 0;
   if (b.n == 0) return;
-  char* W = static_cast<char*>(u.tables[b.k]);
   if (tid == 0 && b.n > a.big) b.route[kRouteHeavy] = 1u;
   if (b.n <= (uint32_t)kBktCap) {
     if (nk > (uint32_t)kBktCap) {   // uniform
@@ -1007,6 +1009,7 @@ __global__ __launch_bounds__(kThreads) void segment_reduce_kernel(GroupArgs a, U
   b.n = sg.n;
   b.low_bits = 0;
   b.route = a.seg_meta;
+  b.H = state_base<OPT>(u, b.k);
   char* W = static_cast<char*>(u.tables[b.k]);
   const int dst = (int)(sg.src ^ 1u);
   reduce_window<DT, G, OPT, WT>(a, u, b, W, a.keys[dst] + sg.start, a.vals[dst] + sg.start, t * kBktCap, dst, s, part);
