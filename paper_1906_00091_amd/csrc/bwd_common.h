@@ -106,7 +106,7 @@ constexpr int kRouteHugeInPlace = 7;            // runs above kHugeRun summed by
 // ---------------------------------------------------------------------------
 // Workspace layout (all offsets 256-byte aligned).  Arrays with several users hold, in the order of an update:
 //   keys[0]            partition: digit_total from the column scan to the scatter; reduce: pair buffer 0
-//   hist               partition: tile counts; update without a partition: route counters; weighted hot rows: partial sums
+//   hist               partition: tile counts and, behind them, tile records (at 1024 digits: in vals[0]); update without a partition: route counters; weighted hot rows: partial sums
 //   tile_heads         segment sort and hot rows: hot_done
 //   seg_start, seg_tbl weighted: PosEntry records, all update long; unweighted hot rows: partial sums
 // The exported grouping uses the last three as named, and runs no reduce.
@@ -183,6 +183,16 @@ inline WsLayout ws_layout(int32_t K, int32_t B, int32_t d, int64_t nnz) {
   return L;
 }
 
+// What the histogram kernel leaves for the scatter about a tile: one 32-byte load instead of the tile map and the
+// search for the tile's first bag, which the histogram does while its row ids are on their way.
+struct alignas(32) TileRec {
+  uint32_t k, t, t0, nt;      // as in TileInfo
+  uint32_t count;             // positions in the tile, 0: no tile
+  uint32_t tbl_start;
+  uint32_t shift;             // of the partition digit
+  uint32_t bag;               // the bag that holds the tile's first position
+};
+
 // ---------------------------------------------------------------------------
 struct GroupArgs {            // everything the grouping kernels need
   const void* indices;        // int64 or int32 (idx32)
@@ -206,6 +216,7 @@ struct GroupArgs {            // everything the grouping kernels need
   uint32_t* keys[2];
   uint32_t* vals[2];
   uint32_t* hist;
+  TileRec* tile_rec;          // [nt_max], between the histogram and the scatter
   uint32_t* digit_total;      // [K << top_bits] pairs per bucket, between the column scan and the scatter
   uint32_t* bucket_start;
   uint32_t* tile_heads;
@@ -621,6 +632,9 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   }
   g.hist = reinterpret_cast<uint32_t*>(base + L.hist);
   g.digit_total = reinterpret_cast<uint32_t*>(base + L.keys[0]);
+  // behind the tile counts, or, with the most digits (over 2^16 lookups a table on average), in pair buffer 0
+  const size_t counts = (((size_t)L.nt_max << tb) + 7) & ~(size_t)7;
+  g.tile_rec = reinterpret_cast<TileRec*>(tb < kMaxTopBits ? base + L.hist + counts * 4 : base + L.vals[0]);
   g.bucket_start = reinterpret_cast<uint32_t*>(base + L.bucket_start);
   g.tile_heads = reinterpret_cast<uint32_t*>(base + L.tile_heads);
   g.seg_start = reinterpret_cast<uint32_t*>(base + L.seg_start);
