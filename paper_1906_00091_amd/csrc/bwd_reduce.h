@@ -287,6 +287,31 @@ __device__ inline void reduce_slabs(const UpdArgs& u, const Bucket& b, char* W, 
   }
 }
 
+// Weighted: every sorted entry is resolved (position -> bag, weight) once, by all threads at the same time.
+__device__ inline void resolve_sorted(const GroupArgs& a, int k, uint32_t* sval, uint32_t n, const ResolvedW& rw) {
+  uint32_t ebag[kBktItems];
+  float ew[kBktItems];
+  const int64_t tbl = a.tbl_off[k];
+#pragma unroll
+  for (int j = 0; j < kBktItems; ++j) {
+    const uint32_t li = threadIdx.x + j * kThreads;
+    if (li < n) {
+      const PosEntry pe = a.pos_entry[tbl + sval[li]];
+      ebag[j] = pe.bag;
+      ew[j] = pe.w;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kBktItems; ++j) {  // a thread rewrites only the slots it read
+    const uint32_t li = threadIdx.x + j * kThreads;
+    if (li < n) {
+      sval[li] = ebag[j];
+      rw.at(li) = ew[j];
+    }
+  }
+  __syncthreads();
+}
+
 // Run heads of sorted keys[0..n) (LDS) into s.heads (positions, ascending) with the sentinel
 // heads[nruns] = n.  Returns nruns.  All threads call it.
 __device__ inline uint32_t compact_heads_lds(SortLds& s, int n) {
@@ -375,6 +400,10 @@ __device__ inline void reduce_window(const GroupArgs& a, const UpdArgs& u, const
   __syncthreads();
 }
 
+// A value that is the same in all lanes, though the compiler cannot see it (it came out of LDS, or from threadIdx): loops and addresses that
+// depend on it are scalar.
+__device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
 // --- 4a. oversized buckets: dominant rows split off first ------------------------------------------
 // A bucket outgrows the LDS sort almost always because a few hot rows own most of its pairs.
 // Rows holding at least kCandMin of the bucket's first kBktCap pairs become candidates (at most
@@ -390,17 +419,6 @@ struct SplitLds {
   uint32_t cbase[kCand + 2];  // exclusive prefix of cnt
   uint32_t nc;
 };
-
-// nc: number of candidates (uniform); most oversized buckets have one or two
-__device__ inline uint32_t class_of(uint32_t key, const uint32_t* cd, uint32_t nc) {
-  uint32_t cls = (uint32_t)kCand;
-#pragma unroll
-  for (int c = 0; c < kCand; ++c) {
-    if ((uint32_t)c >= nc) break;  // uniform
-    cls = key == cd[c] ? (uint32_t)c : cls;
-  }
-  return cls;
-}
 
 // Pairs [bk.start, bk.start + bk.n) of pair buffer src, more than kBktCap of them, that no
 // shortcut applies to: queued as a segment when per-row counters fit LDS, else sorted here.
@@ -436,7 +454,7 @@ __device__ inline void sort_reduce_large(const GroupArgs& a, const UpdArgs& u, c
 
 template <int DT, int G, int OPT, bool WT>
 __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, const Bucket& b, char* W,
-                                        SortLds& s, SplitLds& sp, float* part) {
+                                        SortLds& s, SplitLds& sp, float* part, const ResolvedW& rw) {
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
   // ---- candidates: long runs among the first kBktCap pairs
   if (tid < kCand) sp.cand[tid] = 0xFFFFFFFFu;
@@ -469,50 +487,53 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
     return;
   }
   if (tid == 0) atomicAdd(&b.route[kRouteSplit], 1u);
-  uint32_t cd[kCand];
+  uint32_t cd[kCand];   // scalars, as are the counts below
 #pragma unroll
-  for (int c = 0; c < kCand; ++c) cd[c] = sp.cand[c];
+  for (int c = 0; c < kCand; ++c) cd[c] = uniform(sp.cand[c]);
   const uint32_t* kin = a.keys[1] + b.start;
   const uint32_t* vin = a.vals[1] + b.start;
-  // Both passes: wavefront w streams its own quarter [q0, q1) of the bucket, no barriers inside.
+  constexpr uint32_t kNone = 0xFFFFFFFFu;   // no row
+  // Both passes: wavefront w streams its own quarter [q0, q1) of the bucket, no barriers inside, 8 steps of 64 pairs
+  // at a time, the next 8 in flight.  A candidate costs a comparison of a step and the count of the lanes that agree.
   const uint32_t span = (b.n + kNW * DLRM_WAVE - 1) / (kNW * DLRM_WAVE) * DLRM_WAVE;
-  const uint32_t q0 = (uint32_t)w * span < b.n ? (uint32_t)w * span : b.n;
-  const uint32_t q1 = q0 + span < b.n ? q0 + span : b.n;
-  // ---- pass 1: pairs per (wavefront, class).  A wavefront's lanes mostly agree (the dominant
-  // row): those that agree with the first valid lane are counted with one LDS atomic
-  // (the next 8 steps of 64 pairs are in flight while the current 8 are processed)
-  uint32_t kk[8];
-  if (q0 < q1) {
+  const uint32_t q0 = uniform((uint32_t)w * span < b.n ? (uint32_t)w * span : b.n);
+  const uint32_t q1 = uniform(q0 + span < b.n ? q0 + span : b.n);
+  // ---- pass 1: pairs per (wavefront, class)
+  uint32_t cn[kCand], key[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const uint32_t i = q0 + q * DLRM_WAVE + lane;
-      kk[q] = kin[i < q1 ? i : q1 - 1];
-    }
+  for (int c = 0; c < kCand; ++c) cn[c] = 0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const uint32_t i = q0 + q * DLRM_WAVE + lane;
+    key[q] = kin[i < q1 ? i : q1 - 1u];
+    key[q] = i < q1 ? key[q] : kNone;
   }
   for (uint32_t i0 = q0; i0 < q1; i0 += DLRM_WAVE * 8) {
     uint32_t nk[8];
-    if (i0 + DLRM_WAVE * 8 < q1) {  // uniform
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const uint32_t i = i0 + DLRM_WAVE * 8 + q * DLRM_WAVE + lane;
-        nk[q] = kin[i < q1 ? i : q1 - 1];
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t i = i0 + DLRM_WAVE * 8 + q * DLRM_WAVE + lane;
+      nk[q] = kin[i < q1 ? i : q1 - 1u];
+      nk[q] = i < q1 ? nk[q] : kNone;
+    }
+#pragma unroll
+    for (int c = 0; c < kCand; ++c) {
+      if ((uint32_t)c < nc) {  // uniform
+#pragma unroll
+        for (int q = 0; q < 8; ++q) cn[c] += (uint32_t)__popcll(__ballot(key[q] == cd[c]));
       }
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const uint32_t i = i0 + q * DLRM_WAVE + lane;
-      const bool valid = i < q1;
-      const uint32_t cls = class_of(kk[q], cd, nc);
-      const unsigned long long vm = __ballot(valid);
-      if (vm == 0ull) continue;  // wave-uniform
-      const int first = __ffsll((long long)vm) - 1;
-      const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)cls, first);
-      const unsigned long long same = __ballot(valid && cls == c0);
-      if (lane == first) atomicAdd(&sp.wcnt[w][c0], (uint32_t)__popcll(same));
-      if (valid && cls != c0) atomicAdd(&sp.wcnt[w][cls], 1u);
-    }
+    for (int q = 0; q < 8; ++q) key[q] = nk[q];
+  }
+  if (lane == 0) {
+    uint32_t rest = q1 - q0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) kk[q] = nk[q];
+    for (int c = 0; c < kCand; ++c) {
+      sp.wcnt[w][c] = cn[c];
+      rest -= cn[c];
+    }
+    sp.wcnt[w][kCand] = rest;
   }
   __syncthreads();
   if (tid <= kCand) {
@@ -544,46 +565,49 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
   // destination per class lives in its own LDS row.
   uint32_t* kout = a.keys[0] + b.start;
   uint32_t* vout = a.vals[0] + b.start;
-  const unsigned long long lt = (1ull << lane) - 1ull;
-  uint32_t key[8], val[8];
-  if (q0 < q1) {
+  uint32_t val[8], rest = uniform(sp.wbase[w][kCand]);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const uint32_t i = q0 + q * DLRM_WAVE + lane;
-      key[q] = kin[i < q1 ? i : q1 - 1];
-      val[q] = vin[i < q1 ? i : q1 - 1];
-    }
+  for (int c = 0; c < kCand; ++c) cn[c] = uniform(sp.wbase[w][c]);   // the wavefront's running destinations
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const uint32_t i = q0 + q * DLRM_WAVE + lane;
+    key[q] = kin[i < q1 ? i : q1 - 1u];
+    key[q] = i < q1 ? key[q] : kNone;
+    val[q] = vin[i < q1 ? i : q1 - 1u];
   }
   for (uint32_t i0 = q0; i0 < q1; i0 += DLRM_WAVE * 8) {
-    uint32_t nk[8], nv[8];
-    if (i0 + DLRM_WAVE * 8 < q1) {  // uniform
+    uint32_t nk[8], nv[8], dst[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const uint32_t i = i0 + DLRM_WAVE * 8 + q * DLRM_WAVE + lane;
-        nk[q] = kin[i < q1 ? i : q1 - 1];
-        nv[q] = vin[i < q1 ? i : q1 - 1];
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t i = i0 + DLRM_WAVE * 8 + q * DLRM_WAVE + lane;
+      nk[q] = kin[i < q1 ? i : q1 - 1u];
+      nk[q] = i < q1 ? nk[q] : kNone;
+      nv[q] = vin[i < q1 ? i : q1 - 1u];
+      dst[q] = kNone;
+    }
+#pragma unroll
+    for (int c = 0; c < kCand; ++c) {
+      if ((uint32_t)c < nc) {  // uniform
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const bool mine = key[q] == cd[c];
+          const unsigned long long m = __ballot(mine);
+          const uint32_t at = cn[c] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+          dst[q] = mine ? at : dst[q];
+          cn[c] += (uint32_t)__popcll(m);
+        }
       }
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const uint32_t i = i0 + q * DLRM_WAVE + lane;
-      const bool valid = i < q1;
-      const uint32_t cls = class_of(key[q], cd, nc);
-      unsigned long long rem = __ballot(valid);
-      uint32_t dst = 0;
-      while (rem != 0ull) {  // wave-uniform: one round per class present in the step
-        const int f = __ffsll((long long)rem) - 1;
-        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)cls, f);
-        const unsigned long long m = __ballot(valid && cls == c);
-        const uint32_t bs = sp.wbase[w][c];
-        if (valid && cls == c) dst = bs + (uint32_t)__popcll(m & lt);
-        if (lane == f) sp.wbase[w][c] = bs + (uint32_t)__popcll(m);
-        rem &= ~m;
+      const bool other = key[q] != kNone && dst[q] == kNone;
+      const unsigned long long m = __ballot(other);
+      if (other) {
+        dst[q] = rest + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        kout[dst[q]] = key[q];
       }
-      if (valid) {
-        vout[dst] = val[q];
-        if (cls == (uint32_t)kCand) kout[dst] = key[q];
-      }
+      rest += (uint32_t)__popcll(m);
+      if (key[q] != kNone) vout[dst[q]] = val[q];
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -595,35 +619,57 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
   if ((uint32_t)tid < nc) kout[sp.cbase[tid]] = sp.cand[tid];
   if ((uint32_t)tid <= nc) s.heads[tid] = sp.cbase[tid];
   __syncthreads();
-  // ---- candidate lists are runs: short ones summed here, those above kHugeRun queued as hot rows
+  // ---- candidate lists are runs: those above kHugeRun are queued as hot rows, the others reduced like sorted buckets, as
+  // many whole runs at a time as LDS holds.  Bound by the round trips of one workgroup on which the launch waits.  With run
+  // after run (two barriers and a chain of list and row loads each), classes found by a loop over those present in a step and
+  // their destinations in LDS / now: 26 bf16 tables of 41 K skewed lookups 90 / 81 us for the kernel, 100 fp16 tables with
+  // Adagrad 60 / 50 us (with the state's base as a scalar).
   {
-    const uint32_t nlong = collect_long_runs(s, nc, long_run<G>());
-    reduce_runs<DT, G, OPT, WT>(a, u, b, W, kout, vout, s.heads, 0u, nc, s.longs, nlong, 0, part);
+    const uint32_t nlong = collect_long_runs(s, nc, (uint32_t)kHugeRun);
+    if (nlong != 0)
+      reduce_runs<DT, G, OPT, WT>(a, u, b, W, kout, vout, s.heads, 0u, 0u, s.longs, nlong, 0, part);
   }
-  // ---- the rest
-  Bucket rest = b;
-  rest.start = b.start + sp.cbase[kCand];
-  rest.n = sp.cnt[kCand];
-  __syncthreads();
-  if (rest.n == 0) return;  // uniform
-  if (rest.n > (uint32_t)kBktCap) {
-    sort_reduce_large<DT, G, OPT, WT>(a, u, rest, W, 0, s, part);
-    return;
+  static_assert(kHugeRun <= kBktCap, "a run that is not queued fits LDS");
+  for (uint32_t c0 = 0; c0 <= nc;) {   // uniform; last, as class nc, the rest
+    uint32_t c1 = c0, n = 0;
+    if (c0 < nc) {
+      while (c1 < nc && n + uniform(sp.cnt[c1]) <= (uint32_t)kBktCap) n += uniform(sp.cnt[c1++]);
+      if (n == 0) {   // a queued run
+        ++c0;
+        continue;
+      }
+      const uint32_t from = uniform(sp.cbase[c0]);
+      __syncthreads();   // the previous entries have been read
+      for (uint32_t li = tid; li < n; li += kThreads) {
+        uint32_t c = c0;
+        while (c + 1 < c1 && sp.cbase[c + 1] - from <= li) ++c;
+        s.skey[li] = sp.cand[c];
+        s.sval[li] = vout[from + li];
+      }
+    } else {
+      Bucket others = b;
+      others.start = b.start + uniform(sp.cbase[kCand]);
+      others.n = n = uniform(sp.cnt[kCand]);
+      if (n == 0) return;
+      __syncthreads();
+      if (n > (uint32_t)kBktCap) {
+        sort_reduce_large<DT, G, OPT, WT>(a, u, others, W, 0, s, part);
+        return;
+      }
+      sort_bucket_lds(a, others, s, 0);
+      c1 = nc + 1;
+    }
+    __syncthreads();
+    if constexpr (WT) resolve_sorted(a, b.k, s.sval, n, rw);
+    reduce_slabs<DT, G, OPT, WT>(u, b, W, s.skey, s.sval, n, part, s.heads, rw);
+    c0 = c1;
   }
-  sort_bucket_lds(a, rest, s, 0);
-  if constexpr (!WT) {
-    reduce_slabs<DT, G, OPT>(u, rest, W, s.skey, s.sval, rest.n, part, s.heads);
-    return;
-  }
-  const uint32_t nruns = compact_heads_lds(s, (int)rest.n);
-  const uint32_t nlong = collect_long_runs(s, nruns, long_run<G>());
-  reduce_runs<DT, G, OPT, WT>(a, u, rest, W, s.skey, s.sval, s.heads, 0u, nruns, s.longs, nlong, 0, part);
 }
 
 // A bucket of more than kBktCap pairs (pair buffer 1).
 template <int DT, int G, int OPT, bool WT>
 __device__ inline void reduce_beyond_lds(const GroupArgs& a, const UpdArgs& u, const Bucket& b, char* W, SortLds& s,
-                                         SplitLds& sp, float* part) {
+                                         SplitLds& sp, float* part, const ResolvedW& rw) {
   if (b.low_bits == 0) {  // the bucket holds one row: a single run, already in position order
     if (threadIdx.x == 0) {
       s.heads[0] = 0;
@@ -636,7 +682,7 @@ __device__ inline void reduce_beyond_lds(const GroupArgs& a, const UpdArgs& u, c
                        part);
     return;
   }
-  reduce_oversized<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
+  reduce_oversized<DT, G, OPT, WT>(a, u, b, W, s, sp, part, rw);
 }
 
 template <int DT, int G, int OPT, bool WT, bool KEEP>
@@ -654,49 +700,17 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   if (b.n == 0 || (!listed && b.n > a.big)) return;   // a heavy bucket belongs to one of the first workgroups
   char* W = static_cast<char*>(u.tables[b.k]);
   b.H = state_base<OPT>(u, b.k);
+  const ResolvedW rw{reinterpret_cast<float*>(&s.wcnt[0][0]), wext};
   if (b.n <= (uint32_t)kBktCap) {
     sort_bucket_lds(a, b, s);
-    if constexpr (!WT) {
-      reduce_slabs<DT, G, OPT, false, KEEP>(u, b, W, s.skey, s.sval, b.n, part, s.heads);
-      return;
-    }
-    // weighted: every sorted entry is resolved (position -> bag, weight) once, by all threads at the same time
-    uint32_t ebag[WT ? kBktItems : 1];
-    float ew[WT ? kBktItems : 1];
-    if constexpr (WT) {
-      const int64_t tbl = a.tbl_off[b.k];
-#pragma unroll
-      for (int j = 0; j < kBktItems; ++j) {
-        const uint32_t li = threadIdx.x + j * kThreads;
-        const uint32_t pos = li < b.n ? s.sval[li] : s.sval[0];
-        const PosEntry pe = a.pos_entry[tbl + pos];
-        ebag[j] = pe.bag;
-        ew[j] = pe.w;
-      }
-    }
-    const ResolvedW rw{reinterpret_cast<float*>(&s.wcnt[0][0]), wext};
-    if constexpr (WT) {
-#pragma unroll
-      for (int j = 0; j < kBktItems; ++j) {  // a thread rewrites only the slots it read
-        const uint32_t li = threadIdx.x + j * kThreads;
-        if (li < b.n) {
-          s.sval[li] = ebag[j];
-          rw.at(li) = ew[j];
-        }
-      }
-      __syncthreads();
-    }
+    if constexpr (WT) resolve_sorted(a, b.k, s.sval, b.n, rw);
     reduce_slabs<DT, G, OPT, WT, KEEP>(u, b, W, s.skey, s.sval, b.n, part, s.heads, rw);
     return;
   }
-  reduce_beyond_lds<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
+  reduce_beyond_lds<DT, G, OPT, WT>(a, u, b, W, s, sp, part, rw);
 }
 
 // --- 4, small batches: no partition --------------------------------------------------------------
-// A value that is the same in all lanes, though the compiler cannot see it (it came out of LDS, or from threadIdx): loops and addresses that
-// depend on it are scalar.
-__device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-
 // Bag of a position of table k: binary search in kThreads evenly spaced offsets held in LDS, then
 // between two of them in memory (bags may be empty: the last bag that starts at or before the position).
 struct BagSearch {
@@ -913,6 +927,7 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
   b.start = 0;
   if (b.n == 0) return;
   if (tid == 0 && b.n > a.big) b.route[kRouteHeavy] = 1u;
+  const ResolvedW rw{reinterpret_cast<float*>(&s.wcnt[0][0]), wext};
   if (b.n <= (uint32_t)kBktCap) {
     if (nk > (uint32_t)kBktCap) {   // uniform
       marked_positions(mask, nk, before, [&](uint32_t i, uint32_t pos) { s.sval[i] = pos; });
@@ -941,7 +956,6 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
     } else {
       bags.find_all<kBktItems>(pos, bag);
     }
-    const ResolvedW rw{reinterpret_cast<float*>(&s.wcnt[0][0]), wext};
 #pragma unroll
     for (int j = 0; j < kBktItems; ++j) {  // a thread rewrites only the slots it read
       const uint32_t li = tid + j * kThreads;
@@ -993,7 +1007,7 @@ __global__ __launch_bounds__(kThreads, (OPT == kAdagrad || DT == DLRM_F32) ? 3 :
     }
   }
   __syncthreads();
-  reduce_beyond_lds<DT, G, OPT, WT>(a, u, b, W, s, sp, part);
+  reduce_beyond_lds<DT, G, OPT, WT>(a, u, b, W, s, sp, part, rw);
 }
 
 template <int DT, int G, int OPT, bool WT>
