@@ -151,40 +151,42 @@ __global__ __launch_bounds__(256) void emb_fwd_group_kernel(FwdArgs a) {
   const int64_t p0 = off[b], p1 = off[b + 1];
   const IT* idx = static_cast<const IT*>(a.indices) + a.tbl_off[k];
   const float* wts = WT ? a.weights + a.tbl_off[k] : nullptr;
-  const char* W = static_cast<const char*>(a.tables[k]) + chunk * 16;
-  const int64_t row_bytes = (int64_t)a.chunks * 16;
+  const uint64_t W = reinterpret_cast<uint64_t>(a.tables[k]) + (uint64_t)(chunk * 16);
+  const uint32_t row_bytes = (uint32_t)a.chunks * 16u;
 
   float acc[E];
 #pragma unroll
   for (int i = 0; i < E; ++i) acc[i] = -0.0f;
 
-  for (int64_t p = p0; p < p1; p += U) {
-    // all U index loads, then all U row loads, are issued before anything is consumed; the
-    // tail re-reads the bag's last position (in cache) and is replaced by the identity
-    int64_t r[U];
-    u32x4 v[U];
-    float wt[U];
+  // A round requests its U rows, then the next round's indices, and only then consumes: a round is one round trip and
+  // not two (index, then row).  The tail re-reads the bag's last position (in cache) and is replaced by the identity.
+  // With / without the second trip: 26 bf16 tables, batch 4096, bags of 0..20 rows of 128 bytes 25.2 / 29.0 us; 100 fp16
+  // tables, batch 1024 10.7 / 11.2 us; four rows of 1 KB in flight are HBM-bound either way.  (A wavefront that walks several
+  // bags of such rows: 137 us where this takes 135, 4 tables, batch 8192, bags of 20.)
+  uint32_t r[U];
+  float wt[U];
+  const auto request = [&](int64_t p) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) r[u] = idx[p + u < p1 ? p + u : p1 - 1];
+    for (int u = 0; u < U; ++u) r[u] = (uint32_t)idx[p + u < p1 ? p + u : p1 - 1];   // rows are < 2^31
     if constexpr (WT) {
 #pragma unroll
       for (int u = 0; u < U; ++u) wt[u] = wts[p + u < p1 ? p + u : p1 - 1];
     }
+  };
+  if (p0 < p1) request(p0);
+  for (int64_t p = p0; p < p1; p += U) {
+    u32x4 v[U];
+    float w1[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = load16(W + r[u] * row_bytes);
+    for (int u = 0; u < U; ++u) {
+      v[u] = load16_global(W + (uint64_t)r[u] * row_bytes);
+      w1[u] = WT && p + u < p1 ? wt[u] : 1.0f;  // 1 * (-0) leaves the sum alone
+    }
+    request(p + U);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (p + u >= p1) v[u] = Tab<DT>::ident();
-      float f[E];
-      Tab<DT>::widen(v[u], f);
-      if constexpr (WT) {
-        const float w1 = p + u >= p1 ? 1.0f : wt[u];  // 1 * (-0) leaves the sum alone
-#pragma unroll
-        for (int i = 0; i < E; ++i) acc[i] = fmaf(w1, f[i], acc[i]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < E; ++i) acc[i] += f[i];
-      }
+      add_row<DT, WT>(acc, v[u], w1[u]);
     }
   }
   if (p1 <= p0) {
