@@ -26,6 +26,7 @@ struct PiArgs {
   float* T;
   float* R;
   int32_t K, B, d, pstride;
+  int32_t any;           // the batch has lookups
   uint32_t* stamp;       // optional: see stamp_start
   uint32_t stamp_value;
 };
@@ -54,6 +55,44 @@ __device__ inline f32x4 load_row4(const char* row, int col) {
   }
 }
 
+// The result row of a sample, R_b = [ x_b | pairs ].  A loop that reads a value (from memory, from LDS), waits for it and
+// stores it is a chain of round trips at the end of every sample: x_b is requested before the sample's products (the first
+// 256 columns), the pairs are read kPairsAhead at a time.  26 tables, batch 8192, d = 128: 34.5 / 33.4 us for the kernel.
+constexpr int kDenseAhead = 4, kPairsAhead = 8;
+struct DenseRow {
+  float v[kDenseAhead];   // columns lane, lane + 64, ...
+};
+__device__ inline DenseRow dense_request(const float* x, int d, int lane) {
+  DenseRow r;
+#pragma unroll
+  for (int q = 0; q < kDenseAhead; ++q) {
+    const int c = q * DLRM_WAVE + lane;
+    r.v[q] = x[c < d ? c : d - 1];
+  }
+  return r;
+}
+__device__ inline void store_result(float* R, const DenseRow& r, const float* x, int d, const float* pairs, int P, int lane) {
+#pragma unroll
+  for (int q = 0; q < kDenseAhead; ++q) {
+    const int c = q * DLRM_WAVE + lane;
+    if (c < d) R[c] = r.v[q];
+  }
+  for (int c = kDenseAhead * DLRM_WAVE + lane; c < d; c += DLRM_WAVE) R[c] = x[c];
+  for (int c0 = 0; c0 < P; c0 += DLRM_WAVE * kPairsAhead) {
+    float v[kPairsAhead];
+#pragma unroll
+    for (int q = 0; q < kPairsAhead; ++q) {
+      const int c = c0 + q * DLRM_WAVE + lane;
+      v[q] = pairs[c < P ? c : P - 1];
+    }
+#pragma unroll
+    for (int q = 0; q < kPairsAhead; ++q) {
+      const int c = c0 + q * DLRM_WAVE + lane;
+      if (c < P) R[d + c] = v[q];
+    }
+  }
+}
+
 template <int NB, int DT, typename IT>
 __global__ __launch_bounds__(kPiThreads, NB <= 2 ? 4 : 2) void pooled_interact_fwd_kernel(PiArgs a) {
   constexpr int QC = NB <= 2 ? 4 : 2;  // 16-column chunks per round
@@ -74,21 +113,33 @@ __global__ __launch_bounds__(kPiThreads, NB <= 2 ? 4 : 2) void pooled_interact_f
 
   // this lane's bag in every block of 16 tables; lanes past the last table own an empty bag,
   // whose zero vector only meets interaction entries that are never stored
+  // (no load behind a branch: each of those waited for the loads before it, 35.8 / 34.5 us for the kernel at the shape above)
+  const DenseRow dense = dense_request(xb, d, lane);
   const char* W[NB];
   const IT* idx[NB];
-  int64_t p0[NB], p1[NB], r0[NB];
+  int64_t p0[NB], p1[NB], r0[NB], tbl[NB];
 #pragma unroll
   for (int rb = 0; rb < NB; ++rb) {
     const int e = rb * 16 + i;
     const int ec = e < K ? e : K - 1;
     const int64_t* off = a.offsets + (int64_t)ec * (a.B + 1);
     p0[rb] = off[b];
-    p1[rb] = e < K ? off[b + 1] : p0[rb];
-    idx[rb] = static_cast<const IT*>(a.indices) + a.tbl_off[ec];
+    p1[rb] = off[b + 1];
+    tbl[rb] = a.tbl_off[ec];
     W[rb] = static_cast<const char*>(a.tables[ec]);
   }
 #pragma unroll
-  for (int rb = 0; rb < NB; ++rb) r0[rb] = p1[rb] > p0[rb] ? (int64_t)idx[rb][p0[rb]] : 0;  // row 0 exists, dropped
+  for (int rb = 0; rb < NB; ++rb) {
+    p1[rb] = rb * 16 + i < K ? p1[rb] : p0[rb];
+    idx[rb] = static_cast<const IT*>(a.indices) + tbl[rb];
+    r0[rb] = 0;
+  }
+  if (a.any) {   // uniform: the batch has lookups, so an empty bag may read the first of them and drop it
+#pragma unroll
+    for (int rb = 0; rb < NB; ++rb) r0[rb] = (int64_t) static_cast<const IT*>(a.indices)[p1[rb] > p0[rb] ? tbl[rb] + p0[rb] : 0];
+#pragma unroll
+    for (int rb = 0; rb < NB; ++rb) r0[rb] = p1[rb] > p0[rb] ? r0[rb] : 0;  // row 0 exists, dropped
+  }
 
   f32x4 acc[NTILE];
 #pragma unroll
@@ -186,8 +237,7 @@ __global__ __launch_bounds__(kPiThreads, NB <= 2 ? 4 : 2) void pooled_interact_f
       }
     }
   }
-  for (int c = lane; c < d; c += DLRM_WAVE) Rb[c] = xb[c];  // dense part: exact copy
-  for (int c = lane; c < P; c += DLRM_WAVE) Rb[d + c] = Rp[c];
+  store_result(Rb, dense, xb, d, Rp, P, lane);  // the dense part: an exact copy
 }
 
 template <int NB, int DT, typename IT>
@@ -511,6 +561,7 @@ extern "C" int32_t dlrm_emb_interact_fwd_stamped(const dlrm_sparse_batch* s, con
   a.K = s->K;
   a.B = s->B;
   a.d = s->d;
+  a.any = s->nnz_total > 0;
   a.stamp = stamp;
   a.stamp_value = stamp_value;
   const int P = F * (F - 1) / 2;

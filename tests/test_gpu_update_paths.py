@@ -30,6 +30,10 @@ GROUPINGS = [
     ("many-tables-few-digits", [(k * 37) % 300 for k in range(700)], 5, 4),
     ("column-scan-255-256-257-tiles", [255 * 1024, 256 * 1024, 256 * 1024 + 1], 64, 1 << 20),
     ("column-scan-ragged-tables", [700 * 1024 - 3, 5, 0, 1024], 33, 70000),
+    # bag starts of a tile: 1024 of 1024 (1024 digits too), tables whose later bags are empty, 1365 of 4096
+    ("one-hot-1024-digits", [200000], 1, 5000),
+    ("one-hot-then-empty-bags", [70000, 3, 0, 69999, 1024], 1, 100000),
+    ("large-tiles-short-bags", [1200001, 5000], 3, 3000),
 ]
 
 
@@ -390,3 +394,52 @@ def test_interaction_backward_beyond_one_launch():
         assert (part == want).all()
     del T, dR, dT, part
     torch.cuda.empty_cache()
+
+
+# buckets of n lookups on either side of a wavefront, two and the workgroup (one item of the ranking a lane, then two), from one
+# row to rows of 24 and 25 unsorted bits; repeated rows, their bags in order
+@pytest.mark.parametrize("m,sizes", [(2, (1, 64, 257)), (600, (1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257)),
+                                     (1 << 25, (65, 256, 257)), (1 << 26, (65, 256, 257))])
+def test_small_buckets_at_the_sizes_where_their_sort_changes(m, sizes):
+    print("[case] small buckets m=%d" % m, flush=True)
+    rng = np.random.default_rng(m)
+    B = 40
+    bags = []
+    for n in sizes:
+        rows = rng.integers(0, (m + 1) // 2, size=max(n // 3, 1))   # one bucket: at most two of them (one digit bit)
+        ids = rng.choice(rows, size=n)
+        bags.append([x.tolist() for x in np.split(ids, np.sort(rng.integers(0, n + 1, size=B - 1)))])
+    b = gen.batch_from_lists([m] * len(sizes), bags, d=4, seed=3)
+    for weighted in (False, True):
+        _assert_exact_update(b, gen.F32, weighted, ("sort", "prepared"))
+
+
+# rows split off an oversized bucket: more of them than fit LDS together, the most there can be, one of the largest size that is
+# not queued beside small ones; with and without other rows
+@pytest.mark.parametrize("weighted", [False, True], ids=["sum", "pow2-weights"])
+@pytest.mark.parametrize("dtype,d", [(gen.F32, 24), (gen.F16, 128), (gen.BF16, 8)])
+@pytest.mark.parametrize("runs,others", [([400] * 9, 1500), ([160] * 15, 0), ([2048, 300, 2047, 290], 70)])
+def test_rows_split_off_oversized_buckets_fill_lds_piecewise(runs, others, dtype, d, weighted):
+    print("[case] split rows %s others=%d dtype=%s d=%d weighted=%s" % (runs, others, dtype, d, weighted), flush=True)
+    rng = np.random.default_rng(others)
+    B, m, K = 500, 4000, 8
+    parts = [np.full(n, 700 + i) for i, n in enumerate(runs)] + [rng.integers(640, 768, size=others), rng.integers(0, 600, size=2000)]
+    ids = rng.permutation(np.concatenate(parts))
+    long = [x.tolist() for x in np.split(ids, np.sort(rng.integers(0, len(ids) + 1, size=B - 1)))]
+    short = [[[int(i) for i in rng.integers(0, m, size=n)] for n in rng.integers(0, 3, size=B)] for _ in range(K - 1)]
+    b = gen.batch_from_lists([m] * K, short[:3] + [long] + short[3:], d=d, dtype=dtype, seed=6)
+    assert _assert_exact_update(b, dtype, weighted, ("sort", "prepared"))["dominant_row_splits"] >= 1
+
+
+@pytest.mark.parametrize("dtype,d", [(gen.F32, 4), (gen.F32, 256), (gen.F16, 512)])
+def test_one_launch_forward_without_lookups(dtype, d):
+    """No index to read: every pooled vector is zero, the dense part of the result a copy (rows up to the widest)."""
+    print("[case] forward without lookups dtype=%s d=%d" % (dtype, d), flush=True)
+    K, B = 20, 70
+    t = torch.ones((5, d), dtype=torch.float32 if dtype == gen.F32 else torch.float16, device=DEV)
+    sb = hot.SparseBatch([t] * K, dtype, torch.empty(0, dtype=torch.int64, device=DEV),
+                         torch.zeros((K, B + 1), dtype=torch.int64, device=DEV), torch.zeros(K + 1, dtype=torch.int64, device=DEV), 0)
+    x = torch.randn((B, d), device=DEV)
+    T, R = torch.full((B, K + 1, d), 7.0, device=DEV), torch.full((B, d + K * (K + 1) // 2), 7.0, device=DEV)
+    hot.dlrm_emb_interact_fwd(sb, x, T, R, algo=hot.FWD_FUSED)
+    assert torch.equal(R[:, :d], x) and not R[:, d:].any() and torch.equal(T[:, 0], x) and not T[:, 1:].any()
