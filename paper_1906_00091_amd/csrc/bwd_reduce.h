@@ -562,7 +562,7 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
   // ---- pass 2: stable partition by class into pair buffer 0.  Candidate lists keep only the
   // bags (plus the row id at their first position); the rest keeps (row, bag).  Within a step
   // of 64 pairs the lanes of one class rank themselves by ballot; the wavefront's running
-  // destination per class lives in its own LDS row.
+  // destination per class is a scalar.
   uint32_t* kout = a.keys[0] + b.start;
   uint32_t* vout = a.vals[0] + b.start;
   uint32_t val[8], rest = uniform(sp.wbase[w][kCand]);
