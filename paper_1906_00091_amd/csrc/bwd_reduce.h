@@ -287,27 +287,22 @@ __device__ inline void reduce_slabs(const UpdArgs& u, const Bucket& b, char* W, 
   }
 }
 
-// Weighted: every sorted entry is resolved (position -> bag, weight) once, by all threads at the same time.
+// Weighted: every sorted entry is resolved (position -> bag, weight) once, by all threads at the same time.  All of a thread's
+// entries are requested together: none behind a branch, since each of those waits for the loads before it, up to eight round
+// trips a bucket.  A slot past the end reads the table's first entry and is written like the others; nothing reads it.
 __device__ inline void resolve_sorted(const GroupArgs& a, int k, uint32_t* sval, uint32_t n, const ResolvedW& rw) {
-  uint32_t ebag[kBktItems];
-  float ew[kBktItems];
-  const int64_t tbl = a.tbl_off[k];
+  const PosEntry* const pe = a.pos_entry + a.tbl_off[k];
+  PosEntry e[kBktItems];
 #pragma unroll
   for (int j = 0; j < kBktItems; ++j) {
-    const uint32_t li = threadIdx.x + j * kThreads;
-    if (li < n) {
-      const PosEntry pe = a.pos_entry[tbl + sval[li]];
-      ebag[j] = pe.bag;
-      ew[j] = pe.w;
-    }
+    const uint32_t li = threadIdx.x + j * kThreads, pos = sval[li];
+    e[j] = pe[li < n ? pos : 0u];
   }
 #pragma unroll
   for (int j = 0; j < kBktItems; ++j) {  // a thread rewrites only the slots it read
     const uint32_t li = threadIdx.x + j * kThreads;
-    if (li < n) {
-      sval[li] = ebag[j];
-      rw.at(li) = ew[j];
-    }
+    sval[li] = e[j].bag;
+    rw.at(li) = e[j].w;
   }
   __syncthreads();
 }

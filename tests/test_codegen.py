@@ -1,0 +1,63 @@
+"""What the compiler makes of loops whose point is the order of their loads: a kernel is compiled for gfx950, by itself and with the
+library's flags, and its assembly is read.  A source that asks for loads in flight together can compile to one round trip
+after the other (a load behind a branch, or one merged into another) with every result still right, so that no other test sees it.
+Needs hipcc, no GPU."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_1906_00091_amd import build as hip_build
+
+
+def _assembly(tmp_path, include, kernels):
+    src, out = str(tmp_path / "kernels.hip"), str(tmp_path / "kernels.s")
+    with open(src, "w") as f:
+        f.write('#include "%s"\nnamespace dlrm {\n%s\n}\n' % (include, "\n".join("template __global__ void %s;" % k for k in kernels)))
+    cmd = [hip_build._hipcc()] + hip_build.HIPCC_FLAGS + ["--cuda-device-only", "-S", "-o", out, src]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    with open(out) as f:
+        return f.read()
+
+
+def _kernels(asm):
+    """{kernel symbol: lines of its body}"""
+    found, body = {}, None
+    for line in asm.splitlines():
+        t = line.strip()
+        if re.match(r"_Z\w+:", t):
+            body = found.setdefault(t.split(":")[0], [])
+        elif t.startswith("s_endpgm"):
+            body = None
+        elif body is not None and t and not t.startswith(";"):
+            body.append(t)
+    return found
+
+
+def _waits_for_loads(t):
+    return t.startswith("s_waitcnt") and "vmcnt" in t
+
+
+def _longest_run(lines, load):
+    """Most loads that match with no wait for a load, no branch and no label among them."""
+    best = run = 0
+    for t in lines:
+        if re.match(load, t):
+            run += 1
+            best = max(best, run)
+        elif _waits_for_loads(t) or t.startswith(("s_cbranch", "s_branch", ".LBB")):
+            run = 0
+    return best
+
+
+def test_weighted_entries_of_a_bucket_are_requested_together(tmp_path):
+    """A sorted bucket's (bag, weight) records, 8 bytes each and up to 8 a thread (fp32 rows: no other load of 8 bytes comes
+    more than a few at a time)."""
+    asm = _assembly(tmp_path, "bwd_reduce.h", ["bucket_reduce_kernel<DLRM_F32, 16, %s, true, false>(GroupArgs, UpdArgs)" % o
+                                               for o in ("kSgd", "kAdagrad")])
+    bodies = _kernels(asm)
+    assert len(bodies) == 2
+    for name, lines in bodies.items():
+        assert _longest_run(lines, r"(global|flat)_load_dwordx2 ") >= 8, name
