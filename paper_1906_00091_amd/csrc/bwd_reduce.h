@@ -624,7 +624,8 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
     if (nlong != 0)
       reduce_runs<DT, G, OPT, WT>(a, u, b, W, kout, vout, s.heads, 0u, 0u, s.longs, nlong, 0, part);
   }
-  static_assert(kHugeRun <= kBktCap, "a run that is not queued fits LDS");
+  // (a run between the two limits would be queued and reduced here as well, one beyond the larger limit neither)
+  static_assert(kHugeRun == kBktCap, "a run is queued or fits LDS, never both");
   for (uint32_t c0 = 0; c0 <= nc;) {   // uniform; last, as class nc, the rest
     uint32_t c1 = c0, n = 0;
     if (c0 < nc) {

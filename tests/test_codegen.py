@@ -4,6 +4,7 @@ after the other (a load behind a branch, or one merged into another) with every 
 Needs hipcc, no GPU."""
 import os
 import re
+import shutil
 import subprocess
 
 import pytest
@@ -20,6 +21,28 @@ def _assembly(tmp_path, include, kernels):
     assert r.returncode == 0, r.stderr[-3000:]
     with open(out) as f:
         return f.read()
+
+
+@pytest.mark.parametrize("huge_run,builds", [(2048, True), (1024, False), (4096, False)])
+def test_a_run_is_queued_or_reduced_in_its_bucket_but_never_both(tmp_path, huge_run, builds):
+    """The limit from which a row split off an oversized bucket is queued has to be the size that the bucket's own reduction
+    takes: with any other limit the sources must not compile."""
+    csrc = str(tmp_path / "csrc")
+    shutil.copytree(hip_build.CSRC, csrc)
+    with open(os.path.join(csrc, "bwd_common.h")) as f:
+        text, n = re.subn(r"constexpr int kHugeRun = \d+;", "constexpr int kHugeRun = %d;" % huge_run, f.read())
+    assert n == 1
+    with open(os.path.join(csrc, "bwd_common.h"), "w") as f:
+        f.write(text)
+    src = os.path.join(csrc, "one.hip")
+    with open(src, "w") as f:
+        f.write('#include "bwd_reduce.h"\nnamespace dlrm {\n'
+                'template __global__ void bucket_reduce_kernel<DLRM_F32, 16, kSgd, false, false>(GroupArgs, UpdArgs);\n}\n')
+    flags = ["-I" + csrc if f == hip_build.CSRC else f for f in hip_build.HIPCC_FLAGS if f != "-I"]
+    flags = ["-I" + f if f == hip_build.INCLUDE else f for f in flags]
+    r = subprocess.run([hip_build._hipcc()] + flags + ["--cuda-device-only", "-fsyntax-only", src], capture_output=True, text=True)
+    assert (r.returncode == 0) == builds, r.stderr[-3000:]
+    assert builds or "never both" in r.stderr, r.stderr[-3000:]
 
 
 def _kernels(asm):
