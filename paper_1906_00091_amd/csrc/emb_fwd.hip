@@ -158,11 +158,15 @@ __global__ __launch_bounds__(256) void emb_fwd_group_kernel(FwdArgs a) {
 #pragma unroll
   for (int i = 0; i < E; ++i) acc[i] = -0.0f;
 
-  // A round requests its U rows, then the next round's indices, and only then consumes: a round is one round trip and
-  // not two (index, then row).  The tail re-reads the bag's last position (in cache) and is replaced by the identity.
-  // With / without the second trip: 26 bf16 tables, batch 4096, bags of 0..20 rows of 128 bytes 25.2 / 29.0 us; 100 fp16
-  // tables, batch 1024 10.7 / 11.2 us; four rows of 1 KB in flight are HBM-bound either way.  (A wavefront that walks several
-  // bags of such rows: 137 us where this takes 135, 4 tables, batch 8192, bags of 20.)
+  // A round requests its U rows, then the next round's indices (and weights), and only then consumes: a round is one round trip
+  // and not two (index, then row).  A bag's last round requests no more: bags of four rows have one round, 26.1 / 24.8 us without
+  // that branch / with it (26 fp32 tables, batch 8192, rows of 256 bytes).  The tail re-reads the bag's last position (in
+  // cache) and is replaced by the identity.  Kernel alone, indices requested at the head of their own round / here, us: 26 bf16
+  // tables, batch 4096, bags of 0..20 rows of 128 bytes 18.8 / 17.7 (weighted 20.0 / 19.5); 40 bf16 tables, batch 2048, 2..12 rows
+  // of 256 bytes 21.2 / 20.6; 100 fp16 tables, batch 1024, 1..7 rows of 64 bytes 9.0 / 8.7; 26 fp32 tables, batch 8192, five
+  // rows of 256 bytes 30.2 / 29.6 (weighted 31.1 / 31.3, four rows 25.5 / 25.9: the weighted kernel has a wavefront per SIMD less);
+  // four rows of 1 KB in flight are HBM-bound either way.  (A wavefront that walks several bags of such rows: 137 us where this
+  // takes 135, 4 tables, batch 8192, bags of 20.)
   uint32_t r[U];
   float wt[U];
   const auto request = [&](int64_t p) {
@@ -180,9 +184,10 @@ __global__ __launch_bounds__(256) void emb_fwd_group_kernel(FwdArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       v[u] = load16_global(W + (uint64_t)r[u] * row_bytes);
-      w1[u] = WT && p + u < p1 ? wt[u] : 1.0f;  // 1 * (-0) leaves the sum alone
+      w1[u] = WT && p + u < p1 ? wt[u] : 1.0f;   // 1 * (-0) leaves the sum alone
     }
-    request(p + U);
+    if (p + U < p1) request(p + U);
+    asm volatile("" ::: "memory");   // they stay above this line: the compiler would move them to the head of the next round
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (p + u >= p1) v[u] = Tab<DT>::ident();

@@ -84,3 +84,27 @@ def test_weighted_entries_of_a_bucket_are_requested_together(tmp_path):
     assert len(bodies) == 2
     for name, lines in bodies.items():
         assert _longest_run(lines, r"(global|flat)_load_dwordx2 ") >= 8, name
+
+
+def _loads_behind_rows(lines, row, index, rows):
+    """True if an `index` load follows `rows` loads of rows that have not been waited for, in one pass over straight code."""
+    pending = 0
+    for t in lines:
+        if re.match(row, t):
+            pending += 1
+        elif re.match(index, t) and pending >= rows:
+            return True
+        elif t.startswith(".LBB") or (_waits_for_loads(t) and pending >= rows and
+                                      int(re.search(r"vmcnt\((\d+)\)", t).group(1)) < rows):
+            pending = 0
+    return False
+
+
+def test_pooling_requests_the_next_indices_behind_this_round_s_rows(tmp_path):
+    """A lane group per bag: four rows are requested, then the next round's indices, before anything is waited for."""
+    asm = _assembly(tmp_path, "emb_fwd.hip", [])
+    bodies = {n: b for n, b in _kernels(asm).items() if "emb_fwd_group_kernel" in n}
+    assert len(bodies) == 3 * 7 * 2 * 2   # storage types, lanes per row, weights, index types
+    for name, lines in bodies.items():
+        index = r"global_load_dword " if "EiEEv" in name else r"global_load_dword(x2)? "
+        assert _loads_behind_rows(lines, r"global_load_dwordx4 ", index, 4), name
