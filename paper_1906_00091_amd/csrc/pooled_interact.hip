@@ -56,8 +56,15 @@ __device__ inline f32x4 load_row4(const char* row, int col) {
 }
 
 // The result row of a sample, R_b = [ x_b | pairs ].  A loop that reads a value (from memory, from LDS), waits for it and
-// stores it is a chain of round trips at the end of every sample: x_b is requested before the sample's products (the first
-// 256 columns), the pairs are read kPairsAhead at a time.  26 tables, batch 8192, d = 128: 34.5 / 33.4 us for the kernel.
+// stores it is a chain of round trips at the end of every sample: x_b is requested ahead (the first 256 columns), the pairs are
+// read kPairsAhead at a time.  26 tables, batch 8192, d = 128: 34.5 / 33.4 us for the kernel.
+// x_b ahead of the sample's products costs 4 to 8 registers all through them, behind the products its trip is in part hidden by the
+// pairs.  One-hot, batch 8192, ahead / behind, us: 26 fp32 tables, d = 64 20.0 / 20.7, d = 128 29.6 / 30.2 (the same wavefronts per
+// SIMD); 33 to 48 tables, where the registers are a wavefront per SIMD: fp32, 48, d = 64 41.1 / 37.9, d = 128 64.7 / 62.6, d = 256
+// 115.7 / 116.7; fp16 39.5 / 36.9, 58.9 / 57.0, 99.8 / 101.5; 64 tables, a wavefront less too, but 2 of them are mostly the better
+// number there: d = 32 46.2 / 44.0, 64 64.1 / 62.9, 128 101.9 / 104.3, 256 171.1 / 180.7, batch 4096, bags of 1..4, d = 64 79.3 / 90.6.
+template <int NB>
+constexpr bool kDenseBehind = NB == 3;
 constexpr int kDenseAhead = 4, kPairsAhead = 8;
 struct DenseRow {
   float v[kDenseAhead];   // columns lane, lane + 64, ...
@@ -114,7 +121,8 @@ __global__ __launch_bounds__(kPiThreads, NB <= 2 ? 4 : 2) void pooled_interact_f
   // this lane's bag in every block of 16 tables; lanes past the last table own an empty bag,
   // whose zero vector only meets interaction entries that are never stored
   // (no load behind a branch: each of those waited for the loads before it, 35.8 / 34.5 us for the kernel at the shape above)
-  const DenseRow dense = dense_request(xb, d, lane);
+  DenseRow dense;
+  if constexpr (!kDenseBehind<NB>) dense = dense_request(xb, d, lane);
   const char* W[NB];
   const IT* idx[NB];
   int64_t p0[NB], p1[NB], r0[NB], tbl[NB];
@@ -213,6 +221,7 @@ __global__ __launch_bounds__(kPiThreads, NB <= 2 ? 4 : 2) void pooled_interact_f
       }
     }
   }
+  if constexpr (kDenseBehind<NB>) dense = dense_request(xb, d, lane);
   // pairs gathered in this wavefront's LDS so that they leave as whole contiguous lines;
   // pair (gi, gj), gi > gj, sits at gi(gi-1)/2 + gj, table e being vector e + 1
   float* Rp = lds + wave_id() * a.pstride;

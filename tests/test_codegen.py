@@ -108,3 +108,22 @@ def test_pooling_requests_the_next_indices_behind_this_round_s_rows(tmp_path):
     for name, lines in bodies.items():
         index = r"global_load_dword " if "EiEEv" in name else r"global_load_dword(x2)? "
         assert _loads_behind_rows(lines, r"global_load_dwordx4 ", index, 4), name
+
+
+def _occupancy(asm):
+    """{kernel symbol: wavefronts per SIMD that its registers allow}"""
+    found, name = {}, None
+    for line in asm.splitlines():
+        m = re.match(r"(_Z\w+):", line)
+        name = m.group(1) if m else name
+        m = re.match(r"; Occupancy: (\d+)", line)
+        if m:
+            found[name] = int(m.group(1))
+    return found
+
+
+def test_one_launch_forward_of_33_to_48_tables_keeps_four_wavefronts_per_simd(tmp_path):
+    """Its registers are just below the limit for four; with the dense row held through the products they are above it."""
+    found = {n: o for n, o in _occupancy(_assembly(tmp_path, "pooled_interact.hip", [])).items() if "pooled_interact_fwd_kernelILi3E" in n}
+    assert len(found) == 3 * 2   # storage types, index types
+    assert min(found.values()) >= 4, found
