@@ -275,13 +275,30 @@ __device__ inline void reduce_slabs(const UpdArgs& u, const Bucket& b, char* W, 
   if (col_ok) storef4(part + grp * (G * 4) + chunk * 4, headp);
   if (chunk == 0) flags[grp] = p0 < p1 ? (have ? 1u : 2u) : 0u;   // empty / a run begins here / all continuation
   __syncthreads();
+  // With narrow rows a long run spans up to 255 slabs: those after the next are read kAhead at a time, not each once the one
+  // before has said that the run goes on.  Update alone, 26 tables of 8192 skewed lookups, one by one / now: fp32 d = 4 101 / 74 us,
+  // d = 8 73.5 / 63.4, fp16 d = 8 74.5 / 63.0; of 2048: 36.2 / 22.8, 24.0 / 16.6, 22.4 / 16.5.  Rows of 64 columns (up to 15 slabs)
+  // have nothing to gain (fp16 21.1 / 22.0).
+  constexpr int kAhead = NG >= 32 ? 8 : 1;
   if (have) {
     f32x4 tot = acc;
-    for (int g2 = grp + 1; g2 < NG; ++g2) {
-      const uint32_t f = flags[g2];
-      if (f == 0u) break;
-      tot += loadf4(part + g2 * (G * 4) + cchunk * 4);
-      if (f == 1u) break;
+    uint32_t f = grp + 1 < NG ? flags[grp + 1] : 0u;
+    if (f != 0u) tot += loadf4(part + (grp + 1) * (G * 4) + cchunk * 4);
+    for (int g2 = grp + 2; f == 2u; g2 += kAhead) {
+      uint32_t fs[kAhead];
+      f32x4 more[kAhead];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) {
+        const int gj = g2 + j < NG ? g2 + j : NG - 1;
+        fs[j] = g2 + j < NG ? flags[gj] : 0u;
+        more[j] = loadf4(part + gj * (G * 4) + cchunk * 4);
+      }
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) {   // branch-free: behind the run's end f is 0 or 1, and the identity is added
+        f = f == 2u ? fs[j] : 0u;
+        const bool in = f != 0u;
+        tot += f32x4{in ? more[j].x : -0.0f, in ? more[j].y : -0.0f, in ? more[j].z : -0.0f, in ? more[j].w : -0.0f};
+      }
     }
     if (col_ok) row_update_store<DT, OPT>(cur, curv, tot, u);
   }
@@ -618,7 +635,9 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
   // many whole runs at a time as LDS holds.  Bound by the round trips of one workgroup on which the launch waits.  With run
   // after run (two barriers and a chain of list and row loads each), classes found by a loop over those present in a step and
   // their destinations in LDS / now: 26 bf16 tables of 41 K skewed lookups 90 / 81 us for the kernel, 100 fp16 tables with
-  // Adagrad 60 / 50 us (with the state's base as a scalar).
+  // Adagrad 60 / 50 us (with the state's base as a scalar).  The entries of a group of runs are requested together, and one
+  // pass over the runs' starts gives all of them their rows; each entry's read and search by itself, update alone, 26 fp32
+  // tables of 8192 skewed lookups: d = 4 74.1 / 71.1 us, d = 12 60.1 / 56.9, d = 64 66.2 / 64.2.
   {
     const uint32_t nlong = collect_long_runs(s, nc, (uint32_t)kHugeRun);
     if (nlong != 0)
@@ -635,12 +654,23 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
         continue;
       }
       const uint32_t from = uniform(sp.cbase[c0]);
+      uint32_t row[kBktItems], bag[kBktItems];   // (weighted: positions)
+#pragma unroll
+      for (int j = 0; j < kBktItems; ++j) {   // requested together; a slot past the end re-reads the last entry
+        const uint32_t li = tid + j * kThreads;
+        bag[j] = vout[from + (li < n ? li : n - 1u)];
+        row[j] = 0u;
+      }
+      for (uint32_t c = c0; c < c1; ++c) {
+        const uint32_t first = uniform(sp.cbase[c]) - from, id = uniform(sp.cand[c]);
+#pragma unroll
+        for (int j = 0; j < kBktItems; ++j) row[j] = (uint32_t)(tid + j * kThreads) >= first ? id : row[j];
+      }
       __syncthreads();   // the previous entries have been read
-      for (uint32_t li = tid; li < n; li += kThreads) {
-        uint32_t c = c0;
-        while (c + 1 < c1 && sp.cbase[c + 1] - from <= li) ++c;
-        s.skey[li] = sp.cand[c];
-        s.sval[li] = vout[from + li];
+#pragma unroll
+      for (int j = 0; j < kBktItems; ++j) {
+        s.skey[tid + j * kThreads] = row[j];
+        s.sval[tid + j * kThreads] = bag[j];
       }
     } else {
       Bucket others = b;

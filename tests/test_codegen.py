@@ -127,3 +127,22 @@ def test_one_launch_forward_of_33_to_48_tables_keeps_four_wavefronts_per_simd(tm
     found = {n: o for n, o in _occupancy(_assembly(tmp_path, "pooled_interact.hip", [])).items() if "pooled_interact_fwd_kernelILi3E" in n}
     assert len(found) == 3 * 2   # storage types, index types
     assert min(found.values()) >= 4, found
+
+
+def test_sums_of_narrow_rows_read_several_pieces_of_a_run_together(tmp_path):
+    """A run over many slabs of a bucket: up to 255 of them with rows of 4 columns.  Eight pieces (16 bytes of LDS a lane) are
+    requested before one is waited for; the compiler puts a branch before the last of them."""
+    which = [("DLRM_F32", 1, "kSgd", "false"), ("DLRM_F32", 4, "kAdagrad", "true"), ("DLRM_F16", 2, "kSgd", "false"),
+             ("DLRM_BF16", 8, "kAdagrad", "false")]
+    asm = _assembly(tmp_path, "bwd_reduce.h", ["bucket_reduce_kernel<%s, %d, %s, %s, false>(GroupArgs, UpdArgs)" % w for w in which])
+    bodies = _kernels(asm)
+    assert len(bodies) == len(which)
+    for name, lines in bodies.items():
+        best = run = 0
+        for t in lines:
+            if t.startswith("ds_read_b128 "):
+                run += 1
+                best = max(best, run)
+            elif (t.startswith("s_waitcnt") and "lgkmcnt" in t) or t.startswith(("s_cbranch", "s_branch", ".LBB")):
+                run = 0
+        assert best >= 7, (name, best)
