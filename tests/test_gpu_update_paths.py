@@ -9,7 +9,7 @@ import paper_1906_00091_amd as hot
 from oracle import oracle
 from workloads import gen
 
-from hotpath_util import DEV, Compact, table_to_numpy
+from hotpath_util import DEV, SCALE_FLOOR, Compact, table_to_numpy, widen_host
 from test_gpu_exact_counts import _assert_only_touched_rows_changed, _integer_dS, _integer_tables, _max_run, _pow2_weights, _run_update
 
 pytestmark = pytest.mark.gpu
@@ -323,6 +323,39 @@ def test_small_batches_with_one_long_table(case, weighted):
     assert {n: counts[n] for n in want} == want
 
 
+def _assert_adagrad_update(b, dtype, weighted, modes):
+    """The Adagrad update of batch b with exact gradient sums g: h + g * g is rounded once on both sides and must be equal; the step
+    lr * g / (sqrt(h) + eps) takes a square root, a sum, a quotient, a product and a difference in fp32, half a unit each, and one
+    rounding to the storage type.  Rows without lookups (g = 0, none of them touched) keep their bits."""
+    w = b.workload
+    wts = _pow2_weights(b) if weighted else None
+    dS = _integer_dS(w.B, w.K, w.d, max(_max_run(b), 1), 2.0 if weighted else 1.0)
+    lr, eps = float(np.float32(0.05)), float(np.float32(1e-8))
+    g = [np.zeros((int(m), w.d), dtype=np.float32) for m in b.rows]
+    if weighted:
+        oracle.emb_bag_bwd_weighted(g, gen.F32, b.indices, b.offsets, b.tbl_off, wts, dS, -1.0)
+    else:
+        oracle.emb_bag_bwd_sgd(g, gen.F32, b.indices, b.offsets, b.tbl_off, dS, -1.0)
+    dT = torch.zeros((w.B, w.K + 1, w.d), dtype=torch.float32, device=DEV)
+    dT[:, 1:, :] = torch.from_numpy(dS).to(DEV)
+    start = _integer_tables(b.rows, w.d, dtype, seed=5)
+    bound = 5 * 2.0 ** -24 + {gen.F32: 0.0, gen.F16: 2.0 ** -11, gen.BF16: 2.0 ** -8}[dtype]
+    for mode in modes:
+        tables = [t.clone() for t in start]
+        state = [torch.full((int(m), w.d), 3.0, device=DEV) for m in b.rows]
+        _run_update(b, tables, dT, lr, mode, weights=wts, state=state, eps=eps)
+        for k in range(w.K):
+            h = (3.0 + g[k].astype(np.float64) ** 2).astype(np.float32)
+            assert np.array_equal(state[k].cpu().numpy(), h), (mode, k)
+            before = widen_host(table_to_numpy(start[k], dtype), dtype).astype(np.float64)
+            after = widen_host(table_to_numpy(tables[k], dtype), dtype).astype(np.float64)
+            step = lr * g[k].astype(np.float64) / (np.sqrt(h.astype(np.float64)) + eps)
+            scale = np.abs(before) + np.abs(step)
+            assert (np.abs(after - (before - step)) <= bound * np.maximum(scale, SCALE_FLOOR[dtype])).all(), (mode, k)
+            a0, a1 = int(b.tbl_off[k]), int(b.tbl_off[k + 1])
+            _assert_only_touched_rows_changed(start[k], tables[k], np.unique(b.indices[a0:a1]))
+
+
 # rows on either side of the widths up to which the update keeps rows that share 64-byte sectors in the caches (fp32: SGD
 # below 160 bytes, Adagrad below 256; 16-bit: 128 and 96), and whole sectors; buckets of neighbouring rows
 @pytest.mark.parametrize("dtype,d", [(gen.F32, 4), (gen.F32, 36), (gen.F32, 44), (gen.F32, 60), (gen.F32, 64), (gen.F16, 8),
@@ -335,17 +368,8 @@ def test_updates_of_rows_that_share_sectors(dtype, d):
                                                dist=("uniform",), seed=d))
         for weighted in (False, True):
             _assert_exact_update(b, dtype, weighted, ("sort", "prepared"))
-        # Adagrad: h + g * g of small integers, rounded once on both sides
-        dS = _integer_dS(B, 2, d, _max_run(b))
-        g = [np.zeros((m, d), dtype=np.float32) for _ in range(2)]
-        oracle.emb_bag_bwd_sgd(g, gen.F32, b.indices, b.offsets, b.tbl_off, dS, -1.0)
-        dT = torch.zeros((B, 3, d), dtype=torch.float32, device=DEV)
-        dT[:, 1:, :] = torch.from_numpy(dS).to(DEV)
-        state = [torch.full((m, d), 3.0, device=DEV) for _ in range(2)]
-        _run_update(b, _integer_tables(b.rows, d, dtype, seed=5), dT, 0.05, "sort", state=state, eps=1e-8)
-        for k in range(2):
-            want = (3.0 + g[k].astype(np.float64) ** 2).astype(np.float32)
-            assert np.array_equal(state[k].cpu().numpy(), want), k
+        for weighted in (False, True):
+            _assert_adagrad_update(b, dtype, weighted, ("sort", "prepared"))
 
 
 # two to five row blocks on either side of the batch size up to which wavefronts share a sample; rows of dR at
@@ -400,7 +424,7 @@ def test_interaction_backward_beyond_one_launch():
 # row to rows of 24 and 25 unsorted bits; repeated rows, their bags in order
 @pytest.mark.parametrize("m,sizes", [(2, (1, 64, 257)), (600, (1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257)),
                                      (1 << 25, (65, 256, 257)), (1 << 26, (65, 256, 257))])
-def test_small_buckets_at_the_sizes_where_their_sort_changes(m, sizes):
+def test_small_buckets_on_either_side_of_a_wavefront_and_of_the_workgroup(m, sizes):
     print("[case] small buckets m=%d" % m, flush=True)
     rng = np.random.default_rng(m)
     B = 40
