@@ -464,6 +464,12 @@ constexpr int kSgd = 0, kAdagrad = 1;
 // lookups of 16 bytes: 72 / 62).  With plain stores as well: d = 28 250, 36 293, Adagrad 36 474, 60 657; whole sectors
 // (d = 48 fp32, stores too): 259 / 303.  The limits leave out what was slower (plain stores too): fp32 SGD d = 52
 // 341 / 356, 16-bit d = 72 306 / 313, 16-bit Adagrad d = 56 475 / 488.
+// The rule sees the width alone; where few neighbours are looked up plain loads are no slower either.  Lookup + update, two sets in
+// turn, lookups per row 0.2 / 0.02 / 0.002 / 2 (8 x 1M, 4 x 10M twice, 8 x 0.1M rows): fp32 SGD d = 12 170 / 163, 115 / 105,
+// 37.1 / 35.9, 105 / 98; Adagrad d = 36 515 / 442, 302 / 268, 55.8 / 50.1, 268 / 253; fp16 SGD d = 24 172 / 169, 116 / 109,
+// 36.2 / 34.9, 115 / 102.  Of 90 such pairs four are slower: fp16 SGD d = 40 213 / 222 and 136 / 139 (38.0 / 36.6 and 149 / 134
+// the others), d = 56 161 / 163, fp32 SGD d = 36 173 / 177.  Small batches without a partition, 26 tables of 2000 lookups:
+// fp32 SGD d = 36 25.1 / 22.3, Adagrad d = 4 22.0 / 18.5, fp16 SGD d = 40 22.9 / 21.3.
 constexpr int keep_below(int dtype, int opt) {   // bytes of a row
   return dtype == DLRM_F32 ? (opt == kAdagrad ? 256 : 160) : (opt == kAdagrad ? 96 : 128);
 }

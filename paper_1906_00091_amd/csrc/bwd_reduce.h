@@ -178,7 +178,7 @@ __device__ inline void reduce_runs(const GroupArgs& a, const UpdArgs& u, const B
   }
 }
 
-// A bucket sorted in LDS (unweighted batch), reduced with the WORK, not the runs, dealt evenly: lane
+// A bucket sorted in LDS, reduced with the WORK, not the runs, dealt evenly: lane
 // group g takes the sorted entries [g*E, (g+1)*E), E = ceil(n / groups), whatever runs they belong
 // to, U gradient rows in flight from the first entry to the last.  An entry whose row differs from
 // its predecessor's starts a run (its table row is requested with the gradient rows of its round);
@@ -196,8 +196,9 @@ __device__ inline void reduce_slabs(const UpdArgs& u, const Bucket& b, char* W, 
   // Gradient rows in flight per lane group, each measured with whole libraries on one box.  16-bit tables, SGD (128
   // registers): 3 / 4 / 6 / 8 / 10 -> 1.154 / 1.178 / 1.140 / 1.123 / 1.240 ms per launch on the hot-row workload.
   // fp32, SGD (168 registers): 4 / 8 / 12 -> 165 / 162 / 160 us on the multi-hot workload, step 135.8 / 134.3 /
-  // 132.5 us on the large one-hot one (12 spills 120 bytes; 16 spills 300).  Adagrad: 4 / 6 / 8 -> 325 / 317 / 324 us
-  // (multi-hot), 2.66 / 2.40 / 2.57 ms (hot-row).
+  // 132.5 us on the large one-hot one (12 spills about 80 bytes, 16 three times that).  Adagrad: 6 and 8 are no different now that
+  // a round's row requests do not wait for each other (state_base), and 6 needs fewer registers; before, 4 / 6 / 8 took
+  // 2.66 / 2.40 / 2.57 ms on the hot-row workload.
   constexpr int U = OPT == kAdagrad ? 6 : DT == DLRM_F32 ? 12 : 8;
   const int grp = threadIdx.x / G, chunk = threadIdx.x % G;
   const bool col_ok = chunk * 4 < u.d;
@@ -427,7 +428,7 @@ struct SplitLds {
   uint32_t cand[kCand];       // candidate row ids, in row order; unused slots 0xFFFFFFFF
   uint32_t cnt[kCand + 1];    // pairs per class; class kCand = every other row
   uint32_t wcnt[kNW][kCand + 1];   // the same per wavefront (each streams a quarter of the bucket)
-  uint32_t wbase[kNW][kCand + 1];  // running destination of every (wavefront, class)
+  uint32_t wbase[kNW][kCand + 1];  // first destination of every (wavefront, class)
   uint32_t cbase[kCand + 2];  // exclusive prefix of cnt
   uint32_t nc;
 };
@@ -470,7 +471,6 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
   // ---- candidates: long runs among the first kBktCap pairs
   if (tid < kCand) sp.cand[tid] = 0xFFFFFFFFu;
-  if (tid < kNW * (kCand + 1)) (&sp.wcnt[0][0])[tid] = 0;
   {
     Bucket head = b;
     head.n = (uint32_t)kBktCap;
@@ -638,6 +638,9 @@ __device__ inline void reduce_oversized(const GroupArgs& a, const UpdArgs& u, co
   // Adagrad 60 / 50 us (with the state's base as a scalar).  The entries of a group of runs are requested together, and one
   // pass over the runs' starts gives all of them their rows; each entry's read and search by itself, update alone, 26 fp32
   // tables of 8192 skewed lookups: d = 4 74.1 / 71.1 us, d = 12 60.1 / 56.9, d = 64 66.2 / 64.2.
+  // Rows are read streaming here, also where they share sectors (KEEP).  Streaming / plain loads, 27 updates of such tables: from
+  // 1 % in favour of plain ones to 3 % against (26 x 41 K skewed lookups, us: fp32 d = 36 181.9 / 180.8, weighted 255.1 / 256.9,
+  // fp16 Adagrad d = 40 230.2 / 235.5).
   {
     const uint32_t nlong = collect_long_runs(s, nc, (uint32_t)kHugeRun);
     if (nlong != 0)
