@@ -149,8 +149,9 @@ __global__ __launch_bounds__(256) void emb_fwd_group_kernel(FwdArgs a) {
   const int k = (int)(bag / (uint32_t)a.B), b = (int)(bag - (uint32_t)k * (uint32_t)a.B);
   const int64_t* off = a.offsets + (int64_t)k * (a.B + 1);
   const int64_t p0 = off[b], p1 = off[b + 1];
-  const IT* idx = static_cast<const IT*>(a.indices) + a.tbl_off[k];
-  const float* wts = WT ? a.weights + a.tbl_off[k] : nullptr;
+  const uint32_t n = p1 > p0 ? (uint32_t)(p1 - p0) : 0u;   // a batch has less than 2^31 lookups
+  const IT* idx = static_cast<const IT*>(a.indices) + (a.tbl_off[k] + p0);
+  const float* wts = WT ? a.weights + (a.tbl_off[k] + p0) : nullptr;
   const uint64_t W = reinterpret_cast<uint64_t>(a.tables[k]) + (uint64_t)(chunk * 16);
   const uint32_t row_bytes = (uint32_t)a.chunks * 16u;
 
@@ -161,40 +162,41 @@ __global__ __launch_bounds__(256) void emb_fwd_group_kernel(FwdArgs a) {
   // A round requests its U rows, then the next round's indices (and weights), and only then consumes: a round is one round trip
   // and not two (index, then row).  A bag's last round requests no more: bags of four rows have one round, 26.1 / 24.8 us without
   // that branch / with it (26 fp32 tables, batch 8192, rows of 256 bytes).  The tail re-reads the bag's last position (in
-  // cache) and is replaced by the identity.  Kernel alone, indices requested at the head of their own round / here, us: 26 bf16
-  // tables, batch 4096, bags of 0..20 rows of 128 bytes 18.8 / 17.7 (weighted 20.0 / 19.5); 40 bf16 tables, batch 2048, 2..12 rows
-  // of 256 bytes 21.2 / 20.6; 100 fp16 tables, batch 1024, 1..7 rows of 64 bytes 9.0 / 8.7; 26 fp32 tables, batch 8192, five
-  // rows of 256 bytes 30.2 / 29.6 (weighted 31.1 / 31.3, four rows 25.5 / 25.9: the weighted kernel has a wavefront per SIMD less);
-  // four rows of 1 KB in flight are HBM-bound either way.  (A wavefront that walks several bags of such rows: 137 us where this
-  // takes 135, 4 tables, batch 8192, bags of 20.)
+  // cache) and is replaced by the identity.  Positions are 32 bits from the bag's start: in 64 bits the weighted kernels lose a
+  // wavefront per SIMD (that batch with weights 25.9 / 25.3 us).  Kernel alone, indices requested at the head of their own
+  // round / here, us: 26 bf16 tables, batch 4096, bags of 0..20 rows of 128 bytes 18.7 / 17.7 (weighted 20.1 / 19.6); 40 bf16 tables,
+  // batch 2048, 2..12 rows of 256 bytes 21.3 / 20.8; 100 fp16 tables, batch 1024, 1..7 rows of 64 bytes 9.0 / 8.8; 26 fp32 tables, batch
+  // 8192, five rows of 256 bytes 30.3 / 29.5; rows that are in the L1 leave nothing to overlap (5 tables of 30 rows of 560 bytes,
+  // 655 bags of 1..108 13.6 / 14.0); four rows of 1 KB in flight are HBM-bound either way.  (A wavefront that walks several bags
+  // of such rows: 137 us where this takes 135, 4 tables, batch 8192, bags of 20.)
   uint32_t r[U];
   float wt[U];
-  const auto request = [&](int64_t p) {
+  const auto request = [&](uint32_t p) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) r[u] = (uint32_t)idx[p + u < p1 ? p + u : p1 - 1];   // rows are < 2^31
+    for (int u = 0; u < U; ++u) r[u] = (uint32_t)idx[p + u < n ? p + u : n - 1u];   // rows are < 2^31
     if constexpr (WT) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) wt[u] = wts[p + u < p1 ? p + u : p1 - 1];
+      for (int u = 0; u < U; ++u) wt[u] = wts[p + u < n ? p + u : n - 1u];
     }
   };
-  if (p0 < p1) request(p0);
-  for (int64_t p = p0; p < p1; p += U) {
+  if (n != 0u) request(0u);
+  for (uint32_t p = 0; p < n; p += U) {
     u32x4 v[U];
     float w1[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       v[u] = load16_global(W + (uint64_t)r[u] * row_bytes);
-      w1[u] = WT && p + u < p1 ? wt[u] : 1.0f;   // 1 * (-0) leaves the sum alone
+      w1[u] = WT && p + u < n ? wt[u] : 1.0f;   // 1 * (-0) leaves the sum alone
     }
-    if (p + U < p1) request(p + U);
+    if (p + U < n) request(p + U);
     asm volatile("" ::: "memory");   // they stay above this line: the compiler would move them to the head of the next round
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (p + u >= p1) v[u] = Tab<DT>::ident();
+      if (p + u >= n) v[u] = Tab<DT>::ident();
       add_row<DT, WT>(acc, v[u], w1[u]);
     }
   }
-  if (p1 <= p0) {
+  if (n == 0u) {
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.0f;
   }
