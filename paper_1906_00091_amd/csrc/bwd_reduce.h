@@ -276,37 +276,46 @@ __device__ inline void reduce_slabs(const UpdArgs& u, const Bucket& b, char* W, 
   if (col_ok) storef4(part + grp * (G * 4) + chunk * 4, headp);
   if (chunk == 0) flags[grp] = p0 < p1 ? (have ? 1u : 2u) : 0u;   // empty / a run begins here / all continuation
   __syncthreads();
-  // With narrow rows a long run spans up to 255 slabs: those after the next are read kAhead at a time, not each once the one
-  // before has said that the run goes on.  Update alone, 26 tables of 8192 skewed lookups, one by one / now: fp32 d = 4 101 / 74 us,
-  // d = 8 73.5 / 63.4, fp16 d = 8 74.5 / 63.0; of 2048: 36.2 / 22.8, 24.0 / 16.6, 22.4 / 16.5.  Rows of 64 columns (up to 15 slabs)
-  // have nothing to gain (fp16 21.1 / 22.0).
-  constexpr int kAhead = NG >= 32 ? 8 : 1;
   if (have) {
     f32x4 tot = acc;
-    // the two next slabs, which most runs end in, without waiting for the first one's answer (27 fp32 tables of 2900 uniform
-    // lookups, d = 4, update alone: one, then eight at once 32.0 us, two 31.5)
-    const int g1 = grp + 1 < NG ? grp + 1 : NG - 1, gn = grp + 2 < NG ? grp + 2 : NG - 1;
-    uint32_t f = flags[g1], fn = flags[gn];
-    const f32x4 next = loadf4(part + g1 * (G * 4) + cchunk * 4), after = loadf4(part + gn * (G * 4) + cchunk * 4);
-    f = grp + 1 < NG ? f : 0u;
-    fn = grp + 2 < NG ? fn : 0u;
-    if (f != 0u) tot += next;
-    f = f == 2u ? fn : 0u;
-    if (f != 0u) tot += after;
-    for (int g2 = grp + 3; f == 2u; g2 += kAhead) {
-      uint32_t fs[kAhead];
-      f32x4 more[kAhead];
-#pragma unroll
-      for (int j = 0; j < kAhead; ++j) {
-        const int gj = g2 + j < NG ? g2 + j : NG - 1;
-        fs[j] = g2 + j < NG ? flags[gj] : 0u;
-        more[j] = loadf4(part + gj * (G * 4) + cchunk * 4);
+    if constexpr (NG < 32) {
+      for (int g2 = grp + 1; g2 < NG; ++g2) {
+        const uint32_t f = flags[g2];
+        if (f == 0u) break;
+        tot += loadf4(part + g2 * (G * 4) + cchunk * 4);
+        if (f == 1u) break;
       }
+    } else {
+      // With narrow rows a long run spans up to 255 slabs.  The two next ones, which most runs end in, are read at once, those
+      // behind them kAhead at a time, not each once the one before has said that the run goes on.  Update alone, 26 tables
+      // of 8192 skewed lookups, one by one / now: fp32 d = 4 101 / 71 us, d = 8 73.4 / 61.1, fp16 d = 8 72.8 / 59.5; of 2048:
+      // 36.2 / 23.2, 24.0 / 16.7, 22.3 / 16.4; 27 fp32 tables of 2900 uniform lookups, d = 4: one, then eight 32.0, two, then
+      // eight 31.5.  Rows of 64 columns and more (up to 15 slabs) have nothing to gain, and the registers for it are spilled:
+      // pooling + update, one table, 24 bags of 73 on 8 rows, d = 156, as above / so 39.5 / 40.8.
+      constexpr int kAhead = 8;
+      const int g1 = grp + 1 < NG ? grp + 1 : NG - 1, gn = grp + 2 < NG ? grp + 2 : NG - 1;
+      uint32_t f = flags[g1], fn = flags[gn];
+      const f32x4 next = loadf4(part + g1 * (G * 4) + cchunk * 4), after = loadf4(part + gn * (G * 4) + cchunk * 4);
+      f = grp + 1 < NG ? f : 0u;
+      fn = grp + 2 < NG ? fn : 0u;
+      if (f != 0u) tot += next;
+      f = f == 2u ? fn : 0u;
+      if (f != 0u) tot += after;
+      for (int g2 = grp + 3; f == 2u; g2 += kAhead) {
+        uint32_t fs[kAhead];
+        f32x4 more[kAhead];
 #pragma unroll
-      for (int j = 0; j < kAhead; ++j) {   // branch-free: behind the run's end f is 0 or 1, and the identity is added
-        f = f == 2u ? fs[j] : 0u;
-        const bool in = f != 0u;
-        tot += f32x4{in ? more[j].x : -0.0f, in ? more[j].y : -0.0f, in ? more[j].z : -0.0f, in ? more[j].w : -0.0f};
+        for (int j = 0; j < kAhead; ++j) {
+          const int gj = g2 + j < NG ? g2 + j : NG - 1;
+          fs[j] = g2 + j < NG ? flags[gj] : 0u;
+          more[j] = loadf4(part + gj * (G * 4) + cchunk * 4);
+        }
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {   // branch-free: behind the run's end f is 0 or 1, and the identity is added
+          f = f == 2u ? fs[j] : 0u;
+          const bool in = f != 0u;
+          tot += f32x4{in ? more[j].x : -0.0f, in ? more[j].y : -0.0f, in ? more[j].z : -0.0f, in ? more[j].w : -0.0f};
+        }
       }
     }
     if (col_ok) row_update_store<DT, OPT>(cur, curv, tot, u);
