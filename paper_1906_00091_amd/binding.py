@@ -116,11 +116,14 @@ def _check(fn: str, status: int) -> None:
 
 
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    """Handle of torch's current stream on the current device, what torch.cuda.current_stream().cuda_stream is.  That makes
+    two Python objects on the way (2.8 us; 0.2 us here), more than a whole launch takes the host: a batch of 64 scored in one
+    launch 6.7 / 4.4 us."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 class SparseBatch:
