@@ -597,6 +597,35 @@ __device__ inline float* state_base(const UpdArgs& u, int k) {
 // ---------------------------------------------------------------------------
 int check_batch(const dlrm_sparse_batch* s);  // util.hip
 
+// Bits of the partition digit.  One workgroup reduces a bucket: `buckets` of them at least, where that leaves `least` pairs in each,
+// and 1024 pairs at most.
+inline int bits_for(int64_t nnz, int32_t K, double buckets, double least) {
+  double target = (double)nnz / buckets;
+  if (target < least) target = least;
+  if (target > 1024.0) target = 1024.0;
+  const double per_table = (double)nnz / (double)K;
+  int tb = 0;
+  while (tb < kMaxTopBits && per_table / (double)(1 << tb) > target) ++tb;
+  return tb;
+}
+// Wide rows have few lane groups to a workgroup (four at 64 lanes a row), so a bucket of a given size takes them longer: more and
+// smaller buckets end together and leave hot rows less company.  A bucket of narrow rows is mostly its sort: fewer and larger
+// ones.  Update with its lookup, 1536 buckets of 128 pairs for every width / now, us: 4 tables of 164 K lookups, d = 256 441 / 436;
+// 40 skewed ones of 22 K, d = 256 281 / 237; 26 skewed one-hot ones of 8192, d = 128 162 / 150; 26 bf16 ones of 41 K, d = 64
+// 176 / 162; 13 ones of 37 K, d = 36, Adagrad 135 / 126; 100 fp16 ones of 4096, d = 32, Adagrad 135 / 129; 95 of 2900, d = 4 75 / 63;
+// 4 uniform ones of 47 K, d = 8 44 / 38.  Of 580 such batches (2^16 to 8 M lookups), mean by lanes of a row 4 and less -1.6 %,
+// 8 -0.8, 16 -0.8, 32 -1.8, 64 -5.7; uniform lookups of 100 to 120 pairs a bucket can lose (78 tables of 3700, d = 116 121 / 133).  1024
+// digits only for the widest rows or where 512 leave over 1024 pairs: every tile's counts grow with them (4 tables of 182 K lookups,
+// d = 64 72 / 77).  Small batches keep the split that a batch without a partition has (direct_reduce_kernel: every bucket reads all row
+// ids of its table, 26 x 2048 one-hot 30 / 35 us with twice the buckets), whose bits are those of the prepared call.
+inline int digit_bits(int64_t nnz, int32_t K, int lanes) {
+  if (nnz <= kSmallBatch) return bits_for(nnz, K, 1536.0, 128.0);
+  if (lanes == 64) return bits_for(nnz, K, 4096.0, 112.0);
+  if (lanes < 8) return bits_for(nnz, K, 1536.0, 224.0);
+  const int tb = bits_for(nnz, K, 2560.0, lanes == 8 ? 192.0 : lanes == 16 ? 128.0 : 112.0);
+  return tb < kMaxTopBits ? tb : bits_for(nnz, K, 1536.0, 128.0);
+}
+
 inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLayout& L, void* ws) {
   char* base = static_cast<char*>(ws);
   g.indices = s->indices;
@@ -611,15 +640,8 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   g.max_huge = L.max_huge;
   g.nt_max = (int32_t)L.nt_max;
   g.tile_shift = tile_shift_for(s->nnz_total);
-  // partition digit: one workgroup per bucket, so aim at >= ~1536 buckets when the batch is
-  // large enough, with 128..1024 pairs per bucket (measured on the 8 x 1M x 64 multi-hot batch:
-  // 800 pairs per bucket beat 200 by 8%); never more digits than the row ids have
-  double target = (double)s->nnz_total / 1536.0;
-  if (target < 128.0) target = 128.0;
-  if (target > 1024.0) target = 1024.0;
-  const double per_table = (double)s->nnz_total / (double)s->K;
-  int tb = 0;
-  while (tb < kMaxTopBits && per_table / (double)(1 << tb) > target) ++tb;
+  // never more digits than the row ids have
+  int tb = digit_bits(s->nnz_total, s->K, pow2_ceil(s->d / 4));
   const int kb = ilog2_ceil(s->max_rows);
   if (tb > kb) tb = kb;
   g.top_bits = tb;

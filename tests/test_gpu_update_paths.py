@@ -455,6 +455,21 @@ def test_rows_split_off_oversized_buckets_fill_lds_piecewise(runs, others, dtype
     assert _assert_exact_update(b, dtype, weighted, ("sort", "prepared"))["dominant_row_splits"] >= 1
 
 
+# the partition digit by the lanes of a row (4 and less, 8, 16, 32, 64) at the smallest batches it depends on: tables x lookups a
+# table on both sides of a step of every class, one table of 1024 digits, tables of fewer rows than digits
+@pytest.mark.parametrize("K,per", [(8, 8194), (13, 5043), (16, 7200), (1, 120000)])
+@pytest.mark.parametrize("d", [4, 16, 28, 64, 100, 132])
+def test_partition_digits_by_row_width(K, per, d):
+    print("[case] digits by width K=%d per=%d d=%d" % (K, per, d), flush=True)
+    rng = np.random.default_rng([K, d])
+    B = 900
+    rows = [20000 if k % 3 else 37 for k in range(K)]
+    cuts = np.sort(rng.integers(0, per + 1, size=(K, B - 1)), axis=1)
+    b = _batch([np.diff(c, prepend=0, append=per).tolist() for c in cuts], rows, seed=d, d=d)
+    for weighted in (False, True):
+        _assert_exact_update(b, gen.F32, weighted, ("sort", "prepared"))
+
+
 @pytest.mark.parametrize("dtype,d", [(gen.F32, 4), (gen.F32, 256), (gen.F16, 512)])
 def test_one_launch_forward_without_lookups(dtype, d):
     """No index to read: every pooled vector is zero, the dense part of the result a copy (rows up to the widest)."""
