@@ -123,6 +123,146 @@ __global__ __launch_bounds__(kIntThreads) void interact_fwd_kernel(const float* 
   for (int c = lane; c < P; c += DLRM_WAVE) Rb[d + c] = Rp[c];
 }
 
+// The same products, instructions and order with a workgroup of W wavefronts per sample (W <= NB <= 2 W) and T_b staged in LDS,
+// kSplitCols columns at a time: each row is read from memory once, along its columns, where the operand layout reads 64 bytes
+// of 16 rows at a time.  Wavefront w computes the tiles of row blocks NB - 1 - w and, where there is one, w - (2 W - NB), which
+// deals the tiles evenly (seven blocks: seven each), and the dense row's products with them; all leave together.  Bound by the
+// chain of one sample at small batches, by memory at large ones (65 rows of 128 columns, batch 16384: 4.5 of the copy's 4.6 TB/s).
+// Three wavefronts per SIMD: with what the compiler takes by itself seven and eight blocks have two, 101 rows of 64, batch 16384
+// 240.8 / 209.7 us.  Operands read from memory by each of the four instead: 377.
+constexpr int kSplitCols = 64;
+// words of a staged row: whole 16-column chunks, and 4 words so that the 16 rows an operand is read from fall into 64 banks
+__host__ __device__ inline int split_stride(int d) { return (d < kSplitCols ? (d + 15) & ~15 : kSplitCols) + 4; }
+template <int NB, int W>
+constexpr int kSplitTiles = NB > 2 * NB - 2 * W + 1 ? NB : 2 * NB - 2 * W + 1;   // of a wavefront, at most
+
+// Wavefront w's tiles, one after the other: of row block I1, then of row block I0.  LO: the lane's place in the first staged row.
+template <int NB, int W, int w>
+struct SplitShare {
+  static constexpr int I1 = NB - 1 - w, I0 = w - (2 * W - NB), N1 = I1 + 1, N0 = I0 < 0 ? 0 : I0 + 1;
+  static_assert(N1 + N0 <= kSplitTiles<NB, W>, "a register for each");
+  // the 16-column chunks of the staged columns, `cols` of them
+  static __device__ inline void products(const float* lo, int cs, int cols, f32x4* acc, float* pd) {
+#pragma unroll
+    for (int q = 0; q < kSplitCols / 16; ++q) {
+      if (16 * q < cols) {  // uniform
+        const f32x4 xd = loadf4(lo + 16 * q - (int)(threadIdx.x & 15) * cs - cs);   // the dense row
+        f32x4 x[NB];
+#pragma unroll
+        for (int jb = 0; jb <= I1; ++jb) x[jb] = loadf4(lo + jb * 16 * cs + 16 * q);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          pd[0] = fmaf(x[I1][t], xd[t], pd[0]);
+          if constexpr (N0 > 0) pd[1] = fmaf(x[I0][t], xd[t], pd[1]);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+          for (int jb = 0; jb < N1; ++jb) acc[jb] = mfma16(x[I1][t], x[jb][t], acc[jb]);
+#pragma unroll
+          for (int jb = 0; jb < N0; ++jb) acc[N1 + jb] = mfma16(x[N0 > 0 ? I0 : 0][t], x[jb][t], acc[N1 + jb]);
+        }
+      }
+    }
+  }
+  template <int ib>
+  static __device__ inline void put_row_block(float* pairs, int K, const f32x4* acc, float v) {
+    const int i = lane_id() & 15, h = lane_id() >> 4;
+    v += __shfl_xor(v, 16, DLRM_WAVE);
+    v += __shfl_xor(v, 32, DLRM_WAVE);
+    const int e = ib * 16 + i;
+    if (h == 0 && e < K) pairs[(e + 1) * e / 2] = v;
+#pragma unroll
+    for (int jb = 0; jb <= ib; ++jb) {
+      const int ej = jb * 16 + i;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int ei = ib * 16 + 4 * h + c;
+        if (ej < ei && ei < K) pairs[(ei + 1) * ei / 2 + ej + 1] = acc[jb][c];
+      }
+    }
+  }
+  static __device__ inline void put(float* pairs, int K, const f32x4* acc, const float* pd) {
+    put_row_block<I1>(pairs, K, acc, pd[0]);
+    if constexpr (N0 > 0) put_row_block<I0>(pairs, K, acc + N1, pd[1]);
+  }
+};
+// f(SplitShare of this wavefront)
+template <int NB, int W, typename F>
+__device__ inline void for_share(int w, F f) {
+  if (w == 0) f(SplitShare<NB, W, 0>());
+  if (w == 1) f(SplitShare<NB, W, 1>());
+  if constexpr (W > 2) {
+    if (w == 2) f(SplitShare<NB, W, 2>());
+    if (w == 3) f(SplitShare<NB, W, 3>());
+  }
+}
+
+template <int NB, int W>
+__global__ __launch_bounds__(W * DLRM_WAVE, 3) void interact_fwd_split_kernel(const float* __restrict__ T, float* __restrict__ R,
+                                                                            int F, int d) {
+  static_assert(W <= NB && NB <= 2 * W && (W == 2 || W == 4), "one or two row blocks a wavefront");
+  constexpr int NT = W * DLRM_WAVE;
+  constexpr int RP = NT / 16;                       // rows staged per pass, 16 bytes a lane
+  constexpr int NP = (16 * NB + 1 + RP - 1) / RP;   // passes
+  extern __shared__ __align__(16) float lds[];
+  const int lane = lane_id(), w = (int)__builtin_amdgcn_readfirstlane(wave_id());
+  const int tl = w * DLRM_WAVE + lane;
+  const int b = blockIdx.x;
+  const int K = F - 1;
+  const int P = F * (F - 1) / 2;
+  const float* Tb = T + (int64_t)b * F * d;
+  float* Rb = R + (int64_t)b * ((int64_t)d + P);
+  const int cs = split_stride(d);
+  const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 acc[kSplitTiles<NB, W>];
+#pragma unroll
+  for (int t = 0; t < kSplitTiles<NB, W>; ++t) acc[t] = zero;
+  float pd[2] = {0.0f, 0.0f};   // partial products with the dense row
+  const int srow = tl >> 4, scol = 4 * (tl & 15);   // this thread's piece of a pass
+  f32x4 v[NP];
+  const auto request = [&](int k0) {   // (rows past the last one and columns past d repeat others: no load behind a branch)
+    const int col = k0 + scol < d ? k0 + scol : 0;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int r = p * RP + srow < F ? p * RP + srow : F - 1;
+      v[p] = loadf4(Tb + (int64_t)r * d + col);
+    }
+  };
+  request(0);
+  // row e + 1 of T_b is embedding row e; operands of rows past the last one are whatever lies there: their products land in
+  // entries that are never stored
+  const float* const lo = lds + ((lane & 15) + 1) * cs + 4 * (lane >> 4);
+  for (int k0 = 0; k0 < d; k0 += kSplitCols) {
+    if (k0 > 0) __syncthreads();   // the previous columns have been read
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int r = p * RP + srow;
+      if (r < F && scol + 4 < cs) storef4(lds + r * cs + scol, k0 + scol < d ? v[p] : zero);   // columns past d contribute 0 * 0
+    }
+    __syncthreads();
+    if (k0 + kSplitCols < d) request(k0 + kSplitCols);   // on their way while these are multiplied
+    for_share<NB, W>(w, [&](auto share) { share.products(lo, cs, d - k0, acc, pd); });
+  }
+  for (int c = tl; c < d; c += NT) Rb[c] = Tb[c];  // dense part: exact copy of row 0
+  __syncthreads();   // the staged rows have been read: the pairs take their place
+  for_share<NB, W>(w, [&](auto share) { share.put(lds, K, acc, pd); });
+  __syncthreads();
+  for (int c0 = 0; c0 < P; c0 += NT * 8) {
+    float r[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int c = c0 + q * NT + tl;
+      r[q] = lds[c < P ? c : P - 1];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int c = c0 + q * NT + tl;
+      if (c < P) Rb[d + c] = r[q];
+    }
+  }
+}
+
 // CW consecutive floats (CW = 2 or 4, address CW*4-byte aligned) <-> registers; zeros if !ok
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 template <int CW>
@@ -462,8 +602,41 @@ static int pair_stride(int F) {
   return P < 4 ? 4 : ((P + 3) & ~3);
 }
 
+// Forward of three and more row blocks: a wavefront per sample / W of them, us.  Small batches, whose SIMDs have one wavefront or
+// none, 101 rows of 32 columns, batch 32 / 512 / 1024: 13.3 / 14.9 / 17.2 and 5.5 / 8.2 / 13.5.  Large ones where staging pays, batch
+// 16384: 65 rows of 128 columns 173.5 / 151.5, 66 of 64 124 / 119, 97 of 32 143.7 / 136.7, 113 of 32 247 / 167, 113 of 8 179 / 143.  Where the lines
+// lie: 81 rows of 8 columns, batch 1024 / 2048 8.7 / 7.4, 10.9 / 12.0; 49 rows of 8, 512 / 1024 4.8 / 4.4, 4.8 / 5.1; 66 of 32, 4096 /
+// 16384 25.1 / 22.8, 81.5 / 89.0; 34 of 32, 1024 / 4096 4.9 / 4.7, 10.0 / 11.5, of 64, 2048 / 16384 9.6 / 8.7, 49.3 / 49.8; 50 of 64, 2048 / 8192
+// 15.1 / 16.1, 46.9 / 45.5, of 128, 2048 / 4096 23.5 / 24.7, 43.9 / 40.1.
+static bool split_fwd(int nb, int B, int d) {
+  if (B <= 512) return true;
+  if (d < 32) return nb >= 5 && B <= 1024;
+  if (nb >= 6 || B <= 1024) return true;
+  if (nb == 5) return d >= 64 || B <= 4096;
+  return d >= 64 && (nb == 3 || B >= (d > 64 ? 4096 : 8192));
+}
+constexpr int kTiledPerLaunch = 1 << 23;   // samples: a launch holds fewer than 2^32 threads
+template <int NB>
+static int launch_fwd_split(const float* T, float* R, int B, int F, int d, hipStream_t st) {
+  constexpr int W = NB > 4 ? 4 : 2;
+  const int words = (16 * NB + 1) * split_stride(d), pairs = pair_stride(F);
+  const size_t lds = (size_t)(words > pairs ? words : pairs) * 4;   // <= 35 KB
+  const int64_t row = (int64_t)F * d, res = (int64_t)d + F * (F - 1) / 2;
+  for (int64_t b0 = 0; b0 < B; b0 += kTiledPerLaunch) {
+    const int n = (int)(B - b0 < kTiledPerLaunch ? B - b0 : kTiledPerLaunch);
+    hipLaunchKernelGGL((interact_fwd_split_kernel<NB, W>), dim3(n), dim3(W * DLRM_WAVE), lds, st,
+                       T + b0 * row, R + b0 * res, F, d);
+    DLRM_CHECK_LAUNCH();
+  }
+  return DLRM_OK;
+}
+
 template <int NB>
 static int launch_fwd(const float* T, float* R, int B, int F, int d, hipStream_t st) {
+  static_assert(NB <= 7, "eight row blocks always take the split kernel");
+  if constexpr (NB > 2) {
+    if (split_fwd(NB, B, d)) return launch_fwd_split<NB>(T, R, B, F, d, st);
+  }
   const int pstride = pair_stride(F);
   const size_t lds = (size_t)kIntWaves * pstride * 4;
   if (lds > 64 * 1024) {
@@ -484,7 +657,6 @@ constexpr int kSplitBelow = 1024;   // samples: one wavefront for each of the ma
 // 148 / 377 / 496 and 133 / 371 / 502 us.  From six blocks on tiles are level (90 rows of 4 to 16 columns: 241 and 245 us
 // at batch 16384) or ahead everywhere.
 constexpr int kSplitBelow5 = 4096, kSplitBelow5Wide = 12288;
-constexpr int kTiledPerLaunch = 1 << 23;   // samples: a launch holds fewer than 2^32 threads
 template <int NB>
 static int launch_bwd_tiled(const float* T, const float* dR, float* dT, int B, int F, int d, hipStream_t st) {
   constexpr int WPS = NB >= 4 ? 4 : NB;
@@ -532,7 +704,7 @@ extern "C" int32_t dlrm_interact_dot_fwd(const float* T, int32_t B, int32_t F, i
     case 5: return launch_fwd<5>(T, R, B, F, d, hs);
     case 6: return launch_fwd<6>(T, R, B, F, d, hs);
     case 7: return launch_fwd<7>(T, R, B, F, d, hs);
-    case 8: return launch_fwd<8>(T, R, B, F, d, hs);
+    case 8: return launch_fwd_split<8>(T, R, B, F, d, hs);
   }
   return DLRM_ERR_BAD_SHAPE;
 }

@@ -372,6 +372,28 @@ def test_updates_of_rows_that_share_sectors(dtype, d):
             _assert_adagrad_update(b, dtype, weighted, ("sort", "prepared"))
 
 
+# row blocks, columns and batches on either side of where the forward takes W wavefronts a sample; the last sample of the large
+# batch alone in a call of its own too
+@pytest.mark.parametrize("F,d,B", [(34, 28, 513), (34, 60, 1025), (49, 64, 1025), (50, 32, 1025), (50, 64, 8191), (65, 132, 4095),
+                                   (66, 4, 1025), (66, 36, 4097), (81, 64, 4097), (90, 28, 1025), (101, 32, 1025), (113, 20, 1025),
+                                   (114, 68, 513), (128, 256, 600)])
+def test_interaction_forward_gives_the_same_bits_at_any_batch_size(F, d, B):
+    print("[case] interaction forward F=%d d=%d B=%d" % (F, d, B), flush=True)
+    g = torch.Generator(device=DEV).manual_seed(F)
+    T = torch.randn((B, F, d), generator=g, device=DEV)
+    n = d + F * (F - 1) // 2
+    R = torch.full((B, n), float("nan"), device=DEV)
+    hot.dlrm_interact_dot_fwd(T, R)
+    parts = torch.full((B, n), float("nan"), device=DEV)
+    for b0 in list(range(0, B - 1, 512)) + [B - 1]:
+        b1 = min(b0 + 512, B - 1) if b0 < B - 1 else B
+        hot.dlrm_interact_dot_fwd(T[b0:b1].contiguous(), parts[b0:b1])
+    assert torch.equal(R, parts)
+    ref = oracle.interact_dot_fwd(T[-2:].cpu().numpy())
+    scale = oracle.interact_dot_fwd(T[-2:].abs().cpu().numpy())
+    assert np.max(np.abs(R[-2:].cpu().numpy() - ref) / np.maximum(scale, 1e-30)) <= d * 2.0 ** -24   # fp32 sums of d terms
+
+
 # two to five row blocks on either side of the batch size up to which wavefronts share a sample; rows of dR at
 # every alignment (d + P odd) and at one
 @pytest.mark.parametrize("F,d,below", [(18, 20, 1024), (33, 128, 1024), (34, 36, 1024), (50, 72, 1024), (65, 16, 1024),
