@@ -12,6 +12,8 @@
 // what lets every lane fetch 16 contiguous bytes and use them in 4 consecutive instructions.
 #include "common.h"
 
+#include <type_traits>
+
 namespace dlrm {
 
 constexpr int kIntThreads = 256;
@@ -263,7 +265,7 @@ __global__ __launch_bounds__(W * DLRM_WAVE, 3) void interact_fwd_split_kernel(co
   }
 }
 
-// CW consecutive floats (CW = 2 or 4, address CW*4-byte aligned) <-> registers; zeros if !ok
+// CW consecutive floats (CW = 1, 2 or 4, address CW*4-byte aligned) <-> registers; zeros if !ok
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 template <int CW>
 __device__ inline void load_cols(const float* p, bool ok, float* out) {
@@ -273,6 +275,9 @@ __device__ inline void load_cols(const float* p, bool ok, float* out) {
     out[1] = ok ? v.y : 0.0f;
     out[2] = ok ? v.z : 0.0f;
     out[3] = ok ? v.w : 0.0f;
+  } else if constexpr (CW == 1) {
+    const float v = *p;
+    out[0] = ok ? v : 0.0f;
   } else {
     const f32x2 v = *reinterpret_cast<const f32x2*>(p);
     out[0] = ok ? v.x : 0.0f;
@@ -283,6 +288,8 @@ template <int CW>
 __device__ inline void store_cols(float* p, const float* v) {
   if constexpr (CW == 4) {
     storef4(p, f32x4{v[0], v[1], v[2], v[3]});
+  } else if constexpr (CW == 1) {
+    *p = v[0];
   } else {
     *reinterpret_cast<f32x2*>(p) = f32x2{v[0], v[1]};
   }
@@ -297,16 +304,12 @@ __device__ inline void store_cols(float* p, const float* v) {
 // whose 16 columns are {16*CW*g + CW*x' + u}, so that after the contraction every lane owns CW
 // consecutive columns of 4 rows and stores them as one vector.  The dense row enters and leaves through plain FMAs: a rank-1
 // update of every tile, and one matrix-vector product for its own gradient.
-template <int NB>
+template <int NB, int CW>
 __global__ __launch_bounds__(kIntThreads) void interact_bwd_kernel(const float* __restrict__ T,
                                                                     const float* __restrict__ dR,
                                                                     float* __restrict__ dT, int B, int F,
                                                                     int d, int gstride) {
   constexpr int JS = 4 * NB;  // contraction steps of 4 embedding rows
-  // columns per lane and round: 4 (64-column groups) while the operand registers allow three
-  // wavefronts per SIMD (up to 4 row blocks: 144 registers; measured on 65 rows of 128 columns, batch 16384:
-  // 0.348 ms with 2 columns, 0.317 ms with 4), else 2 -- a lane then owns CW consecutive columns of 4 rows
-  constexpr int CW = NB <= 4 ? 4 : 2;
   extern __shared__ float lds[];
   const int lane = lane_id();
   const int b = blockIdx.x * kIntWaves + wave_id();
@@ -429,11 +432,10 @@ __global__ __launch_bounds__(kIntThreads) void interact_bwd_kernel(const float* 
 constexpr int kGRow = 17, kGTile = 16 * kGRow;
 __host__ __device__ constexpr int g_words(int NB) { return NB * (NB + 1) / 2 * kGTile + 16 * NB; }
 
-template <int NB, int WPS>
+template <int NB, int WPS, int CW>
 __global__ __launch_bounds__(WPS * DLRM_WAVE) void interact_bwd_tiled_kernel(
     const float* __restrict__ T, const float* __restrict__ dR, float* __restrict__ dT, int F, int d) {
   constexpr int JS = 4 * NB;  // contraction steps of 4 embedding rows
-  constexpr int CW = NB <= 4 ? 4 : 2;
   extern __shared__ __align__(16) float lds[];
   const int lane = lane_id();
   const int sub = wave_id();
@@ -657,6 +659,19 @@ constexpr int kSplitBelow = 1024;   // samples: one wavefront for each of the ma
 // 148 / 377 / 496 and 133 / 371 / 502 us.  From six blocks on tiles are level (90 rows of 4 to 16 columns: 241 and 245 us
 // at batch 16384) or ahead everywhere.
 constexpr int kSplitBelow5 = 4096, kSplitBelow5Wide = 12288;
+// f(columns per lane and round): 4 (64-column groups) while the operand registers allow three wavefronts per SIMD (up to 4 row
+// blocks: 144 registers; measured on 65 rows of 128 columns, batch 16384: 0.348 ms with 2 columns, 0.317 ms with 4), else 2 -- a
+// lane then owns CW consecutive columns of 4 rows.  Narrow rows: 1 or 2 columns, so that a row's columns occupy all 16 lanes; with 4
+// (five blocks and more 2) most of the instructions multiplied columns past d.  27 rows of 16 columns, batch 2048 / 16384
+// 7.8 / 6.0, 36.7 / 21.1 us; 65 rows of 16, 1024 / 16384 15.8 / 8.1, 150.6 / 73.7; of 32 16.4 / 10.4, 156.0 / 103.7; 101 rows of 16
+// 24.4 / 15.3, 288 / 178; 9 rows of 16, 16384 14.4 / 11.6.
+template <int NB, typename F>
+static void for_columns(int d, F f) {
+  if (d <= 16) return f(std::integral_constant<int, 1>());
+  if (d <= 32 || NB > 4) return f(std::integral_constant<int, 2>());
+  if constexpr (NB <= 4) f(std::integral_constant<int, 4>());
+}
+
 template <int NB>
 static int launch_bwd_tiled(const float* T, const float* dR, float* dT, int B, int F, int d, hipStream_t st) {
   constexpr int WPS = NB >= 4 ? 4 : NB;
@@ -665,8 +680,10 @@ static int launch_bwd_tiled(const float* T, const float* dR, float* dT, int B, i
   const int64_t row = (int64_t)F * d, grad = (int64_t)d + F * (F - 1) / 2;
   for (int64_t b0 = 0; b0 < B; b0 += kTiledPerLaunch) {
     const int n = (int)(B - b0 < kTiledPerLaunch ? B - b0 : kTiledPerLaunch);
-    hipLaunchKernelGGL((interact_bwd_tiled_kernel<NB, WPS>), dim3(n), dim3(WPS * DLRM_WAVE), lds, st, T + b0 * row,
-                       dR + b0 * grad, dT + b0 * row, F, d);
+    for_columns<NB>(d, [&](auto cw) {
+      hipLaunchKernelGGL((interact_bwd_tiled_kernel<NB, WPS, decltype(cw)::value>), dim3(n), dim3(WPS * DLRM_WAVE), lds, st,
+                         T + b0 * row, dR + b0 * grad, dT + b0 * row, F, d);
+    });
     DLRM_CHECK_LAUNCH();
   }
   return DLRM_OK;
@@ -680,8 +697,10 @@ static int launch_bwd(const float* T, const float* dR, float* dT, int B, int F, 
   }
   const int gstride = pair_stride(F);
   const size_t lds = (size_t)kIntWaves * gstride * 4;   // <= 52 KB
-  hipLaunchKernelGGL((interact_bwd_kernel<NB>), dim3(div_up(B, kIntWaves)), dim3(kIntThreads), lds, st, T, dR,
-                     dT, B, F, d, gstride);
+  for_columns<NB>(d, [&](auto cw) {
+    hipLaunchKernelGGL((interact_bwd_kernel<NB, decltype(cw)::value>), dim3(div_up(B, kIntWaves)), dim3(kIntThreads), lds, st, T,
+                       dR, dT, B, F, d, gstride);
+  });
   DLRM_CHECK_LAUNCH();
   return DLRM_OK;
 }

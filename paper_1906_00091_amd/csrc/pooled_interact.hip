@@ -274,7 +274,7 @@ static int dispatch_it(const PiArgs& a, bool idx32, hipStream_t st) {
   return idx32 ? dispatch_nb<DT, int32_t>(a, st) : dispatch_nb<DT, int64_t>(a, st);
 }
 
-// CW consecutive floats (CW = 2 or 4, address CW*4-byte aligned) <-> registers; zeros if !ok
+// CW consecutive floats (CW = 1, 2 or 4, address CW*4-byte aligned) <-> registers; zeros if !ok
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 template <int CW>
 __device__ inline void load_cols(const float* p, bool ok, float* out) {
@@ -284,6 +284,9 @@ __device__ inline void load_cols(const float* p, bool ok, float* out) {
     out[1] = ok ? v.y : 0.0f;
     out[2] = ok ? v.z : 0.0f;
     out[3] = ok ? v.w : 0.0f;
+  } else if constexpr (CW == 1) {
+    const float v = *p;
+    out[0] = ok ? v : 0.0f;
   } else {
     const f32x2 v = *reinterpret_cast<const f32x2*>(p);
     out[0] = ok ? v.x : 0.0f;
@@ -294,6 +297,8 @@ template <int CW>
 __device__ inline void store_cols(float* p, const float* v) {
   if constexpr (CW == 4) {
     storef4(p, f32x4{v[0], v[1], v[2], v[3]});
+  } else if constexpr (CW == 1) {
+    *p = v[0];
   } else {
     *reinterpret_cast<f32x2*>(p) = f32x2{v[0], v[1]};
   }
@@ -320,7 +325,7 @@ struct PbArgs {
 
 constexpr int kPbInfoWords = 4;  // per bag in LDS: length, first position (global), table base lo / hi
 
-// CW (4 or 2) consecutive table elements from a device address held as an integer, widened to fp32
+// CW (4, 2 or 1) consecutive table elements from a device address held as an integer, widened to fp32
 template <int DT, int CW>
 __device__ inline void gload_cols(uint64_t addr, float* out) {
   typedef const __attribute__((address_space(1))) f32x4* g16;
@@ -330,6 +335,8 @@ __device__ inline void gload_cols(uint64_t addr, float* out) {
     if constexpr (CW == 4) {
       const f32x4 v = *(g16)addr;
       out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
+    } else if constexpr (CW == 1) {
+      out[0] = u2f(*(g4)addr);
     } else {
       const u32x2 v = *(g8)addr;
       out[0] = u2f(v.x); out[1] = u2f(v.y);
@@ -340,10 +347,17 @@ __device__ inline void gload_cols(uint64_t addr, float* out) {
       const u32x2 v = *(g8)addr;
       w0 = v.x;
       w1 = v.y;
+    } else if constexpr (CW == 1) {
+      typedef const __attribute__((address_space(1))) uint16_t* g2;
+      w0 = *(g2)addr;
     } else {
       w0 = *(g4)addr;
     }
-    if constexpr (DT == DLRM_F16) {
+    if constexpr (CW == 1) {
+      float none;   // the other half: zero
+      if constexpr (DT == DLRM_F16) half2_to_float2(w0, out[0], none);
+      else bf162_to_float2(w0, out[0], none);
+    } else if constexpr (DT == DLRM_F16) {
       half2_to_float2(w0, out[0], out[1]);
       if constexpr (CW == 4) half2_to_float2(w1, out[2], out[3]);
     } else {
@@ -353,10 +367,9 @@ __device__ inline void gload_cols(uint64_t addr, float* out) {
   }
 }
 
-template <int NB, int DT, typename IT>
+template <int NB, int DT, int CW, typename IT>
 __global__ __launch_bounds__(kPiThreads) void pooled_interact_bwd_kernel(PbArgs a) {
   constexpr int JS = 4 * NB;  // contraction steps of 4 embedding rows
-  constexpr int CW = NB <= 2 ? 4 : 2;
   constexpr int EB = Tab<DT>::EB;
   extern __shared__ float lds[];
   const int lane = lane_id();
@@ -504,13 +517,22 @@ __global__ __launch_bounds__(kPiThreads) void pooled_interact_bwd_kernel(PbArgs 
   }
 }
 
-template <int NB, int DT, typename IT>
-static int launch_pb(const PbArgs& a, hipStream_t st) {
+template <int NB, int DT, int CW, typename IT>
+static int launch_pb_cols(const PbArgs& a, hipStream_t st) {
   const size_t lds = (size_t)kPiWaves * a.gstride * 4 + (size_t)kPiWaves * 16 * kPiMaxNB * kPbInfoWords * 4;
-  hipLaunchKernelGGL((pooled_interact_bwd_kernel<NB, DT, IT>), dim3(div_up(a.B, kPiWaves)), dim3(kPiThreads), lds,
+  hipLaunchKernelGGL((pooled_interact_bwd_kernel<NB, DT, CW, IT>), dim3(div_up(a.B, kPiWaves)), dim3(kPiThreads), lds,
                      st, a);
   DLRM_CHECK_LAUNCH();
   return DLRM_OK;
+}
+
+// Columns per lane as in interact_bwd_kernel (4 up to two row blocks, else 2), with 1 and 2 for narrow rows: 27 rows of 16 fp32 columns,
+// one row a bag, batch 4096 / 16384 14.3 / 10.3, 43.9 / 31.3 us; 65 rows of 16 41.6 / 31.7, 156.4 / 99.7; 27 rows of 32 15.4 / 12.9, 45.6 / 39.8.
+template <int NB, int DT, typename IT>
+static int launch_pb(const PbArgs& a, hipStream_t st) {
+  if (a.d <= 16) return launch_pb_cols<NB, DT, 1, IT>(a, st);
+  if (a.d <= 32 || NB > 2) return launch_pb_cols<NB, DT, 2, IT>(a, st);
+  if constexpr (NB <= 2) return launch_pb_cols<NB, DT, 4, IT>(a, st);
 }
 
 template <int DT, typename IT>

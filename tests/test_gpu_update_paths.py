@@ -419,6 +419,27 @@ def test_interaction_backward_gives_the_same_bits_at_any_batch_size(F, d, below)
     assert ((whole[:3].double().cpu() - want).abs() / scale).max() <= 1e-5
 
 
+# one, two and four columns a lane, every storage type, one to four row blocks; bags of no row, one and more
+@pytest.mark.parametrize("dtype", [gen.F32, gen.F16, gen.BF16])
+@pytest.mark.parametrize("K,d", [(7, 8), (16, 16), (17, 24), (26, 32), (26, 40), (40, 16), (64, 8), (64, 24)])
+def test_backward_without_T_of_narrow_rows(K, d, dtype):
+    print("[case] backward without T K=%d d=%d dtype=%s" % (K, d, dtype), flush=True)
+    b = gen.make_batch(gen.custom_workload("narrow", K=K, B=77, d=d, dtype=dtype, rows=50, bag=("uniform", 0, 3), dist=("uniform",), seed=K))
+    g = torch.Generator(device=DEV).manual_seed(d)
+    tables = [(torch.randn((50, d), generator=g, device=DEV)).to({gen.F32: torch.float32, gen.F16: torch.float16}.get(dtype, torch.bfloat16))
+              for _ in range(K)]
+    sb = hot.SparseBatch(tables, dtype, torch.from_numpy(b.indices).to(DEV), torch.from_numpy(b.offsets).to(DEV),
+                         torch.from_numpy(b.tbl_off).to(DEV), b.nnz)
+    F, n = K + 1, d + (K + 1) * K // 2
+    x, dR = torch.randn((77, d), generator=g, device=DEV), torch.randn((77, n), generator=g, device=DEV)
+    T, R = torch.full((77, F, d), -5.0, device=DEV), torch.empty((77, n), device=DEV)
+    hot.dlrm_emb_interact_fwd(sb, x, T, R, algo=hot.FWD_FUSED)
+    want, got = torch.full_like(T, -5.0), torch.full_like(T, -7.0)
+    hot.dlrm_interact_dot_bwd(T, dR, want)
+    hot.dlrm_emb_interact_bwd(sb, x, dR, got)
+    assert torch.equal(got, want)
+
+
 def test_interaction_backward_beyond_one_launch():
     """2^24 samples of 82 rows, a workgroup of 256 threads each: more threads than one launch holds.  The samples repeat,
     so the gradients must too."""
