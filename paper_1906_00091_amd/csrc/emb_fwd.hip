@@ -80,6 +80,33 @@ __device__ inline void add_row(float* acc, u32x4 v, float w) {
   }
 }
 
+// The last rounds of a chunk, up to U of them, with U row loads in flight and no branch: positions past the end re-read n - 1 and
+// add the identity.
+template <int DT, int G, int U, bool WT>
+__device__ inline void gather_tail(float* acc, uint64_t Wbase, uint32_t row_bytes, uint32_t rows, float wts, int n, int slot,
+                                   int q) {
+  constexpr int S = DLRM_WAVE / G;
+  u32x4 v[U];
+  float wt[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int e = (q + u) * S + slot;
+    const uint32_t r = (uint32_t)__shfl((int)rows, e < n ? e : n - 1, DLRM_WAVE);
+    wt[u] = 1.0f;
+    if constexpr (WT) wt[u] = __shfl(wts, e < n ? e : n - 1, DLRM_WAVE);
+    v[u] = load16_global(Wbase + (uint64_t)r * row_bytes);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const bool past = (q + u) * S + slot >= n;
+    if (past) {
+      v[u] = Tab<DT>::ident();
+      wt[u] = 1.0f;   // 1 * (-0) leaves the sum alone
+    }
+    add_row<DT, WT>(acc, v[u], wt[u]);
+  }
+}
+
 // Rows [0, n) of an index chunk held one per lane in `rows` (weights in `wts`): lane group `slot` adds the
 // rows at positions slot, slot + S, ... in ascending order, U row loads in flight.  Wbase: address of this
 // lane's 16 bytes of row 0.  Rounds that lie entirely inside the chunk carry no per-lane bounds logic.
@@ -104,27 +131,13 @@ __device__ inline void gather_chunk(float* acc, uint64_t Wbase, uint32_t row_byt
 #pragma unroll
     for (int u = 0; u < U; ++u) add_row<DT, WT>(acc, v[u], wt[u]);
   }
-  for (; q < iters; q += U) {   // the tail: branch-free, positions past the end re-read n - 1 and add the identity
-    u32x4 v[U];
-    float wt[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = (q + u) * S + slot;
-      const uint32_t r = (uint32_t)__shfl((int)rows, e < n ? e : n - 1, DLRM_WAVE);
-      wt[u] = 1.0f;
-      if constexpr (WT) wt[u] = __shfl(wts, e < n ? e : n - 1, DLRM_WAVE);
-      v[u] = load16_global(Wbase + (uint64_t)r * row_bytes);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool past = (q + u) * S + slot >= n;
-      if (past) {
-        v[u] = Tab<DT>::ident();
-        wt[u] = 1.0f;   // 1 * (-0) leaves the sum alone
-      }
-      add_row<DT, WT>(acc, v[u], wt[u]);
-    }
-  }
+  // a short bag is all tail: no more loads than its rounds ask for, to within two
+  const int left = iters - q;   // <= U, the same in all lanes
+  static_assert(U == 8, "the cases below");
+  if (left > 6) gather_tail<DT, G, 8, WT>(acc, Wbase, row_bytes, rows, wts, n, slot, q);
+  else if (left > 4) gather_tail<DT, G, 6, WT>(acc, Wbase, row_bytes, rows, wts, n, slot, q);
+  else if (left > 2) gather_tail<DT, G, 4, WT>(acc, Wbase, row_bytes, rows, wts, n, slot, q);
+  else if (left > 0) gather_tail<DT, G, 2, WT>(acc, Wbase, row_bytes, rows, wts, n, slot, q);
 }
 
 template <int DT>
