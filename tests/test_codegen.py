@@ -110,6 +110,39 @@ def test_pooling_requests_the_next_indices_behind_this_round_s_rows(tmp_path):
         assert _loads_behind_rows(lines, r"global_load_dwordx4 ", index, 4), name
 
 
+def _rows_in_flight(lines, row):
+    """Of every straight piece of code with loads that match: how many there are, and how many are on their way at once."""
+    found, total, flying, most = [], 0, 0, 0
+    for t in lines + [".LBB"]:
+        if t.startswith(("s_cbranch", "s_branch", ".LBB")):
+            if total:
+                found.append((total, most))
+            total = flying = most = 0
+        elif re.match(row, t):
+            total, flying = total + 1, flying + 1
+            most = max(most, flying)
+        elif _waits_for_loads(t):   # loads return in order: a wait that leaves n on their way may be for an older one
+            flying = min(flying, int(re.search(r"vmcnt\((\d+)\)", t).group(1)))
+    return found
+
+
+def test_pooling_by_wavefronts_requests_the_rows_of_a_round_together(tmp_path):
+    """A wavefront per bag, alone or walking several: 16-bit rows of a round, of eight or of a bag's last rounds, are all requested
+    before one is waited for (64 positions are at most G rounds of 64 / G rows; rows of 64 lanes are pooled by lane groups);
+    where the compiler is left to itself, more than half of them."""
+    asm = _assembly(tmp_path, "emb_fwd.hip", [])
+    bodies = {n: b for n, b in _kernels(asm).items() if re.search(r"emb_fwd_wave(_seq)?_kernel", n)}
+    assert len(bodies) == 2 * 3 * 7 * 2 * 2   # kernels, storage types, lanes per row, weights, index types
+    for name, lines in bodies.items():
+        dtype, lanes, weighted = (int(x) for x in re.search(r"ILi(\d)ELi(\d+)ELi8ELb(\d)E", name).groups())
+        if lanes == 64:
+            continue
+        rounds = _rows_in_flight(lines, r"global_load_dwordx4 ")
+        held = dtype == 1 or (dtype == 2 and (weighted or lanes < 32))
+        assert all(total == most if held else 2 * most > total for total, most in rounds), (name, rounds)
+        assert max(total for total, _ in rounds) >= min(8, lanes), (name, rounds)
+
+
 def _occupancy(asm):
     """{kernel symbol: wavefronts per SIMD that its registers allow}"""
     found, name = {}, None
