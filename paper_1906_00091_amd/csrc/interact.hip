@@ -130,8 +130,11 @@ __global__ __launch_bounds__(kIntThreads) void interact_fwd_kernel(const float* 
 // of 16 rows at a time.  Wavefront w computes the tiles of row blocks NB - 1 - w and, where there is one, w - (2 W - NB), which
 // deals the tiles evenly (seven blocks: seven each), and the dense row's products with them; all leave together.  Bound by the
 // chain of one sample at small batches, by memory at large ones (65 rows of 128 columns, batch 16384: 4.5 of the copy's 4.6 TB/s).
-// Three wavefronts per SIMD: with what the compiler takes by itself seven and eight blocks have two, 101 rows of 64, batch 16384
-// 240.8 / 209.7 us.  Operands read from memory by each of the four instead: 377.
+// Three wavefronts per SIMD up to seven row blocks.  Eight would have 26 registers spilled by that, between the staged columns of
+// rows wider than kSplitCols; they have two.  A wavefront per sample / three to a SIMD / two, us: 128 rows of 256 columns, batch 1024 /
+// 4096 64.1 / 81.8 / 57.1, 263.5 / 284.5 / 210.5; of 96, 4096 135.7 / 147.5 / 110.5; 120 rows of 64, 16384 388 / 310 / 307; of 16, 300 /
+// 1024 / 2048 14.6 / 9.6 / 8.1, 16.5 / 17.3 / 15.2, 30.6 / 27.1 / 26.2.  Operands read from memory by each of the four wavefronts
+// instead of from LDS: 101 rows of 64, batch 16384 377 us for 209.7.
 constexpr int kSplitCols = 64;
 // words of a staged row: whole 16-column chunks, and 4 words so that the 16 rows an operand is read from fall into 64 banks
 __host__ __device__ inline int split_stride(int d) { return (d < kSplitCols ? (d + 15) & ~15 : kSplitCols) + 4; }
@@ -201,8 +204,8 @@ __device__ inline void for_share(int w, F f) {
 }
 
 template <int NB, int W>
-__global__ __launch_bounds__(W * DLRM_WAVE, 3) void interact_fwd_split_kernel(const float* __restrict__ T, float* __restrict__ R,
-                                                                            int F, int d) {
+__global__ __launch_bounds__(W * DLRM_WAVE, NB < 8 ? 3 : 2) void interact_fwd_split_kernel(const float* __restrict__ T,
+                                                                                         float* __restrict__ R, int F, int d) {
   static_assert(W <= NB && NB <= 2 * W && (W == 2 || W == 4), "one or two row blocks a wavefront");
   constexpr int NT = W * DLRM_WAVE;
   constexpr int RP = NT / 16;                       // rows staged per pass, 16 bytes a lane

@@ -143,13 +143,13 @@ def test_pooling_by_wavefronts_requests_the_rows_of_a_round_together(tmp_path):
         assert max(total for total, _ in rounds) >= min(8, lanes), (name, rounds)
 
 
-def _occupancy(asm):
-    """{kernel symbol: wavefronts per SIMD that its registers allow}"""
+def _figures(asm, which):
+    """{kernel symbol: one of the figures that the compiler states behind it}"""
     found, name = {}, None
     for line in asm.splitlines():
         m = re.match(r"(_Z\w+):", line)
         name = m.group(1) if m else name
-        m = re.match(r"; Occupancy: (\d+)", line)
+        m = re.match(r"; %s: (\d+)" % which, line)
         if m:
             found[name] = int(m.group(1))
     return found
@@ -157,9 +157,15 @@ def _occupancy(asm):
 
 def test_one_launch_forward_of_33_to_48_tables_keeps_four_wavefronts_per_simd(tmp_path):
     """Its registers are just below the limit for four; with the dense row held through the products they are above it."""
-    found = {n: o for n, o in _occupancy(_assembly(tmp_path, "pooled_interact.hip", [])).items() if "pooled_interact_fwd_kernelILi3E" in n}
+    found = {n: o for n, o in _figures(_assembly(tmp_path, "pooled_interact.hip", []), "Occupancy").items() if "pooled_interact_fwd_kernelILi3E" in n}
     assert len(found) == 3 * 2   # storage types, index types
     assert min(found.values()) >= 4, found
+
+
+def test_interaction_forward_keeps_its_tiles_in_registers(tmp_path):
+    """No row block count spills: staged rows wait in registers while the columns before them are multiplied."""
+    found = {n: v for n, v in _figures(_assembly(tmp_path, "interact.hip", []), "ScratchSize").items() if "interact_fwd" in n}
+    assert len(found) == 7 + 6 and not any(found.values()), found   # a wavefront per sample, several
 
 
 def test_sums_of_narrow_rows_read_several_pieces_of_a_run_together(tmp_path):
