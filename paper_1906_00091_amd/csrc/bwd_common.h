@@ -597,33 +597,56 @@ __device__ inline float* state_base(const UpdArgs& u, int k) {
 // ---------------------------------------------------------------------------
 int check_batch(const dlrm_sparse_batch* s);  // util.hip
 
-// Bits of the partition digit.  One workgroup reduces a bucket: `buckets` of them at least, where that leaves `least` pairs in each,
-// and 1024 pairs at most.
-inline int bits_for(int64_t nnz, int32_t K, double buckets, double least) {
+// Bits of the partition digit, 1 << bits buckets a table, one workgroup to each: the fewest bits that leave a bucket no more pairs on
+// average than a `buckets`-th of the batch, `most` where that is fewer, or 1024 where that is more.  (Bits halve a bucket: where
+// `most` decides, a bucket has between half of it and all of it.)
+inline int bits_for(int64_t nnz, int32_t K, double buckets, double most) {
   double target = (double)nnz / buckets;
-  if (target < least) target = least;
+  if (target < most) target = most;
   if (target > 1024.0) target = 1024.0;
   const double per_table = (double)nnz / (double)K;
   int tb = 0;
   while (tb < kMaxTopBits && per_table / (double)(1 << tb) > target) ++tb;
   return tb;
 }
-// Wide rows have few lane groups to a workgroup (four at 64 lanes a row), so a bucket of a given size takes them longer: more and
-// smaller buckets end together and leave hot rows less company.  A bucket of narrow rows is mostly its sort: fewer and larger
-// ones.  Update with its lookup, 1536 buckets of 128 pairs for every width / now, us: 4 tables of 164 K lookups, d = 256 441 / 436;
-// 40 skewed ones of 22 K, d = 256 281 / 237; 26 skewed one-hot ones of 8192, d = 128 162 / 150; 26 bf16 ones of 41 K, d = 64
-// 176 / 162; 13 ones of 37 K, d = 36, Adagrad 135 / 126; 100 fp16 ones of 4096, d = 32, Adagrad 135 / 129; 95 of 2900, d = 4 75 / 63;
-// 4 uniform ones of 47 K, d = 8 44 / 38.  Of 580 such batches (2^16 to 8 M lookups), mean by lanes of a row 4 and less -1.6 %,
-// 8 -0.8, 16 -0.8, 32 -1.8, 64 -5.7; uniform lookups of 100 to 120 pairs a bucket can lose (78 tables of 3700, d = 116 121 / 133).  1024
-// digits only for the widest rows or where 512 leave over 1024 pairs: every tile's counts grow with them (4 tables of 182 K lookups,
-// d = 64 72 / 77).  Small batches keep the split that a batch without a partition has (direct_reduce_kernel: every bucket reads all row
-// ids of its table, 26 x 2048 one-hot 30 / 35 us with twice the buckets), whose bits are those of the prepared call.
-inline int digit_bits(int64_t nnz, int32_t K, int lanes) {
-  if (nnz <= kSmallBatch) return bits_for(nnz, K, 1536.0, 128.0);
-  if (lanes == 64) return bits_for(nnz, K, 4096.0, 112.0);
-  if (lanes < 8) return bits_for(nnz, K, 1536.0, 224.0);
-  const int tb = bits_for(nnz, K, 2560.0, lanes == 8 ? 192.0 : lanes == 16 ? 128.0 : 112.0);
-  return tb < kMaxTopBits ? tb : bits_for(nnz, K, 1536.0, 128.0);
+// 1536 buckets of 128 pairs for every width are the rule of small batches, whose split a batch without a partition shares
+// (direct_reduce_kernel: every bucket reads all row ids of its table, 26 x 2048 one-hot 30 / 35 us with twice the buckets).
+// Otherwise:
+// Narrow rows.  A bucket is mostly its sort, so many tables (few bits) take fewer and larger ones, 70 skewed tables of 2864 lookups,
+// d = 4 51.9 / 44.6 us an update, 50 uniform ones of 3526 37.7 / 32.7; with more bits a hot row's bucket gets too long, 13 skewed
+// tables of 10540, d = 16 36.3 / 49.7.
+// Wide rows.  A workgroup has few lane groups (four at 64 lanes), so a bucket of a given size takes it longer; one bit more, two at 64
+// lanes, lets the buckets end together and leaves a hot row less company: 36 skewed tables of 20708, d = 96 186 / 149; 12
+// uniform ones of 98814, d = 128 409 / 399; 36 skewed ones of 56105, d = 132 584 / 486.  The line is the mean bucket before the
+// bit from which uniform lookups do not lose (13800 batches of 2^16 to 4 M lookups; of those with the bit uniform ones are 2 to 5 %
+// ahead by width, skewed ones 8 to 13).  It is higher
+// - for 64 digits and fewer of 32 lanes, 79 uniform tables of 3785, d = 116 124.6 / 134.0;
+// - where tables have fewer rows than lookups, which a bucket adds up in LDS, 8 uniform ones of 43048 and 1975 rows, d = 96 46.9 / 53.3;
+// - for 512 digits (1024 at 64 lanes), every tile's counts growing with them, 8 uniform ones of 53677, d = 20 43.3 / 53.6.
+inline int digit_bits(int64_t nnz, int32_t K, int lanes, int64_t max_rows) {
+  const int tb = bits_for(nnz, K, 1536.0, 128.0);
+  if (nnz <= kSmallBatch) return tb;
+  if (lanes <= 8 && tb <= 5) {
+    const int fewer = bits_for(nnz, K, 1536.0, lanes < 8 ? 224.0 : 192.0);
+    if (fewer < tb) return fewer;
+  }
+  if (lanes < 8) return tb;
+  const double per_table = (double)nnz / (double)K, full = (double)nnz / (lanes == 64 ? 4096.0 : 2560.0);
+  const bool few_rows = per_table > (double)max_rows;
+  int bits = tb;
+  for (; bits < (lanes == 64 ? kMaxTopBits : kMaxTopBits - 1); ++bits) {
+    const double mean = per_table / (double)(1 << bits);
+    double least = lanes == 64 ? 112.0 : lanes == 32 ? (bits < 6 ? 160.0 : 112.0) : lanes == 16 ? 200.0 : (bits < 6 ? 256.0 : 400.0);
+    if (few_rows && lanes < 64) least *= 1.5;
+    if (bits + 1 > (lanes == 64 ? 9 : 8) && (few_rows || lanes != 32)) least *= 2.0;
+    if (mean < least || mean <= full) break;
+  }
+  return bits;
+}
+// ... of a batch: never more than its row ids have
+inline int partition_bits(int64_t nnz, int32_t K, int32_t d, int64_t max_rows) {
+  const int tb = digit_bits(nnz, K, pow2_ceil(d / 4), max_rows), kb = ilog2_ceil(max_rows);
+  return tb < kb ? tb : kb;
 }
 
 inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLayout& L, void* ws) {
@@ -640,10 +663,7 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   g.max_huge = L.max_huge;
   g.nt_max = (int32_t)L.nt_max;
   g.tile_shift = tile_shift_for(s->nnz_total);
-  // never more digits than the row ids have
-  int tb = digit_bits(s->nnz_total, s->K, pow2_ceil(s->d / 4));
-  const int kb = ilog2_ceil(s->max_rows);
-  if (tb > kb) tb = kb;
+  const int tb = partition_bits(s->nnz_total, s->K, s->d, s->max_rows);
   g.top_bits = tb;
   // Only for slices well above a die's 4 MB of L2 (measured: the hot-row workload's 8.4 MB slices -3.5 %
   // time and -21 % fetched bytes; 0.5 MB slices +8 % time), because a die then has whole tables and tables
@@ -660,7 +680,8 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   }
   g.hist = reinterpret_cast<uint32_t*>(base + L.hist);
   g.digit_total = reinterpret_cast<uint32_t*>(base + L.keys[0]);
-  // behind the tile counts, or, with the most digits (over 2^16 lookups a table on average), in pair buffer 0
+  // behind the tile counts, or, with the most digits, in pair buffer 0: over 2^16 lookups a table on average, 4 bytes each, and at
+  // most a record of 32 bytes for 1024 of them and one a table
   const size_t counts = (((size_t)L.nt_max << tb) + 7) & ~(size_t)7;
   g.tile_rec = reinterpret_cast<TileRec*>(tb < kMaxTopBits ? base + L.hist + counts * 4 : base + L.vals[0]);
   g.bucket_start = reinterpret_cast<uint32_t*>(base + L.bucket_start);

@@ -152,3 +152,28 @@ def widen_host(a: np.ndarray, dtype: int) -> np.ndarray:
     if dtype == gen.BF16:
         return (a.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
     return a.astype(np.float64)
+
+
+def partition_bits(nnz: int, K: int, d: int, max_rows: int) -> int:
+    """The rule by which the update cuts a table into buckets, written once more: cases that are meant to have a number of
+    digits state it (test_partition_bits.py holds this to the library's own)."""
+    def fewest(most):
+        target = min(max(nnz / 1536, most), 1024)
+        return next((t for t in range(10) if nnz / K / 2 ** t <= target), 10)
+
+    lanes = 1 << max(0, (d // 4 - 1).bit_length())
+    bits = fewest(128)
+    if nnz > 65536:
+        few_tables_bits = fewest(192 if lanes == 8 else 224) if lanes <= 8 and bits <= 5 else bits
+        if few_tables_bits < bits:
+            bits = few_tables_bits
+        elif lanes >= 8:
+            few_rows = nnz / K > max_rows
+            while bits < (10 if lanes == 64 else 9):
+                least = {8: 256 if bits < 6 else 400, 16: 200, 32: 160 if bits < 6 else 112, 64: 112}[lanes]
+                least *= 1.5 if few_rows and lanes < 64 else 1
+                least *= 2 if bits >= (9 if lanes == 64 else 8) and (few_rows or lanes != 32) else 1
+                if nnz / K / 2 ** bits < least or nnz / K / 2 ** bits <= nnz / (4096 if lanes == 64 else 2560):
+                    break
+                bits += 1
+    return min(bits, (max_rows - 1).bit_length())

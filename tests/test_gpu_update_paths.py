@@ -9,7 +9,7 @@ import paper_1906_00091_amd as hot
 from oracle import oracle
 from workloads import gen
 
-from hotpath_util import DEV, SCALE_FLOOR, Compact, table_to_numpy, widen_host
+from hotpath_util import DEV, SCALE_FLOOR, Compact, partition_bits, table_to_numpy, widen_host
 from test_gpu_exact_counts import _assert_only_touched_rows_changed, _integer_dS, _integer_tables, _max_run, _pow2_weights, _run_update
 
 pytestmark = pytest.mark.gpu
@@ -22,25 +22,27 @@ def _batch(lengths, rows, seed, d=4):
     return gen.batch_from_lists(rows, bags, d=d, seed=seed)
 
 
-# name, tables, lookups of every table (in bags of about `bag`), rows: partition digits 1, 2, 4 and more; no tile, one
+# name, lookups of every table (in bags of about `bag`), rows, bits of the partition digit: 1, 2, 4 and more digits; no tile, one
 # tile and more tiles than a round of the column scan takes; more tables than lookups
 GROUPINGS = [
-    ("tables-without-lookups-between", [0, 1, 0, 1023, 1024, 1025, 0], 7, 3000),
-    ("more-tables-than-lookups", [1 if k % 7 == 0 else 0 for k in range(600)], 1, 50),
-    ("many-tables-few-digits", [(k * 37) % 300 for k in range(700)], 5, 4),
-    ("column-scan-255-256-257-tiles", [255 * 1024, 256 * 1024, 256 * 1024 + 1], 64, 1 << 20),
-    ("column-scan-ragged-tables", [700 * 1024 - 3, 5, 0, 1024], 33, 70000),
+    ("tables-without-lookups-between", [0, 1, 0, 1023, 1024, 1025, 0], 7, 3000, 2),
+    ("more-tables-than-lookups", [1 if k % 7 == 0 else 0 for k in range(600)], 1, 50, 0),
+    ("many-tables-one-digit", [(k * 37) % 300 for k in range(700)], 5, 4, 0),
+    ("many-tables-two-digits", [(k * 37) % 600 for k in range(700)], 5, 4, 1),
+    ("column-scan-255-256-257-tiles", [255 * 1024, 256 * 1024, 256 * 1024 + 1], 64, 1 << 20, 9),
+    ("column-scan-ragged-tables", [700 * 1024 - 3, 5, 0, 1024], 33, 70000, 9),
     # bag starts of a tile: 1024 of 1024 (1024 digits too), tables whose later bags are empty, 1365 of 4096
-    ("one-hot-1024-digits", [200000], 1, 5000),
-    ("one-hot-then-empty-bags", [70000, 3, 0, 69999, 1024], 1, 100000),
-    ("large-tiles-short-bags", [1200001, 5000], 3, 3000),
+    ("one-hot-1024-digits", [200000], 1, 5000, 10),
+    ("one-hot-then-empty-bags", [70000, 3, 0, 69999, 1024], 1, 100000, 8),
+    ("large-tiles-short-bags", [1200001, 5000], 3, 3000, 10),
 ]
 
 
 @pytest.mark.parametrize("case", GROUPINGS, ids=[c[0] for c in GROUPINGS])
 def test_grouping_equals_the_oracle_at_partition_edges(case):
-    name, per_table, bag, m = case
+    name, per_table, bag, m, bits = case
     print("[case] grouping " + name, flush=True)
+    assert partition_bits(sum(per_table), len(per_table), 4, m) == bits
     B = max(1, max(per_table) // bag)
     lengths = [[n // B + (1 if b < n % B else 0) for b in range(B)] for n in per_table]
     K = len(per_table)
@@ -499,7 +501,7 @@ def test_rows_split_off_oversized_buckets_fill_lds_piecewise(runs, others, dtype
 
 
 # the partition digit by the lanes of a row (4 and less, 8, 16, 32, 64) at the smallest batches it depends on: tables x lookups a
-# table on both sides of a step of every class, one table of 1024 digits, tables of fewer rows than digits
+# table, tables of fewer rows than digits among larger ones and one such table alone
 @pytest.mark.parametrize("K,per", [(8, 8194), (13, 5043), (16, 7200), (1, 120000)])
 @pytest.mark.parametrize("d", [4, 16, 28, 64, 100, 132])
 def test_partition_digits_by_row_width(K, per, d):
@@ -507,6 +509,26 @@ def test_partition_digits_by_row_width(K, per, d):
     rng = np.random.default_rng([K, d])
     B = 900
     rows = [20000 if k % 3 else 37 for k in range(K)]
+    cuts = np.sort(rng.integers(0, per + 1, size=(K, B - 1)), axis=1)
+    b = _batch([np.diff(c, prepend=0, append=per).tolist() for c in cuts], rows, seed=d, d=d)
+    for weighted in (False, True):
+        _assert_exact_update(b, gen.F32, weighted, ("sort", "prepared"))
+
+
+# the lines of that rule: tables, lookups a table, rows, columns, bits.  Both sides of a step of every class, few rows; 1024 digits
+# by narrow and by wide rows, with and without the column scan (more than 512 tiles); tables of fewer rows than digits among larger
+# ones, and alone
+@pytest.mark.parametrize("K,per,m,d,bits", [
+    (40, 3584, 20000, 4, 4), (40, 3585, 20000, 16, 5), (40, 3072, 20000, 28, 4), (40, 3073, 20000, 28, 5), (24, 4097, 20000, 28, 6),
+    (13, 5043, 20000, 64, 6), (13, 5119, 20000, 100, 6), (13, 7168, 20000, 100, 7), (8, 8194, 20000, 132, 7), (13, 7168, 7168, 100, 7),
+    (13, 7168, 7167, 100, 6), (8, 8194, 20000, 100, 7), (8, 8194, 37, 100, 6), (1, 120000, 20000, 4, 10), (1, 120000, 20000, 100, 10),
+    (1, 120000, 37, 28, 6), (4, 114688, 30000, 132, 10), (4, 114687, 30000, 132, 9), (4, 164000, 30000, 132, 10)])
+def test_partition_digits_on_either_side_of_a_line(K, per, m, d, bits):
+    print("[case] digits at a line K=%d per=%d m=%d d=%d" % (K, per, m, d), flush=True)
+    assert partition_bits(K * per, K, d, m) == bits
+    rng = np.random.default_rng([K, d])
+    B = 900
+    rows = [37 if k % 3 == 1 else m for k in range(K)]
     cuts = np.sort(rng.integers(0, per + 1, size=(K, B - 1)), axis=1)
     b = _batch([np.diff(c, prepend=0, append=per).tolist() for c in cuts], rows, seed=d, d=d)
     for weighted in (False, True):
