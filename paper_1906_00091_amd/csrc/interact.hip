@@ -608,13 +608,16 @@ static int pair_stride(int F) {
 }
 
 // Forward of three and more row blocks: a wavefront per sample / W of them, us.  Small batches, whose SIMDs have one wavefront or
-// none, 101 rows of 32 columns, batch 32 / 512 / 1024: 13.3 / 14.9 / 17.2 and 5.5 / 8.2 / 13.5.  Large ones where staging pays, batch
-// 16384: 65 rows of 128 columns 173.5 / 151.5, 66 of 64 124 / 119, 97 of 32 143.7 / 136.7, 113 of 32 247 / 167, 113 of 8 179 / 143.  Where the lines
+// none, 101 rows of 32 columns, batch 32 / 512 / 1024: 13.3 / 14.9 / 17.2 and 5.5 / 8.2 / 13.5.  From 102 rows on the pairs of four samples
+// take more than half of a compute unit's 160 KB of LDS, which leaves it one workgroup of the other kernel: 102 rows of 16, batch 4096
+// 45.1 / 32.4, 113 of 8, 2048 / 16384 24.9 / 19.6, 178.1 / 145.7, 113 of 32, 16384 247 / 167; 101 of 8, 2048 17.0 / 18.3.  Large batches
+// where staging pays, 16384: 65 rows of 128 columns 173.5 / 151.5, 66 of 64 124 / 119, 97 of 32 143.7 / 136.7.  Where the other lines
 // lie: 81 rows of 8 columns, batch 1024 / 2048 8.7 / 7.4, 10.9 / 12.0; 49 rows of 8, 512 / 1024 4.8 / 4.4, 4.8 / 5.1; 66 of 32, 4096 /
 // 16384 25.1 / 22.8, 81.5 / 89.0; 34 of 32, 1024 / 4096 4.9 / 4.7, 10.0 / 11.5, of 64, 2048 / 16384 9.6 / 8.7, 49.3 / 49.8; 50 of 64, 2048 / 8192
-// 15.1 / 16.1, 46.9 / 45.5, of 128, 2048 / 4096 23.5 / 24.7, 43.9 / 40.1.
-static bool split_fwd(int nb, int B, int d) {
-  if (B <= 512) return true;
+// 15.1 / 16.1, 46.9 / 45.5, of 128, 2048 / 4096 23.5 / 24.7, 43.9 / 40.1; 90 of 32, 1100 / 2048 / 4096 16.2 / 12.5, 17.9 / 19.5,
+// 34.9 / 33.5 (2048 wavefronts are two a SIMD, all that fit of the other kernel).
+static bool split_fwd(int F, int nb, int B, int d) {
+  if (B <= 512 || kIntWaves * pair_stride(F) * 4 > 80 * 1024) return true;
   if (d < 32) return nb >= 5 && B <= 1024;
   if (nb >= 6 || B <= 1024) return true;
   if (nb == 5) return d >= 64 || B <= 4096;
@@ -640,7 +643,7 @@ template <int NB>
 static int launch_fwd(const float* T, float* R, int B, int F, int d, hipStream_t st) {
   static_assert(NB <= 7, "eight row blocks always take the split kernel");
   if constexpr (NB > 2) {
-    if (split_fwd(NB, B, d)) return launch_fwd_split<NB>(T, R, B, F, d, st);
+    if (split_fwd(F, NB, B, d)) return launch_fwd_split<NB>(T, R, B, F, d, st);
   }
   const int pstride = pair_stride(F);
   const size_t lds = (size_t)kIntWaves * pstride * 4;

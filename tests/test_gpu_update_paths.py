@@ -377,8 +377,8 @@ def test_updates_of_rows_that_share_sectors(dtype, d):
 # row blocks, columns and batches on either side of where the forward takes W wavefronts a sample; the last sample of the large
 # batch alone in a call of its own too
 @pytest.mark.parametrize("F,d,B", [(34, 28, 513), (34, 60, 1025), (49, 64, 1025), (50, 32, 1025), (50, 64, 8191), (65, 132, 4095),
-                                   (66, 4, 1025), (66, 36, 4097), (81, 64, 4097), (90, 28, 1025), (101, 32, 1025), (113, 20, 1025),
-                                   (114, 68, 513), (128, 256, 600)])
+                                   (66, 4, 1025), (66, 36, 4097), (81, 64, 4097), (90, 28, 1025), (101, 20, 1025), (101, 32, 1025),
+                                   (102, 20, 1025), (113, 4, 2049), (113, 20, 1025), (114, 68, 513), (128, 256, 600)])
 def test_interaction_forward_gives_the_same_bits_at_any_batch_size(F, d, B):
     print("[case] interaction forward F=%d d=%d B=%d" % (F, d, B), flush=True)
     g = torch.Generator(device=DEV).manual_seed(F)
