@@ -396,6 +396,26 @@ def test_interaction_forward_gives_the_same_bits_at_any_batch_size(F, d, B):
     assert np.max(np.abs(R[-2:].cpu().numpy() - ref) / np.maximum(scale, 1e-30)) <= d * 2.0 ** -24   # fp32 sums of d terms
 
 
+def test_interaction_forward_beyond_one_launch():
+    """2^23 samples and more of 34 rows, a workgroup each: as many as one launch is given.  The samples repeat, so the results must
+    too."""
+    print("[case] interaction forward F=34 B=2^23+64", flush=True)
+    F, d, n = 34, 64, 64
+    m, B = d + F * (F - 1) // 2, (1 << 23) + n
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < B * (F * d + m) * 4 + (8 << 30):
+        pytest.skip("needs 102 GB of device memory")
+    g = torch.Generator(device=DEV).manual_seed(F)
+    T, R, want = torch.empty((B, F, d), device=DEV), torch.full((B, m), -5.0, device=DEV), torch.empty((n, m), device=DEV)
+    T.view(-1, n, F, d).copy_(torch.randn((n, F, d), generator=g, device=DEV).expand(B // n, n, F, d))
+    hot.dlrm_interact_dot_fwd(T[:n], want)
+    hot.dlrm_interact_dot_fwd(T, R)
+    for part in R.view(-1, n, m).split(1 << 14):
+        assert (part == want).all()
+    del T, R, part
+    torch.cuda.empty_cache()
+
+
 # two to five row blocks on either side of the batch size up to which wavefronts share a sample; rows of dR at
 # every alignment (d + P odd) and at one
 @pytest.mark.parametrize("F,d,below", [(18, 20, 1024), (33, 128, 1024), (34, 36, 1024), (50, 72, 1024), (65, 16, 1024),
