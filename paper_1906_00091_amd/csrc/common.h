@@ -153,6 +153,35 @@ __device__ inline void store8_stream(void* p, u32x2 v) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(p));
 }
 __device__ inline void storef4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
+// CW consecutive floats (CW = 1, 2 or 4, address CW*4-byte aligned) <-> registers; zeros if !ok
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+template <int CW>
+__device__ inline void load_cols(const float* p, bool ok, float* out) {
+  if constexpr (CW == 4) {
+    const f32x4 v = loadf4(p);
+    out[0] = ok ? v.x : 0.0f;
+    out[1] = ok ? v.y : 0.0f;
+    out[2] = ok ? v.z : 0.0f;
+    out[3] = ok ? v.w : 0.0f;
+  } else if constexpr (CW == 1) {
+    const float v = *p;
+    out[0] = ok ? v : 0.0f;
+  } else {
+    const f32x2 v = *reinterpret_cast<const f32x2*>(p);
+    out[0] = ok ? v.x : 0.0f;
+    out[1] = ok ? v.y : 0.0f;
+  }
+}
+template <int CW>
+__device__ inline void store_cols(float* p, const float* v) {
+  if constexpr (CW == 4) {
+    storef4(p, f32x4{v[0], v[1], v[2], v[3]});
+  } else if constexpr (CW == 1) {
+    *p = v[0];
+  } else {
+    *reinterpret_cast<f32x2*>(p) = f32x2{v[0], v[1]};
+  }
+}
 
 // The first thread of a launch tells a polling host that the launch has begun (and so, by stream
 // order, that everything enqueued before it on its stream is done): a system-scope store that

@@ -3,9 +3,12 @@
 //   bwd: dT[b,i,:] = sum_{j != i} g(i,j) T[b,j,:]  (+ dR[b,0:d] on row 0),
 //        g(i,j) = dR[b, d + pair(max(i,j), min(i,j))]
 // Both are small dense contractions per sample (Z = T T^t, dT = G T with G symmetric), run on
-// the matrix cores in fp32: v_mfma_f32_16x16x4_f32, one wavefront per sample, operands loaded
+// the matrix cores in fp32: v_mfma_f32_16x16x4_f32.  A wavefront per sample loads its operands
 // straight from global memory into the register layout the instruction wants (no LDS staging
-// of T, no workgroup barriers), so HBM sees each input and output once.
+// of T, no workgroup barriers), so HBM sees each input and output once.  A workgroup per sample
+// takes over where one wavefront is a long chain or too few fit a compute unit: the forward from
+// three row blocks on stages T in LDS (interact_fwd_split_kernel, split_fwd), the backward lays
+// out G there (interact_bwd_tiled_kernel, kSplitBelow); both with barriers and with the same bits.
 //   16x16x4 layout: lane l supplies A[m = l%16][k = l/16] and B[k = l/16][n = l%16] and holds
 //   D[m = 4*(l/16) + v][n = l%16] in element v of its accumulator.
 // The contraction index may be visited in any order as long as A and B agree on it, which is
@@ -141,7 +144,8 @@ __host__ __device__ inline int split_stride(int d) { return (d < kSplitCols ? (d
 template <int NB, int W>
 constexpr int kSplitTiles = NB > 2 * NB - 2 * W + 1 ? NB : 2 * NB - 2 * W + 1;   // of a wavefront, at most
 
-// Wavefront w's tiles, one after the other: of row block I1, then of row block I0.  LO: the lane's place in the first staged row.
+// Wavefront w's tiles, one after the other: of row block I1, then of row block I0.  lo: the lane's place in the first staged
+// embedding row.
 template <int NB, int W, int w>
 struct SplitShare {
   static constexpr int I1 = NB - 1 - w, I0 = w - (2 * W - NB), N1 = I1 + 1, N0 = I0 < 0 ? 0 : I0 + 1;
@@ -268,42 +272,12 @@ __global__ __launch_bounds__(W * DLRM_WAVE, NB < 8 ? 3 : 2) void interact_fwd_sp
   }
 }
 
-// CW consecutive floats (CW = 1, 2 or 4, address CW*4-byte aligned) <-> registers; zeros if !ok
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-template <int CW>
-__device__ inline void load_cols(const float* p, bool ok, float* out) {
-  if constexpr (CW == 4) {
-    const f32x4 v = loadf4(p);
-    out[0] = ok ? v.x : 0.0f;
-    out[1] = ok ? v.y : 0.0f;
-    out[2] = ok ? v.z : 0.0f;
-    out[3] = ok ? v.w : 0.0f;
-  } else if constexpr (CW == 1) {
-    const float v = *p;
-    out[0] = ok ? v : 0.0f;
-  } else {
-    const f32x2 v = *reinterpret_cast<const f32x2*>(p);
-    out[0] = ok ? v.x : 0.0f;
-    out[1] = ok ? v.y : 0.0f;
-  }
-}
-template <int CW>
-__device__ inline void store_cols(float* p, const float* v) {
-  if constexpr (CW == 4) {
-    storef4(p, f32x4{v[0], v[1], v[2], v[3]});
-  } else if constexpr (CW == 1) {
-    *p = v[0];
-  } else {
-    *reinterpret_cast<f32x2*>(p) = f32x2{v[0], v[1]};
-  }
-}
-
 // --- backward -------------------------------------------------------------------------------
 // dT_b = G T_b with G the symmetric F x F matrix of pair gradients (zero diagonal), held per
 // wavefront in LDS as the lower triangle exactly as dR stores it.  For the K embedding rows,
 // row block ib of G is the A operand (lane: embedding row 16*ib + l%16, column 4s + l/16 in
 // step s); the B operand of step s is embedding row 4s + l/16, of which lane x = l%16 fetches
-// CW = 4 (or 2) floats at columns 16*CW*g + CW*x: element u of them belongs to the output tile
+// CW = 4, 2 or 1 floats at columns 16*CW*g + CW*x: element u of them belongs to the output tile
 // whose 16 columns are {16*CW*g + CW*x' + u}, so that after the contraction every lane owns CW
 // consecutive columns of 4 rows and stores them as one vector.  The dense row enters and leaves through plain FMAs: a rank-1
 // update of every tile, and one matrix-vector product for its own gradient.

@@ -274,36 +274,6 @@ static int dispatch_it(const PiArgs& a, bool idx32, hipStream_t st) {
   return idx32 ? dispatch_nb<DT, int32_t>(a, st) : dispatch_nb<DT, int64_t>(a, st);
 }
 
-// CW consecutive floats (CW = 1, 2 or 4, address CW*4-byte aligned) <-> registers; zeros if !ok
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-template <int CW>
-__device__ inline void load_cols(const float* p, bool ok, float* out) {
-  if constexpr (CW == 4) {
-    const f32x4 v = loadf4(p);
-    out[0] = ok ? v.x : 0.0f;
-    out[1] = ok ? v.y : 0.0f;
-    out[2] = ok ? v.z : 0.0f;
-    out[3] = ok ? v.w : 0.0f;
-  } else if constexpr (CW == 1) {
-    const float v = *p;
-    out[0] = ok ? v : 0.0f;
-  } else {
-    const f32x2 v = *reinterpret_cast<const f32x2*>(p);
-    out[0] = ok ? v.x : 0.0f;
-    out[1] = ok ? v.y : 0.0f;
-  }
-}
-template <int CW>
-__device__ inline void store_cols(float* p, const float* v) {
-  if constexpr (CW == 4) {
-    storef4(p, f32x4{v[0], v[1], v[2], v[3]});
-  } else if constexpr (CW == 1) {
-    *p = v[0];
-  } else {
-    *reinterpret_cast<f32x2*>(p) = f32x2{v[0], v[1]};
-  }
-}
-
 // --- backward without T ---------------------------------------------------------------------
 // dT_b = G T_b as in interact_bwd_kernel (interact.hip: same operand layout, same instructions in the
 // same order), but the rows of T_b are not read from memory: the B operand of contraction step s,
@@ -526,8 +496,9 @@ static int launch_pb_cols(const PbArgs& a, hipStream_t st) {
   return DLRM_OK;
 }
 
-// Columns per lane as in interact_bwd_kernel (4 up to two row blocks, else 2), with 1 and 2 for narrow rows: 27 rows of 16 fp32 columns,
-// one row a bag, batch 4096 / 16384 14.3 / 10.3, 43.9 / 31.3 us; 65 rows of 16 41.6 / 31.7, 156.4 / 99.7; 27 rows of 32 15.4 / 12.9, 45.6 / 39.8.
+// Columns per lane: 4 up to two row blocks (interact_bwd_kernel up to four; the rows gathered here take registers of their own), else
+// 2, with 1 and 2 for narrow rows as there: 27 rows of 16 fp32 columns, one row a bag, batch 4096 / 16384 14.3 / 10.3, 43.9 / 31.3 us;
+// 65 rows of 16 41.6 / 31.7, 156.4 / 99.7; 27 rows of 32 15.4 / 12.9, 45.6 / 39.8.
 template <int NB, int DT, typename IT>
 static int launch_pb(const PbArgs& a, hipStream_t st) {
   if (a.d <= 16) return launch_pb_cols<NB, DT, 1, IT>(a, st);
