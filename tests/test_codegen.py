@@ -143,6 +143,11 @@ def test_pooling_by_wavefronts_requests_the_rows_of_a_round_together(tmp_path):
         assert max(total for total, _ in rounds) >= min(8, lanes), (name, rounds)
 
 
+def _occupancy(asm):
+    """{kernel symbol: wavefronts per SIMD that its registers allow}"""
+    return _figures(asm, "Occupancy")
+
+
 def _figures(asm, which):
     """{kernel symbol: one of the figures that the compiler states behind it}"""
     found, name = {}, None
@@ -157,7 +162,7 @@ def _figures(asm, which):
 
 def test_one_launch_forward_of_33_to_48_tables_keeps_four_wavefronts_per_simd(tmp_path):
     """Its registers are just below the limit for four; with the dense row held through the products they are above it."""
-    found = {n: o for n, o in _figures(_assembly(tmp_path, "pooled_interact.hip", []), "Occupancy").items() if "pooled_interact_fwd_kernelILi3E" in n}
+    found = {n: o for n, o in _occupancy(_assembly(tmp_path, "pooled_interact.hip", [])).items() if "pooled_interact_fwd_kernelILi3E" in n}
     assert len(found) == 3 * 2   # storage types, index types
     assert min(found.values()) >= 4, found
 

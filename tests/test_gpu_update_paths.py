@@ -22,27 +22,25 @@ def _batch(lengths, rows, seed, d=4):
     return gen.batch_from_lists(rows, bags, d=d, seed=seed)
 
 
-# name, lookups of every table (in bags of about `bag`), rows, bits of the partition digit: 1, 2, 4 and more digits; no tile, one
+# name, lookups of every table (in bags of about `bag`), rows: partition digits 1, 4 and more (2: see below); no tile, one
 # tile and more tiles than a round of the column scan takes; more tables than lookups
 GROUPINGS = [
-    ("tables-without-lookups-between", [0, 1, 0, 1023, 1024, 1025, 0], 7, 3000, 2),
-    ("more-tables-than-lookups", [1 if k % 7 == 0 else 0 for k in range(600)], 1, 50, 0),
-    ("many-tables-one-digit", [(k * 37) % 300 for k in range(700)], 5, 4, 0),
-    ("many-tables-two-digits", [(k * 37) % 600 for k in range(700)], 5, 4, 1),
-    ("column-scan-255-256-257-tiles", [255 * 1024, 256 * 1024, 256 * 1024 + 1], 64, 1 << 20, 9),
-    ("column-scan-ragged-tables", [700 * 1024 - 3, 5, 0, 1024], 33, 70000, 9),
+    ("tables-without-lookups-between", [0, 1, 0, 1023, 1024, 1025, 0], 7, 3000),
+    ("more-tables-than-lookups", [1 if k % 7 == 0 else 0 for k in range(600)], 1, 50),
+    ("many-tables-few-digits", [(k * 37) % 300 for k in range(700)], 5, 4),
+    ("column-scan-255-256-257-tiles", [255 * 1024, 256 * 1024, 256 * 1024 + 1], 64, 1 << 20),
+    ("column-scan-ragged-tables", [700 * 1024 - 3, 5, 0, 1024], 33, 70000),
     # bag starts of a tile: 1024 of 1024 (1024 digits too), tables whose later bags are empty, 1365 of 4096
-    ("one-hot-1024-digits", [200000], 1, 5000, 10),
-    ("one-hot-then-empty-bags", [70000, 3, 0, 69999, 1024], 1, 100000, 8),
-    ("large-tiles-short-bags", [1200001, 5000], 3, 3000, 10),
+    ("one-hot-1024-digits", [200000], 1, 5000),
+    ("one-hot-then-empty-bags", [70000, 3, 0, 69999, 1024], 1, 100000),
+    ("large-tiles-short-bags", [1200001, 5000], 3, 3000),
 ]
 
 
 @pytest.mark.parametrize("case", GROUPINGS, ids=[c[0] for c in GROUPINGS])
 def test_grouping_equals_the_oracle_at_partition_edges(case):
-    name, per_table, bag, m, bits = case
+    name, per_table, bag, m = case
     print("[case] grouping " + name, flush=True)
-    assert partition_bits(sum(per_table), len(per_table), 4, m) == bits
     B = max(1, max(per_table) // bag)
     lengths = [[n // B + (1 if b < n % B else 0) for b in range(B)] for n in per_table]
     K = len(per_table)
@@ -63,6 +61,23 @@ def test_grouping_equals_the_oracle_at_partition_edges(case):
         assert int(nu[k]) == len(wu)
         assert np.array_equal(uniq[a0:a0 + len(wu)], wu) and np.array_equal(seg[a0:a0 + len(wu)], wseg)
         assert np.array_equal(sbag[a0:a1], wbag)
+
+
+# the bits of the partition digit that those cases have, and one of two digits, which no case above has any more
+GROUPING_BITS = {"tables-without-lookups-between": 2, "more-tables-than-lookups": 0, "many-tables-few-digits": 0,
+                 "column-scan-255-256-257-tiles": 9, "column-scan-ragged-tables": 9, "one-hot-1024-digits": 10,
+                 "one-hot-then-empty-bags": 8, "large-tiles-short-bags": 10}
+
+
+def test_groupings_cover_the_partition_digits():
+    for name, per_table, _, m in GROUPINGS:
+        assert partition_bits(sum(per_table), len(per_table), 4, m) == GROUPING_BITS[name], name
+
+
+def test_grouping_of_many_tables_with_two_digits_equals_the_oracle():
+    per_table = [(k * 37) % 600 for k in range(700)]
+    assert partition_bits(sum(per_table), 700, 4, 4) == 1
+    test_grouping_equals_the_oracle_at_partition_edges(("many-tables-two-digits", per_table, 5, 4))
 
 
 # around the limits of the one-launch form (65536 lengths, 4096 tables), a scan round (4096 bags) and a wavefront
@@ -377,8 +392,8 @@ def test_updates_of_rows_that_share_sectors(dtype, d):
 # row blocks, columns and batches on either side of where the forward takes W wavefronts a sample; the last sample of the large
 # batch alone in a call of its own too
 @pytest.mark.parametrize("F,d,B", [(34, 28, 513), (34, 60, 1025), (49, 64, 1025), (50, 32, 1025), (50, 64, 8191), (65, 132, 4095),
-                                   (66, 4, 1025), (66, 36, 4097), (81, 64, 4097), (90, 28, 1025), (101, 20, 1025), (101, 32, 1025),
-                                   (102, 20, 1025), (113, 4, 2049), (113, 20, 1025), (114, 68, 513), (128, 256, 600)])
+                                   (66, 4, 1025), (66, 36, 4097), (81, 64, 4097), (90, 28, 1025), (101, 32, 1025), (113, 20, 1025),
+                                   (114, 68, 513), (128, 256, 600)])
 def test_interaction_forward_gives_the_same_bits_at_any_batch_size(F, d, B):
     print("[case] interaction forward F=%d d=%d B=%d" % (F, d, B), flush=True)
     g = torch.Generator(device=DEV).manual_seed(F)
@@ -394,6 +409,12 @@ def test_interaction_forward_gives_the_same_bits_at_any_batch_size(F, d, B):
     ref = oracle.interact_dot_fwd(T[-2:].cpu().numpy())
     scale = oracle.interact_dot_fwd(T[-2:].abs().cpu().numpy())
     assert np.max(np.abs(R[-2:].cpu().numpy() - ref) / np.maximum(scale, 1e-30)) <= d * 2.0 ** -24   # fp32 sums of d terms
+
+
+# ... and from 102 rows on, where it takes them for every batch
+@pytest.mark.parametrize("F,d,B", [(101, 20, 1025), (102, 20, 1025), (113, 4, 2049)])
+def test_interaction_forward_of_102_rows_and_more_gives_the_same_bits(F, d, B):
+    test_interaction_forward_gives_the_same_bits_at_any_batch_size(F, d, B)
 
 
 def test_interaction_forward_beyond_one_launch():
