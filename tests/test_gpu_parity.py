@@ -3,12 +3,14 @@ inputs.  Integer / index work must match bit for bit; floating point within
 1e-5 (fp32 tables) or 1e-2 (fp16/bf16 tables) max error relative to the magnitude
 of the sum that produced the element, sum_j |term_j| (the oracle run on absolute
 values; equal to |reference| where nothing cancels)."""
+import threading
+
 import numpy as np
 import pytest
 import torch
 
 import paper_1906_00091_amd as hot
-from paper_1906_00091_amd import ceilings
+from paper_1906_00091_amd import binding, ceilings
 from oracle import oracle
 from workloads import gen
 
@@ -500,6 +502,30 @@ def test_prepare_on_a_second_stream_then_update_gives_the_same_bits(case):
     torch.cuda.synchronize()
     for k in range(K):
         assert torch.equal(one[k].view(torch.uint8), two[k].view(torch.uint8))
+
+
+
+def test_calls_go_to_torch_s_current_stream():
+    """The handle that calls are enqueued on is that of torch's current stream: the default one, one entered, one set, and another
+    thread's own."""
+    def same():
+        return binding._stream() == torch.cuda.current_stream().cuda_stream
+
+    handles = [binding._stream()]
+    assert same()
+    sides = [torch.cuda.Stream() for _ in range(2)]
+    with torch.cuda.stream(sides[0]):
+        assert same()
+        handles.append(binding._stream())
+        other = []
+        worker = threading.Thread(target=lambda: other.extend([same(), binding._stream()]))
+        worker.start()
+        worker.join()
+        assert other == [True, handles[0]]
+        torch.cuda.set_stream(sides[1])
+        assert same()
+        handles.append(binding._stream())
+    assert same() and binding._stream() == handles[0] and len(set(handles)) == 3
 
 
 FLAT_CASES = [
