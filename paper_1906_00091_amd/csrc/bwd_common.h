@@ -612,9 +612,11 @@ inline int bits_for(int64_t nnz, int32_t K, double buckets, double most) {
 // 1536 buckets of 128 pairs for every width are the rule of small batches, whose split a batch without a partition shares
 // (direct_reduce_kernel: every bucket reads all row ids of its table, 26 x 2048 one-hot 30 / 35 us with twice the buckets).
 // Otherwise:
-// Narrow rows.  A bucket is mostly its sort, so many tables (few bits) take fewer and larger ones, 70 skewed tables of 2864 lookups,
-// d = 4 51.9 / 44.6 us an update, 50 uniform ones of 3526 37.7 / 32.7; with more bits a hot row's bucket gets too long, 13 skewed
-// tables of 10540, d = 16 36.3 / 49.7.
+// Narrow rows.  A bucket is mostly its sort, so fewer and larger ones take less, 70 skewed tables of 2864 lookups, d = 4 51.9 / 44.6
+// us an update, 50 uniform ones of 3526 37.7 / 32.7; but a hot row's bucket outgrows the LDS sort sooner, 13 skewed tables of
+// 10540, d = 16 36.3 / 49.7.  They are taken where neither uniform nor skewed lookups lose on average (4800 batches, mean of the
+// update uniform / skewed, by the bits of 128 pairs): up to 4 lanes 6 bits -12 / -9 %, 7 -9 / -1, 10 -17 / -1; 8 lanes 6 -9 / -5,
+// 10 -13 / -2.  Not 4 lanes 8 and 9 -11 / +4, -13 / +4 (one skewed one in five over 10 % behind); 8 lanes 7 -7 / +5, 8 -8 / +5.
 // Wide rows.  A workgroup has few lane groups (four at 64 lanes), so a bucket of a given size takes it longer; one bit more, two at 64
 // lanes, lets the buckets end together and leaves a hot row less company: 36 skewed tables of 20708, d = 96 186 / 149; 12
 // uniform ones of 98814, d = 128 409 / 399; 36 skewed ones of 56105, d = 132 584 / 486.  The line is the mean bucket before the
@@ -622,11 +624,12 @@ inline int bits_for(int64_t nnz, int32_t K, double buckets, double most) {
 // ahead by width, skewed ones 8 to 13).  It is higher
 // - for 64 digits and fewer of 32 lanes, 79 uniform tables of 3785, d = 116 124.6 / 134.0;
 // - where tables have fewer rows than lookups, which a bucket adds up in LDS, 8 uniform ones of 43048 and 1975 rows, d = 96 46.9 / 53.3;
-// - for 512 digits (1024 at 64 lanes), every tile's counts growing with them, 8 uniform ones of 53677, d = 20 43.3 / 53.6.
+// - for 512 digits (1024 at 64 lanes), every tile's counts growing with them, 8 uniform ones of 53677, d = 20 43.3 / 53.6; with more
+//   rows than lookups 32 and 64 lanes do not lose by them (64 lanes, 310 batches 1024 digits / 512, uniform -1 %, skewed -4).
 inline int digit_bits(int64_t nnz, int32_t K, int lanes, int64_t max_rows) {
   const int tb = bits_for(nnz, K, 1536.0, 128.0);
   if (nnz <= kSmallBatch) return tb;
-  if (lanes <= 8 && tb <= 5) {
+  if (lanes <= 8 && (tb <= (lanes < 8 ? 7 : 6) || tb == kMaxTopBits)) {
     const int fewer = bits_for(nnz, K, 1536.0, lanes < 8 ? 224.0 : 192.0);
     if (fewer < tb) return fewer;
   }
@@ -638,7 +641,7 @@ inline int digit_bits(int64_t nnz, int32_t K, int lanes, int64_t max_rows) {
     const double mean = per_table / (double)(1 << bits);
     double least = lanes == 64 ? 112.0 : lanes == 32 ? (bits < 6 ? 160.0 : 112.0) : lanes == 16 ? 200.0 : (bits < 6 ? 256.0 : 400.0);
     if (few_rows && lanes < 64) least *= 1.5;
-    if (bits + 1 > (lanes == 64 ? 9 : 8) && (few_rows || lanes != 32)) least *= 2.0;
+    if (bits + 1 > (lanes == 64 ? 9 : 8) && (few_rows || lanes < 32)) least *= 2.0;
     if (mean < least || mean <= full) break;
   }
   return bits;
@@ -680,7 +683,7 @@ inline void fill_group_args(GroupArgs& g, const dlrm_sparse_batch* s, const WsLa
   }
   g.hist = reinterpret_cast<uint32_t*>(base + L.hist);
   g.digit_total = reinterpret_cast<uint32_t*>(base + L.keys[0]);
-  // behind the tile counts, or, with the most digits, in pair buffer 0: over 2^16 lookups a table on average, 4 bytes each, and at
+  // behind the tile counts, or, with the most digits, in pair buffer 0: 57344 lookups a table on average or more, 4 bytes each, and at
   // most a record of 32 bytes for 1024 of them and one a table
   const size_t counts = (((size_t)L.nt_max << tb) + 7) & ~(size_t)7;
   g.tile_rec = reinterpret_cast<TileRec*>(tb < kMaxTopBits ? base + L.hist + counts * 4 : base + L.vals[0]);

@@ -41,9 +41,10 @@ def library_bits(tmp_path_factory):
 @pytest.mark.parametrize("batch,bits", [
     # small batches: buckets of 128 pairs whatever the width
     ((2048, 32, 256, 10 ** 6), 4), ((2048, 32, 4, 10 ** 6), 4), ((65536, 1, 64, 10 ** 6), 9),
-    # narrow rows: of 224 (192 at eight lanes) where buckets of 128 take five bits or fewer
+    # narrow rows: of 224 (192 at eight lanes) where buckets of 128 take seven bits (six) or fewer, or ten
     ((224 * 16, 40, 16, 10 ** 6), 4), ((224 * 16 + 1, 40, 16, 10 ** 6), 5), ((112 * 32, 40, 20, 10 ** 6), 5), ((96 * 32, 40, 20, 10 ** 6), 4),
-    ((128 * 32, 24, 16, 10 ** 6), 5), ((128 * 32 + 1, 24, 16, 10 ** 6), 6), ((128 * 32 + 1, 24, 20, 10 ** 6), 6),
+    ((128 * 64, 12, 20, 10 ** 6), 6), ((128 * 64 + 1, 12, 20, 10 ** 6), 7), ((128 * 128, 6, 16, 10 ** 6), 7), ((128 * 128 + 1, 6, 16, 10 ** 6), 8),
+    ((128 * 512, 2, 16, 10 ** 6), 9), ((128 * 512 + 1, 2, 16, 10 ** 6), 9), ((224 * 512 + 1, 1, 16, 10 ** 6), 10), ((192 * 512, 1, 20, 10 ** 6), 9), ((192 * 512 + 1, 1, 20, 10 ** 6), 10),
     # wide rows: a bit more from a mean bucket on
     ((256 * 16 - 1, 100, 32, 10 ** 6), 4), ((256 * 16, 100, 32, 10 ** 6), 5), ((400 * 64 - 1, 25, 32, 10 ** 6), 6), ((400 * 64, 25, 32, 10 ** 6), 7),
     ((200 * 64 - 1, 26, 64, 10 ** 6), 6), ((200 * 64, 26, 64, 10 ** 6), 7),
@@ -54,7 +55,7 @@ def library_bits(tmp_path_factory):
     ((8192, 26, 256, 8191), 7),
     # 512 digits and 1024
     ((112 * 256, 6, 128, 10 ** 6), 9), ((400 * 256 - 1, 6, 64, 10 ** 6), 8), ((400 * 256, 6, 64, 10 ** 6), 9), ((336 * 256 - 1, 6, 128, 80000), 8),
-    ((336 * 256, 6, 128, 80000), 9), ((224 * 512 - 1, 4, 256, 10 ** 6), 9), ((224 * 512, 4, 256, 10 ** 6), 10), ((224 * 512, 4, 128, 10 ** 6), 9),
+    ((336 * 256, 6, 128, 80000), 9), ((112 * 512 - 1, 4, 256, 10 ** 6), 9), ((112 * 512, 4, 256, 10 ** 6), 10), ((224 * 512 - 1, 4, 256, 80000), 9), ((224 * 512, 4, 256, 80000), 10), ((224 * 512, 4, 128, 10 ** 6), 9),
     # never more buckets than the batch fills, never more bits than the row ids have
     ((524288, 64, 128, 10 ** 6), 9), ((120000, 1, 4, 20000), 10), ((120000, 1, 132, 1024), 10), ((120000, 1, 132, 1023), 10), ((120000, 1, 4, 512), 9),
     ((120000, 1, 4, 37), 6), ((120000, 1, 4, 1), 0)])
