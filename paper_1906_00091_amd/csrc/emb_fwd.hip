@@ -85,11 +85,14 @@ __device__ inline void add_row(float* acc, u32x4 v, float w) {
 // with weights or of few lanes.  Pooling of bags of 1..200 rows, a wavefront per bag, without / with it, us: 8 tables of 1M rows,
 // batch 2048, fp16 rows of 64, 128, 256 columns 41.7 / 38.8, 90.5 / 77.3, 184.5 / 162.2, bf16 rows of 128 with weights 99.6 / 78.2;
 // 26 tables of 1000 fp16 rows of 128 with weights, batch 500 35.5 / 23.0.  The other kernels request most rows of a round together
-// as they are, in an order that takes more registers: fewer wavefronts, fewer tables in the L2 at a time.  Bags of 1..300 of 26
-// tables of 1000 rows, batch 500, fp32 rows of 128 columns 55.9 / 68.8, bf16 ones of 256 59.1 / 67.6.
-template <int DT, int G, bool WT>
+// as they are, in an order that takes more registers: fewer wavefronts, fewer tables in the L2 at a time.  bf16 rows of 32 lanes
+// take longer that way where a SIMD has one wavefront or two anyway, 13 tables of 3186 rows of 208 columns, batch 21, bags of 272
+// 18.0 / 14.8, 14 of 2170 rows of 184, 347, 199 43.0 / 38.2, and less where many share the L2, 31 tables of 997 rows of 216, 303, 1..231
+// 46.3 / 51.0; of 1500 such batches -4 %.  fp32 rows are left alone: 1850 batches +3 %, 26 tables of 1000 rows of 128 columns, batch
+// 500, bags of 1..300 55.9 / 68.8.
+template <int DT>
 __device__ inline void rows_requested() {
-  if constexpr (DT == DLRM_F16 || (DT == DLRM_BF16 && (WT || G < 32))) __builtin_amdgcn_sched_barrier(0);
+  if constexpr (DT != DLRM_F32) __builtin_amdgcn_sched_barrier(0);
 }
 
 // The last rounds of a chunk, up to U of them, with U row loads in flight and no branch: positions past the end re-read n - 1 and
@@ -108,7 +111,7 @@ __device__ inline void gather_tail(float* acc, uint64_t Wbase, uint32_t row_byte
     if constexpr (WT) wt[u] = __shfl(wts, e < n ? e : n - 1, DLRM_WAVE);
     v[u] = load16_global(Wbase + (uint64_t)r * row_bytes);
   }
-  rows_requested<DT, G, WT>();
+  rows_requested<DT>();
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const bool past = (q + u) * S + slot >= n;
@@ -141,7 +144,7 @@ __device__ inline void gather_chunk(float* acc, uint64_t Wbase, uint32_t row_byt
       if constexpr (WT) wt[u] = __shfl(wts, e, DLRM_WAVE);
       v[u] = load16_global(Wbase + (uint64_t)r * row_bytes);
     }
-    rows_requested<DT, G, WT>();
+    rows_requested<DT>();
 #pragma unroll
     for (int u = 0; u < U; ++u) add_row<DT, WT>(acc, v[u], wt[u]);
   }

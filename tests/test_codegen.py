@@ -129,17 +129,16 @@ def _rows_in_flight(lines, row):
 def test_pooling_by_wavefronts_requests_the_rows_of_a_round_together(tmp_path):
     """A wavefront per bag, alone or walking several: 16-bit rows of a round, of eight or of a bag's last rounds, are all requested
     before one is waited for (64 positions are at most G rounds of 64 / G rows; rows of 64 lanes are pooled by lane groups);
-    where the compiler is left to itself, more than half of them."""
+    where the compiler is left to itself, with fp32 rows, more than half of them."""
     asm = _assembly(tmp_path, "emb_fwd.hip", [])
     bodies = {n: b for n, b in _kernels(asm).items() if re.search(r"emb_fwd_wave(_seq)?_kernel", n)}
     assert len(bodies) == 2 * 3 * 7 * 2 * 2   # kernels, storage types, lanes per row, weights, index types
     for name, lines in bodies.items():
-        dtype, lanes, weighted = (int(x) for x in re.search(r"ILi(\d)ELi(\d+)ELi8ELb(\d)E", name).groups())
+        dtype, lanes = (int(x) for x in re.search(r"ILi(\d)ELi(\d+)ELi8E", name).groups())
         if lanes == 64:
             continue
         rounds = _rows_in_flight(lines, r"global_load_dwordx4 ")
-        held = dtype == 1 or (dtype == 2 and (weighted or lanes < 32))
-        assert all(total == most if held else 2 * most > total for total, most in rounds), (name, rounds)
+        assert all(total == most if dtype else 2 * most > total for total, most in rounds), (name, rounds)
         assert max(total for total, _ in rounds) >= min(8, lanes), (name, rounds)
 
 
