@@ -134,10 +134,11 @@ __global__ __launch_bounds__(kIntThreads) void interact_fwd_kernel(const float* 
 // deals the tiles evenly (seven blocks: seven each), and the dense row's products with them; all leave together.  Bound by the
 // chain of one sample at small batches, by memory at large ones (65 rows of 128 columns, batch 16384: 4.5 of the copy's 4.6 TB/s).
 // Three wavefronts per SIMD up to seven row blocks.  Eight would have 26 registers spilled by that, between the staged columns of
-// rows wider than kSplitCols; they have two.  A wavefront per sample / three to a SIMD / two, us: 128 rows of 256 columns, batch 1024 /
-// 4096 64.1 / 81.8 / 57.1, 263.5 / 284.5 / 210.5; of 96, 4096 135.7 / 147.5 / 110.5; 120 rows of 64, 16384 388 / 310 / 307; of 16, 300 /
-// 1024 / 2048 14.6 / 9.6 / 8.1, 16.5 / 17.3 / 15.2, 30.6 / 27.1 / 26.2.  Operands read from memory by each of the four wavefronts
-// instead of from LDS: 101 rows of 64, batch 16384 377 us for 209.7.
+// rows wider than kSplitCols; those have two.  A wavefront per sample / three to a SIMD / two, us: 128 rows of 256 columns, batch 1024 /
+// 4096 64.1 / 81.8 / 57.1, 263.5 / 284.5 / 210.5; of 96, 4096 135.7 / 147.5 / 110.5.  Rows of one stage have a kernel of their own
+// without the loop: no row waits in registers while others are multiplied, 84 of them, and the LDS sets the limit.  With the loop, three to
+// a SIMD / its own: 125 rows of 28, batch 506 11.2 / 9.7; 122 of 4, 5032 54.3 / 38.0; 128 of 64, 1257 30.7 / 27.9.  Operands read
+// from memory by each of the four wavefronts instead of from LDS: 101 rows of 64, batch 16384 377 us for 209.7.
 constexpr int kSplitCols = 64;
 // words of a staged row: whole 16-column chunks, and 4 words so that the 16 rows an operand is read from fall into 64 banks
 __host__ __device__ inline int split_stride(int d) { return (d < kSplitCols ? (d + 15) & ~15 : kSplitCols) + 4; }
@@ -207,9 +208,10 @@ __device__ inline void for_share(int w, F f) {
   }
 }
 
-template <int NB, int W>
-__global__ __launch_bounds__(W * DLRM_WAVE, NB < 8 ? 3 : 2) void interact_fwd_split_kernel(const float* __restrict__ T,
-                                                                                         float* __restrict__ R, int F, int d) {
+template <int NB, int W, bool WIDE>   // WIDE: rows of more than kSplitCols columns too
+__global__ __launch_bounds__(W * DLRM_WAVE, NB == 8 && WIDE ? 2 : 3) void interact_fwd_split_kernel(const float* __restrict__ T,
+                                                                                                  float* __restrict__ R, int F,
+                                                                                                  int d) {
   static_assert(W <= NB && NB <= 2 * W && (W == 2 || W == 4), "one or two row blocks a wavefront");
   constexpr int NT = W * DLRM_WAVE;
   constexpr int RP = NT / 16;                       // rows staged per pass, 16 bytes a lane
@@ -250,8 +252,11 @@ __global__ __launch_bounds__(W * DLRM_WAVE, NB < 8 ? 3 : 2) void interact_fwd_sp
       if (r < F && scol + 4 < cs) storef4(lds + r * cs + scol, k0 + scol < d ? v[p] : zero);   // columns past d contribute 0 * 0
     }
     __syncthreads();
-    if (k0 + kSplitCols < d) request(k0 + kSplitCols);   // on their way while these are multiplied
+    if constexpr (WIDE) {
+      if (k0 + kSplitCols < d) request(k0 + kSplitCols);   // on their way while these are multiplied
+    }
     for_share<NB, W>(w, [&](auto share) { share.products(lo, cs, d - k0, acc, pd); });
+    if constexpr (!WIDE) break;
   }
   for (int c = tl; c < d; c += NT) Rb[c] = Tb[c];  // dense part: exact copy of row 0
   __syncthreads();   // the staged rows have been read: the pairs take their place
@@ -606,8 +611,12 @@ static int launch_fwd_split(const float* T, float* R, int B, int F, int d, hipSt
   const int64_t row = (int64_t)F * d, res = (int64_t)d + F * (F - 1) / 2;
   for (int64_t b0 = 0; b0 < B; b0 += kTiledPerLaunch) {
     const int n = (int)(B - b0 < kTiledPerLaunch ? B - b0 : kTiledPerLaunch);
-    hipLaunchKernelGGL((interact_fwd_split_kernel<NB, W>), dim3(n), dim3(W * DLRM_WAVE), lds, st,
-                       T + b0 * row, R + b0 * res, F, d);
+    if (NB == 8 && d <= kSplitCols)
+      hipLaunchKernelGGL((interact_fwd_split_kernel<NB, W, NB != 8>), dim3(n), dim3(W * DLRM_WAVE), lds, st,
+                         T + b0 * row, R + b0 * res, F, d);
+    else
+      hipLaunchKernelGGL((interact_fwd_split_kernel<NB, W, true>), dim3(n), dim3(W * DLRM_WAVE), lds, st,
+                         T + b0 * row, R + b0 * res, F, d);
     DLRM_CHECK_LAUNCH();
   }
   return DLRM_OK;

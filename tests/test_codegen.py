@@ -168,8 +168,11 @@ def test_one_launch_forward_of_33_to_48_tables_keeps_four_wavefronts_per_simd(tm
 
 def test_interaction_forward_keeps_its_tiles_in_registers(tmp_path):
     """No row block count spills: staged rows wait in registers while the columns before them are multiplied."""
-    found = {n: v for n, v in _figures(_assembly(tmp_path, "interact.hip", []), "ScratchSize").items() if "interact_fwd" in n}
-    assert len(found) == 7 + 6 and not any(found.values()), found   # a wavefront per sample, several
+    asm = _assembly(tmp_path, "interact.hip", [])
+    found = {n: v for n, v in _figures(asm, "ScratchSize").items() if "interact_fwd" in n}
+    assert len(found) == 7 + 7 and not any(found.values()), found   # a wavefront per sample, several
+    narrow = [v for n, v in _occupancy(asm).items() if "interact_fwd_split_kernelILi8ELi4ELb0E" in n]   # no staged rows wait there
+    assert len(narrow) == 1 and narrow[0] >= 4, narrow   # workgroups that fit the LDS
 
 
 def test_sums_of_narrow_rows_read_several_pieces_of_a_run_together(tmp_path):
