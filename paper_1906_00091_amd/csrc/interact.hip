@@ -594,13 +594,20 @@ static int pair_stride(int F) {
 // lie: 81 rows of 8 columns, batch 1024 / 2048 8.7 / 7.4, 10.9 / 12.0; 49 rows of 8, 512 / 1024 4.8 / 4.4, 4.8 / 5.1; 66 of 32, 4096 /
 // 16384 25.1 / 22.8, 81.5 / 89.0; 34 of 32, 1024 / 4096 4.9 / 4.7, 10.0 / 11.5, of 64, 2048 / 16384 9.6 / 8.7, 49.3 / 49.8; 50 of 64, 2048 / 8192
 // 15.1 / 16.1, 46.9 / 45.5, of 128, 2048 / 4096 23.5 / 24.7, 43.9 / 40.1; 90 of 32, 1100 / 2048 / 4096 16.2 / 12.5, 17.9 / 19.5,
-// 34.9 / 33.5 (2048 wavefronts are two a SIMD, all that fit of the other kernel).
+// 34.9 / 33.5 (2048 wavefronts are two a SIMD, all that fit of the other kernel).  Three row blocks whose last stage is not full
+// lose between 2048 and 3072 samples, 4096 below 96 columns, where the other kernel's last wavefronts, one for every SIMD, are most
+// of 1024: 47 rows of 76 columns, 2242 / 2767 / 3470 / 5069 14.1 / 13.6, 15.2 / 16.7, 18.9 / 19.6, 27.9 / 25.3 (2900 batches: +2 to +9 %
+// in what is left out, -3 and more beside it).  One chunk of 16 columns in the last stage loses longer: 36 rows of 80, 4888
+// 20.1 / 22.1, 43 of 144, 2928 21.8 / 23.4.
 static bool split_fwd(int F, int nb, int B, int d) {
   if (B <= 512 || kIntWaves * pair_stride(F) * 4 > 80 * 1024) return true;
   if (d < 32) return nb >= 5 && B <= 1024;
   if (nb >= 6 || B <= 1024) return true;
   if (nb == 5) return d >= 64 || B <= 4096;
-  return d >= 64 && (nb == 3 || B >= (d > 64 ? 4096 : 8192));
+  if (nb == 4) return d >= 64 && B >= (d > 64 ? 4096 : 8192);
+  if (d < 64) return false;
+  if (d % kSplitCols == 0 || d > 144 || (B - 1) % 1024 < 384) return true;
+  return B <= 2048 || B > (d % kSplitCols == 16 ? (d < 96 ? 7168 : 4096) : d < 96 ? 4096 : 3072);
 }
 constexpr int kTiledPerLaunch = 1 << 23;   // samples: a launch holds fewer than 2^32 threads
 template <int NB>

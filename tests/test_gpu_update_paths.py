@@ -411,9 +411,12 @@ def test_interaction_forward_gives_the_same_bits_at_any_batch_size(F, d, B):
     assert np.max(np.abs(R[-2:].cpu().numpy() - ref) / np.maximum(scale, 1e-30)) <= d * 2.0 ** -24   # fp32 sums of d terms
 
 
-# ... and from 102 rows on, where it takes them for every batch
-@pytest.mark.parametrize("F,d,B", [(101, 20, 1025), (102, 20, 1025), (113, 4, 2049)])
-def test_interaction_forward_of_102_rows_and_more_gives_the_same_bits(F, d, B):
+# ... and from 102 rows on, where it takes them for every batch, with eight row blocks of rows of one stage and of more, and with three
+# row blocks on either side of batches that it leaves out
+@pytest.mark.parametrize("F,d,B", [(101, 20, 1025), (102, 20, 1025), (113, 4, 2049), (114, 4, 1025), (128, 64, 513), (121, 68, 513),
+                                   (47, 80, 2432), (47, 80, 2433), (47, 92, 4096), (47, 92, 4097), (49, 140, 3072), (49, 140, 3456),
+                                   (36, 80, 7168), (36, 80, 7169), (34, 144, 4096), (34, 144, 4481)])
+def test_interaction_forward_gives_the_same_bits_on_its_other_lines_too(F, d, B):
     test_interaction_forward_gives_the_same_bits_at_any_batch_size(F, d, B)
 
 
