@@ -614,14 +614,17 @@ inline int bits_for(int64_t nnz, int32_t K, double buckets, double most) {
 // Otherwise:
 // Narrow rows.  A bucket is mostly its sort, so fewer and larger ones take less, 70 skewed tables of 2864 lookups, d = 4 51.9 / 44.6
 // us an update, 50 uniform ones of 3526 37.7 / 32.7; but a hot row's bucket outgrows the LDS sort sooner, 13 skewed tables of
-// 10540, d = 16 36.3 / 49.7.  They are taken where neither uniform nor skewed lookups lose on average (4800 batches, mean of the
-// update uniform / skewed, by the bits of 128 pairs): up to 4 lanes 6 bits -12 / -9 %, 7 -9 / -1, 10 -17 / -1; 8 lanes 6 -9 / -5,
-// 10 -13 / -2.  Not 4 lanes 8 and 9 -11 / +4, -13 / +4 (one skewed one in five over 10 % behind); 8 lanes 7 -7 / +5, 8 -8 / +5.
+// 10540, d = 16 36.3 / 49.7.  They are taken where neither uniform nor skewed lookups lose on average over tables of one size and of
+// sizes over three decades (6700 batches; mean of the update uniform / skewed of one size, of many, by the bits of 128 pairs): up to 4
+// lanes 6 bits -12 / -9 %, -11 / +4, 10 -17 / -1, -16 / +1.  Not 7 -9 / -1, -8 / +13, 8 -11 / +4, -9 / +8, 9 -13 / +4, -11 / +5; 8 lanes
+// 6 -9 / -5, -9 / +8, 7 -7 / +5, -9 / +8; 10 -13 / -2, -16 / -3.
 // Wide rows.  A workgroup has few lane groups (four at 64 lanes), so a bucket of a given size takes it longer; one bit more, two at 64
 // lanes, lets the buckets end together and leaves a hot row less company: 36 skewed tables of 20708, d = 96 186 / 149; 12
 // uniform ones of 98814, d = 128 409 / 399; 36 skewed ones of 56105, d = 132 584 / 486.  The line is the mean bucket before the
 // bit from which uniform lookups do not lose (13800 batches of 2^16 to 4 M lookups; of those with the bit uniform ones are 2 to 5 %
-// ahead by width, skewed ones 8 to 13).  It is higher
+// ahead by width, skewed ones 8 to 13), beside a power of two rather than on it: 2^n samples with bags of 1..7 are 2^(n+2) lookups
+// of a table but for a few, which would give the same program one digit and the other by turns (100 fp16 tables of 1024 such bags, d = 32,
+// Adagrad 126 us a step with five bits, 130 by turns).  It is higher
 // - for 64 digits and fewer of 32 lanes, 79 uniform tables of 3785, d = 116 124.6 / 134.0;
 // - where tables have fewer rows than lookups, which a bucket adds up in LDS, 8 uniform ones of 43048 and 1975 rows, d = 96 46.9 / 53.3;
 // - for 512 digits (1024 at 64 lanes), every tile's counts growing with them, 8 uniform ones of 53677, d = 20 43.3 / 53.6; with more
@@ -629,7 +632,7 @@ inline int bits_for(int64_t nnz, int32_t K, double buckets, double most) {
 inline int digit_bits(int64_t nnz, int32_t K, int lanes, int64_t max_rows) {
   const int tb = bits_for(nnz, K, 1536.0, 128.0);
   if (nnz <= kSmallBatch) return tb;
-  if (lanes <= 8 && (tb <= (lanes < 8 ? 7 : 6) || tb == kMaxTopBits)) {
+  if (lanes <= 8 && (tb <= (lanes < 8 ? 6 : 5) || tb == kMaxTopBits)) {
     const int fewer = bits_for(nnz, K, 1536.0, lanes < 8 ? 224.0 : 192.0);
     if (fewer < tb) return fewer;
   }
@@ -639,7 +642,7 @@ inline int digit_bits(int64_t nnz, int32_t K, int lanes, int64_t max_rows) {
   int bits = tb;
   for (; bits < (lanes == 64 ? kMaxTopBits : kMaxTopBits - 1); ++bits) {
     const double mean = per_table / (double)(1 << bits);
-    double least = lanes == 64 ? 112.0 : lanes == 32 ? (bits < 6 ? 160.0 : 112.0) : lanes == 16 ? 200.0 : (bits < 6 ? 256.0 : 400.0);
+    double least = lanes == 64 ? 112.0 : lanes == 32 ? (bits < 6 ? 160.0 : 112.0) : lanes == 16 ? 200.0 : (bits < 6 ? 240.0 : 400.0);
     if (few_rows && lanes < 64) least *= 1.5;
     if (bits + 1 > (lanes == 64 ? 9 : 8) && (few_rows || lanes < 32)) least *= 2.0;
     if (mean < least || mean <= full) break;

@@ -164,14 +164,14 @@ def partition_bits(nnz: int, K: int, d: int, max_rows: int) -> int:
     lanes = 1 << max(0, (d // 4 - 1).bit_length())
     bits = fewest(128)
     if nnz > 65536:
-        larger = lanes <= 8 and (bits <= (6 if lanes == 8 else 7) or bits == 10)
+        larger = lanes <= 8 and (bits <= (5 if lanes == 8 else 6) or bits == 10)
         fewer = fewest(192 if lanes == 8 else 224) if larger else bits
         if fewer < bits:
             bits = fewer
         elif lanes >= 8:
             few_rows = nnz / K > max_rows
             while bits < (10 if lanes == 64 else 9):
-                least = {8: 256 if bits < 6 else 400, 16: 200, 32: 160 if bits < 6 else 112, 64: 112}[lanes]
+                least = {8: 240 if bits < 6 else 400, 16: 200, 32: 160 if bits < 6 else 112, 64: 112}[lanes]
                 least *= 1.5 if few_rows and lanes < 64 else 1
                 least *= 2 if bits >= (9 if lanes == 64 else 8) and (few_rows or lanes < 32) else 1
                 if nnz / K / 2 ** bits < least or nnz / K / 2 ** bits <= nnz / (4096 if lanes == 64 else 2560):

@@ -563,8 +563,8 @@ def test_partition_digits_by_row_width(K, per, d):
 # by narrow and by wide rows, with and without the column scan (more than 512 tiles); tables of fewer rows than digits among larger
 # ones, and alone
 @pytest.mark.parametrize("K,per,m,d,bits", [
-    (40, 3584, 20000, 4, 4), (40, 3585, 20000, 16, 5), (40, 3072, 20000, 28, 4), (40, 3073, 20000, 28, 5), (24, 4097, 20000, 28, 5), (10, 8192, 20000, 28, 6), (10, 8193, 20000, 28, 7),
-    (10, 8193, 20000, 16, 6), (6, 16385, 20000, 16, 8), (1, 114688, 20000, 4, 9),
+    (40, 3584, 20000, 4, 4), (40, 3585, 20000, 16, 5), (40, 3072, 20000, 28, 4), (40, 3073, 20000, 28, 5), (24, 4097, 20000, 28, 6), (12, 7168, 20000, 16, 5),
+    (12, 8193, 20000, 16, 7), (97, 3840, 20000, 28, 5), (97, 3839, 20000, 28, 4), (1, 114688, 20000, 4, 9),
     (13, 5043, 20000, 64, 6), (13, 5119, 20000, 100, 6), (13, 7168, 20000, 100, 7), (8, 8194, 20000, 132, 7), (13, 7168, 7168, 100, 7),
     (13, 7168, 7167, 100, 6), (8, 8194, 20000, 100, 7), (8, 8194, 37, 100, 6), (1, 120000, 20000, 4, 10), (1, 120000, 20000, 100, 10),
     (1, 120000, 37, 28, 6), (4, 114688, 30000, 132, 10), (4, 114687, 30000, 132, 9), (2, 57344, 60000, 132, 10), (2, 57343, 60000, 132, 9), (4, 164000, 30000, 132, 10)])

@@ -41,12 +41,13 @@ def library_bits(tmp_path_factory):
 @pytest.mark.parametrize("batch,bits", [
     # small batches: buckets of 128 pairs whatever the width
     ((2048, 32, 256, 10 ** 6), 4), ((2048, 32, 4, 10 ** 6), 4), ((65536, 1, 64, 10 ** 6), 9),
-    # narrow rows: of 224 (192 at eight lanes) where buckets of 128 take seven bits (six) or fewer, or ten
+    # narrow rows: of 224 (192 at eight lanes) where buckets of 128 take six bits (five) or fewer, or ten
     ((224 * 16, 40, 16, 10 ** 6), 4), ((224 * 16 + 1, 40, 16, 10 ** 6), 5), ((112 * 32, 40, 20, 10 ** 6), 5), ((96 * 32, 40, 20, 10 ** 6), 4),
-    ((128 * 64, 12, 20, 10 ** 6), 6), ((128 * 64 + 1, 12, 20, 10 ** 6), 7), ((128 * 128, 6, 16, 10 ** 6), 7), ((128 * 128 + 1, 6, 16, 10 ** 6), 8),
-    ((128 * 512, 2, 16, 10 ** 6), 9), ((128 * 512 + 1, 2, 16, 10 ** 6), 9), ((224 * 512 + 1, 1, 16, 10 ** 6), 10), ((192 * 512, 1, 20, 10 ** 6), 9), ((192 * 512 + 1, 1, 20, 10 ** 6), 10),
+    ((128 * 32, 24, 16, 10 ** 6), 5), ((128 * 32 + 1, 24, 20, 10 ** 6), 6), ((128 * 64, 12, 16, 10 ** 6), 6), ((224 * 32, 12, 16, 10 ** 6), 5),
+    ((128 * 64 + 1, 12, 16, 10 ** 6), 7), ((128 * 512, 2, 16, 10 ** 6), 9), ((128 * 512 + 1, 2, 16, 10 ** 6), 9), ((224 * 512 + 1, 1, 16, 10 ** 6), 10),
+    ((192 * 512, 1, 20, 10 ** 6), 9), ((192 * 512 + 1, 1, 20, 10 ** 6), 10),
     # wide rows: a bit more from a mean bucket on
-    ((256 * 16 - 1, 100, 32, 10 ** 6), 4), ((256 * 16, 100, 32, 10 ** 6), 5), ((400 * 64 - 1, 25, 32, 10 ** 6), 6), ((400 * 64, 25, 32, 10 ** 6), 7),
+    ((240 * 16 - 1, 100, 32, 10 ** 6), 4), ((240 * 16, 100, 32, 10 ** 6), 5), ((400 * 64 - 1, 25, 32, 10 ** 6), 6), ((400 * 64, 25, 32, 10 ** 6), 7),
     ((200 * 64 - 1, 26, 64, 10 ** 6), 6), ((200 * 64, 26, 64, 10 ** 6), 7),
     ((160 * 32 - 1, 50, 128, 10 ** 6), 5), ((3785, 79, 116, 10 ** 6), 5), ((160 * 32, 50, 128, 10 ** 6), 6), ((112 * 64 - 1, 26, 128, 10 ** 6), 6), ((112 * 64, 26, 128, 10 ** 6), 7),
     ((112 * 32 - 1, 50, 256, 10 ** 6), 5), ((112 * 32, 50, 256, 10 ** 6), 6),
