@@ -623,8 +623,7 @@ inline int bits_for(int64_t nnz, int32_t K, double buckets, double most) {
 // uniform ones of 98814, d = 128 409 / 399; 36 skewed ones of 56105, d = 132 584 / 486.  The line is the mean bucket before the
 // bit from which uniform lookups do not lose (13800 batches of 2^16 to 4 M lookups; of those with the bit uniform ones are 2 to 5 %
 // ahead by width, skewed ones 8 to 13), beside a power of two rather than on it: 2^n samples with bags of 1..7 are 2^(n+2) lookups
-// of a table but for a few, which would give the same program one digit and the other by turns (100 fp16 tables of 1024 such bags, d = 32,
-// Adagrad 126 us a step with five bits, 130 by turns).  It is higher
+// of a table but for a few, which would give the same program one digit and the other by turns.  It is higher
 // - for 64 digits and fewer of 32 lanes, 79 uniform tables of 3785, d = 116 124.6 / 134.0;
 // - where tables have fewer rows than lookups, which a bucket adds up in LDS, 8 uniform ones of 43048 and 1975 rows, d = 96 46.9 / 53.3;
 // - for 512 digits (1024 at 64 lanes), every tile's counts growing with them, 8 uniform ones of 53677, d = 20 43.3 / 53.6; with more
